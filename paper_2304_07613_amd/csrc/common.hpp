@@ -164,6 +164,11 @@ nmg_status check_p_layout(const nmg_p_layout *L);
 int p_pattern_count(int m, int n);
 nmg_status launch_p_compress(const nmg_p_layout *L, const void *W, int64_t ldw, void *values,
                              uint8_t *index, hipStream_t stream);
+// the converters for few patterns, rows in registers (k_chunked_pack.hip);
+// swaps: the swap search instead of the greedy
+bool p_pack_rows_supported(const nmg_p_layout *L, bool swaps);
+nmg_status p_pack_rows(const nmg_p_layout *L, const void *W, int64_t ldw, void *values,
+                       uint8_t *index, bool swaps, hipStream_t stream);
 nmg_status launch_p_densify(const nmg_p_layout *L, const void *values, const uint8_t *index,
                             void *W_out, int64_t ldw, hipStream_t stream);
 nmg_status launch_p_refine(const nmg_p_layout *L, const void *W, int64_t ldw, void *values,

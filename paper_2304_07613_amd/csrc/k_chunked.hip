@@ -12,6 +12,8 @@
 //                 lower row) -- the same pairs, in the same order, as scanning
 //                 the sorted list of all pairs, since a pair that is not
 //                 eligible never becomes eligible again.
+//                 (Layouts of at most 8 patterns of at most 8 columns take the
+//                 converters of k_chunked_pack.hip instead of these.)
 //   k_p_compress_w the same greedy for chunks of at most 1536 (row, pattern)
 //                 pairs: one wave per chunk, each lane holding up to 24 pairs'
 //                 keys in registers with a mask of the pairs still eligible;
@@ -48,7 +50,7 @@
 //                 row) and mutual best partners swap, until no swap improves
 //                 (at most 8 * S rounds).  Gains are symmetric, so while a swap
 //                 improves there is a mutual pair.
-#include "common.hpp"
+#include "chunked.hpp"
 
 namespace {
 
@@ -60,36 +62,6 @@ constexpr int kPRowsWave = 16;
 constexpr int kPTokens = 256;      // 4 per lane
 constexpr int kPWin = 32;          // block columns per inverse table
 constexpr int kPStageRows = 32;    // X rows staged per window by k_p_spmm (256 tokens each)
-
-__host__ __device__ inline int p_binom(int m, int n) {
-    int64_t v = 1;
-    for (int i = 1; i <= n; ++i) {
-        v = v * (m - n + i) / i;
-        if (v > 4096) return 4097;
-    }
-    return (int)v;
-}
-
-// Offsets (ascending) of pattern `idx` of the revolving-door list of the
-// n-subsets of {0 .. m-1}: the list of (m, n) is the list of (m-1, n)
-// followed by the list of (m-1, n-1) reversed, each with m-1 added; (m, m)
-// holds the single full set.  Unranked from the top: every binomial on the way
-// is at most C(m, n).
-__device__ void p_unrank(int m, int n, int idx, uint8_t *out) {
-    while (n > 0) {
-        if (n == m) {
-            for (int i = 0; i < n; ++i) out[i] = (uint8_t)i;
-            return;
-        }
-        const int first = p_binom(m - 1, n);
-        if (idx >= first) {  // in the second half: m-1 is in the pattern
-            idx = p_binom(m - 1, n - 1) - 1 - (idx - first);
-            out[n - 1] = (uint8_t)(m - 1);
-            --n;
-        }
-        --m;
-    }
-}
 
 template <typename T>
 __device__ __forceinline__ float p_abs(const T *p) { return fabsf((float)*p); }
@@ -169,13 +141,6 @@ constexpr int kPwWaves = 4;
 constexpr int kPwPairs = 24;       // pairs per lane, at most (the live mask is 32 bits)
 constexpr int kPwWblk = 1024;      // S * m weights per chunk
 constexpr int kPwPat = 1024;       // P * n pattern offsets per chunk
-
-__device__ __forceinline__ void p_wave_sync() {
-    // this wave's LDS writes are done before its later LDS reads
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // PP pairs per lane (16 for chunks of up to 1024 pairs, else kPwPairs: every
 // step scans all PP, so small chunks take the smaller PP).
@@ -790,6 +755,7 @@ int p_pattern_count(int m, int n) { return p_binom(m, n); }
 nmg_status launch_p_compress(const nmg_p_layout *L, const void *W, int64_t ldw, void *values,
                              uint8_t *index, hipStream_t stream) {
     if (!p_fits(L)) return NMG_ERR_UNSUPPORTED;
+    if (p_pack_rows_supported(L, false)) return p_pack_rows(L, W, ldw, values, index, false, stream);
     const int64_t chunks = (int64_t)(L->M / L->S) * L->B;
     if (L->S * L->P <= 64 * kPwPairs && L->S * L->m <= kPwWblk && L->P * L->n <= kPwPat &&
         chunks <= INT32_MAX - kPwWaves) {
@@ -823,6 +789,7 @@ nmg_status launch_p_compress(const nmg_p_layout *L, const void *W, int64_t ldw, 
 nmg_status launch_p_refine(const nmg_p_layout *L, const void *W, int64_t ldw, void *values,
                            uint8_t *index, hipStream_t stream) {
     if (!p_fits(L)) return NMG_ERR_UNSUPPORTED;
+    if (p_pack_rows_supported(L, true)) return p_pack_rows(L, W, ldw, values, index, true, stream);
     const int64_t chunks = (int64_t)(L->M / L->S) * L->B;
     if (L->S * L->P <= 64 * kPwPairs && L->S * L->m <= kPwWblk && L->P * L->n <= kPwPat &&
         chunks <= INT32_MAX - kPwWaves) {

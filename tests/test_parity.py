@@ -905,3 +905,34 @@ def test_chunked_swap_search(nmg, M, K, N, n, m, g, dtype):
         rv, ridx, rounds = oracle.p_refine(np_of(W), np_of(start), n, m, g)
         assert np.array_equal(np_of(ridx_g), ridx), name
         assert np.array_equal(bits(np_of(rv_g)), bits(rv)), name
+
+
+# the converters with whole rows in registers: several chunks on a wave (S <=
+# 32), one (33 .. 64), rows over 2, 3 and 4 registers, patterns of 4 and of up
+# to 8 columns, groups the swap search's lane segments do not take (3, 5)
+@pytest.mark.parametrize("kind", ["normal", "ties", "mid", "wide", "zeros", "f16ties"])
+@pytest.mark.parametrize("n,m,g", [(2, 4, 1), (2, 4, 5), (1, 4, 3), (1, 8, 4), (2, 4, 8), (1, 4, 16),
+                                   (5, 6, 16), (1, 4, 32), (2, 4, 32), (1, 3, 64), (3, 4, 64), (7, 8, 32)])
+def test_chunked_few_patterns(nmg, n, m, g, kind):
+    rng = np.random.RandomState(100 * n + 10 * m + g)
+    S = math_comb(m, n) * g
+    M, K = 2 * S, 7 * m
+    W = (rng.randn(M, K) * 0.02).astype(np.float32)
+    if kind in ("ties", "f16ties"):
+        W = (rng.randint(-3, 4, size=(M, K)) / 2).astype(np.float16 if kind == "f16ties" else np.float32)
+    elif kind == "mid":      # ties in the range that keeps gain and row apart
+        W = (rng.randint(-3, 4, size=(M, K)) / 2 * np.exp2(rng.choice([0, 22], size=(M, K)))).astype(np.float32)
+    elif kind == "wide":     # magnitudes too far apart for whole multiples of the smallest unit
+        W = (W * np.exp2(rng.randint(-30, 30, size=(M, K)))).astype(np.float32)
+    elif kind == "zeros":
+        W[rng.rand(M, K) < 0.6] = 0
+    Wd = torch.from_numpy(W).to(DEV)
+    print(f"[chunked rows] {n}:{m}:{g} {kind}", flush=True)
+    v, idx, L = nmg.p_compress(Wd, n, m, g)
+    torch.cuda.synchronize()
+    rv, ridx = oracle.p_compress(W, n, m, g)
+    assert np.array_equal(np_of(idx), ridx) and np.array_equal(bits(np_of(v)), bits(rv))
+    v, idx = nmg.p_refine(Wd, idx, L)
+    torch.cuda.synchronize()
+    rv, ridx, _ = oracle.p_refine(W, ridx, n, m, g)
+    assert np.array_equal(np_of(idx), ridx) and np.array_equal(bits(np_of(v)), bits(rv))
