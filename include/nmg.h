@@ -145,7 +145,7 @@ typedef enum nmg_kernel {
     NMG_KERNEL_MFMA_SPLIT = 10,  /* binary32 layouts on the same binary16
                                     instruction, each operand carried as two
                                     binary16 parts (see nmg_spmm_x16)         */
-    NMG_KERNEL_MFMA_EXPAND = 11  /* the matrix cores for groups they cannot
+    NMG_KERNEL_MFMA_EXPAND = 11, /* the matrix cores for groups they cannot
                                     share (g % 4 != 0, n not a power of two):
                                     W_s written out dense (zeros elsewhere)
                                     into scratch memory (M K elements + K
@@ -156,6 +156,19 @@ typedef enum nmg_kernel {
                                     reaches every output of its token, as in a
                                     dense product; needs M % 4 == 0 and
                                     M K < 2^31                               */
+    NMG_KERNEL_SPARSE = 12       /* gfx950's sparse matrix instructions on a
+                                    weight stream made in scratch memory on
+                                    every call (stream-ordered; 3.25 bytes per
+                                    entry of W for binary32, 1.25 for
+                                    binary16): any g, any alignment, any N;
+                                    needs n = 1 (m >= 2) or n = 2 with m % 4
+                                    == 0.  Binary32 operands are carried
+                                    exactly as three bfloat16 numbers and
+                                    summed in binary32 from the six leading
+                                    part products; results that are not finite
+                                    or below 2^-80 in magnitude are recomputed
+                                    as binary32 multiply-adds over the kept
+                                    columns                                   */
 } nmg_kernel;
 /* With n == m every column is kept and every index row is 0 .. m-1, so the
  * matrix-core kernels treat the weight as one group whatever g is. */
@@ -253,7 +266,28 @@ nmg_status nmg_spmm_epilogue_noalloc(const nmg_layout *layout, nmg_kernel kernel
                                      int64_t N, const void *R, int64_t ldr, void *Y,
                                      int64_t ldy, hipStream_t stream);
 
-/* The kernel family NMG_KERNEL_AUTO picks for this layout and N, assuming
+/* nmg_spmm_epilogue with scratch memory from the caller: same arguments, and
+ * `workspace` (device, 256-byte aligned, `workspace_bytes` long, the call's
+ * alone until its work on `stream` is done; may be NULL) serves the families
+ * with scratch memory when it is large enough, in place of a stream-ordered
+ * allocation.  With NMG_KERNEL_AUTO it also lets the library take
+ * NMG_KERNEL_SPARSE for layouts whose choice without a workspace has no
+ * scratch memory (other summation order, same error bounds). */
+nmg_status nmg_spmm_epilogue_ws(const nmg_layout *layout, nmg_kernel kernel, nmg_epilogue epilogue,
+                                const void *values, const uint8_t *indices, const void *X,
+                                int64_t ldx, int64_t N, const void *R, int64_t ldr, void *Y,
+                                int64_t ldy, void *workspace, int64_t workspace_bytes,
+                                hipStream_t stream);
+
+/* Bytes of workspace that serve nmg_spmm_epilogue_ws for this layout, kernel
+ * and N whatever the alignment of X; 0 when the call needs and would use none
+ * (or the arguments are invalid).  Pure host code. */
+int64_t nmg_spmm_workspace_bytes(const nmg_layout *layout, nmg_kernel kernel, int64_t N);
+
+/* The kernel family NMG_KERNEL_AUTO picks for this layout and N without
+ * scratch memory for NMG_KERNEL_SPARSE (which it takes instead of
+ * NMG_KERNEL_MFMA_EXPAND for the layouts that kernel takes, and instead of
+ * others where nmg_spmm_epilogue_ws brings a workspace), assuming
  * 16-byte aligned X, 4-byte aligned indices and ldx = N (never
  * NMG_KERNEL_MFMA; NMG_KERNEL_AUTO only for an invalid layout). */
 nmg_kernel nmg_spmm_auto_kernel(const nmg_layout *layout, int64_t N);
@@ -414,6 +448,17 @@ nmg_status nmg_p_spmm(const nmg_p_layout *layout, const void *values, const uint
 nmg_status nmg_p_spmm_with(const nmg_p_layout *layout, nmg_kernel kernel, const void *values,
                            const uint8_t *index, const void *X, int64_t ldx, int64_t N, void *Y,
                            int64_t ldy, hipStream_t stream);
+
+/* nmg_p_spmm_with with scratch memory from the caller (device, 256-byte
+ * aligned, may be NULL), which lets NMG_KERNEL_AUTO take gfx950's sparse
+ * matrix instructions (n <= 2 of m in {4, 8, 16}; see NMG_KERNEL_SPARSE);
+ * nmg_p_spmm_workspace_bytes: the bytes it needs for this N, 0 when it would
+ * use none.  Pure host code. */
+nmg_status nmg_p_spmm_ws(const nmg_p_layout *layout, nmg_kernel kernel, const void *values,
+                         const uint8_t *index, const void *X, int64_t ldx, int64_t N, void *Y,
+                         int64_t ldy, void *workspace, int64_t workspace_bytes,
+                         hipStream_t stream);
+int64_t nmg_p_spmm_workspace_bytes(const nmg_p_layout *layout, nmg_kernel kernel, int64_t N);
 
 /* Chunked layout -> dense W_out (M x K, leading dimension ldw >= K). */
 nmg_status nmg_p_densify(const nmg_p_layout *layout, const void *values, const uint8_t *index,

@@ -83,6 +83,24 @@ int kernel_occupancy(const void *kernel, int threads) {
 
 using namespace nmg_internal;
 
+namespace {
+
+// The family AUTO (or MFMA) stands for without scratch memory for the sparse
+// matrix instructions; values, indices and X may be NULL (taken as aligned)
+nmg_kernel auto_family(const nmg_layout *L, nmg_kernel requested, const void *values,
+                       const uint8_t *indices, const void *X, int64_t ldx, int64_t N) {
+    return spmm_half_supported(L, X, ldx, N) ? NMG_KERNEL_MFMA_F16
+           : spmm_smfmac_supported(L, values, indices, X, ldx, N) ? NMG_KERNEL_SMFMAC_F16
+           : spmm_direct_preferred(L, N, ldx) ? NMG_KERNEL_MFMA_DIRECT
+           : spmm_scalar_supported(L, indices, ldx) ? NMG_KERNEL_MFMA_SCALAR
+           : spmm_general_supported(L, N) || requested == NMG_KERNEL_MFMA ? NMG_KERNEL_MFMA_GENERAL
+           : expand_preferred(L, ldx) ? NMG_KERNEL_MFMA_EXPAND
+           : spmm_valu_staged_preferred(L, X, ldx, N) ? NMG_KERNEL_VALU_STAGED
+                                                      : NMG_KERNEL_VALU;
+}
+
+}  // namespace
+
 extern "C" {
 
 nmg_status nmg_layout_init(nmg_layout *layout, int32_t M, int32_t K, int32_t n, int32_t m,
@@ -144,13 +162,7 @@ nmg_kernel nmg_spmm_auto_kernel(const nmg_layout *L, int64_t N) {
         dense.g = L->M;
         L = &dense;
     }
-    if (spmm_half_supported(L, nullptr, N, N)) return NMG_KERNEL_MFMA_F16;
-    if (spmm_smfmac_supported(L, nullptr, nullptr, nullptr, N, N)) return NMG_KERNEL_SMFMAC_F16;
-    if (spmm_direct_preferred(L, N, N)) return NMG_KERNEL_MFMA_DIRECT;
-    if (spmm_scalar_supported(L, nullptr, N)) return NMG_KERNEL_MFMA_SCALAR;
-    if (spmm_general_supported(L, N)) return NMG_KERNEL_MFMA_GENERAL;
-    if (expand_preferred(L, N)) return NMG_KERNEL_MFMA_EXPAND;
-    return spmm_valu_staged_preferred(L, nullptr, N, N) ? NMG_KERNEL_VALU_STAGED : NMG_KERNEL_VALU;
+    return auto_family(L, NMG_KERNEL_AUTO, nullptr, nullptr, nullptr, N, N);
 }
 
 nmg_status nmg_spmm_with(const nmg_layout *L, nmg_kernel kernel, const void *values,
@@ -165,7 +177,18 @@ nmg_status nmg_spmm_epilogue(const nmg_layout *L, nmg_kernel kernel, nmg_epilogu
                              int64_t ldx, int64_t N, const void *R, int64_t ldr, void *Y,
                              int64_t ldy, hipStream_t stream) {
     return spmm_epilogue_ws(L, kernel, epi, values, indices, X, ldx, N, R, ldr, Y, ldy, stream,
-                            nullptr);
+                            Scratch{});
+}
+
+nmg_status nmg_spmm_epilogue_ws(const nmg_layout *L, nmg_kernel kernel, nmg_epilogue epi,
+                                const void *values, const uint8_t *indices, const void *X,
+                                int64_t ldx, int64_t N, const void *R, int64_t ldr, void *Y,
+                                int64_t ldy, void *workspace, int64_t workspace_bytes,
+                                hipStream_t stream) {
+    if (workspace_bytes < 0) return NMG_ERR_PARAM;
+    if (workspace && !aligned(workspace, 256)) return NMG_ERR_ALIGN;
+    return spmm_epilogue_ws(L, kernel, epi, values, indices, X, ldx, N, R, ldr, Y, ldy, stream,
+                            Scratch{nullptr, workspace, workspace ? workspace_bytes : 0, 0});
 }
 
 }  // extern "C"
@@ -185,9 +208,10 @@ nmg_layout expanded_layout(const nmg_layout *L) {
 
 constexpr int64_t round256(int64_t b) { return (b + 255) / 256 * 256; }
 
-// Scratch memory from the caller's source, else in stream order
-void *take_scratch(scratch_source src, int64_t bytes, hipStream_t stream, nmg_status *st) {
-    if (src) return src(bytes, stream, st);
+// Scratch memory: the caller's workspace, its source, else in stream order
+void *take_scratch(const Scratch &src, int64_t bytes, hipStream_t stream, nmg_status *st) {
+    if (src.workspace && bytes <= src.workspace_bytes) return src.workspace;
+    if (src.source) return src.source(bytes, stream, st);
     void *p = nullptr;
     if (hipMallocAsync(&p, (size_t)bytes, stream) != hipSuccess || p == nullptr) {
         (void)hipGetLastError();
@@ -197,8 +221,8 @@ void *take_scratch(scratch_source src, int64_t bytes, hipStream_t stream, nmg_st
     return p;
 }
 
-nmg_status give_back_scratch(scratch_source src, void *p, hipStream_t stream, nmg_status st) {
-    if (!src && hipFreeAsync(p, stream) != hipSuccess) {
+nmg_status give_back_scratch(const Scratch &src, void *p, hipStream_t stream, nmg_status st) {
+    if (!src.source && p != src.workspace && hipFreeAsync(p, stream) != hipSuccess) {
         (void)hipGetLastError();
         if (st == NMG_OK) st = NMG_ERR_LAUNCH;
     }
@@ -275,7 +299,7 @@ nmg_status nmg_internal::spmm_epilogue_ws(const nmg_layout *L, nmg_kernel kernel
                                           const void *values, const uint8_t *indices,
                                           const void *X, int64_t ldx, int64_t N, const void *R,
                                           int64_t ldr, void *Y, int64_t ldy, hipStream_t stream,
-                                          scratch_source scratch) {
+                                          const Scratch &scratch) {
     nmg_status st = check_layout(L);
     if (st != NMG_OK) return st;
     if (!values || !indices || !X || !Y) return NMG_ERR_NULL;
@@ -300,17 +324,21 @@ nmg_status nmg_internal::spmm_epilogue_ws(const nmg_layout *L, nmg_kernel kernel
     SpmmArgs a{L, values, indices, X, ldx, (int)N, Y, ldy, stream};
     const bool half_ok = spmm_half_supported(L, X, ldx, N);
     const bool scalar_ok = spmm_scalar_supported(L, indices, ldx);
+    const nmg_kernel requested = kernel;
     if (kernel == NMG_KERNEL_AUTO || kernel == NMG_KERNEL_MFMA) {
-        const bool direct = spmm_direct_preferred(L, N, ldx);
-        kernel = half_ok     ? NMG_KERNEL_MFMA_F16
-                 : spmm_smfmac_supported(L, values, indices, X, ldx, N) ? NMG_KERNEL_SMFMAC_F16
-                 : direct    ? NMG_KERNEL_MFMA_DIRECT
-                 : scalar_ok ? NMG_KERNEL_MFMA_SCALAR
-                 : spmm_general_supported(L, N) || kernel == NMG_KERNEL_MFMA
-                     ? NMG_KERNEL_MFMA_GENERAL
-                 : expand_preferred(L, ldx) ? NMG_KERNEL_MFMA_EXPAND
-                 : spmm_valu_staged_preferred(L, X, ldx, N) ? NMG_KERNEL_VALU_STAGED
-                                                              : NMG_KERNEL_VALU;
+        kernel = auto_family(L, kernel, values, indices, X, ldx, N);
+        // the sparse matrix instructions where their scratch memory is at
+        // hand: in the caller's workspace, or where the choice has scratch
+        // memory anyway (never from the shared array of the allocation-free
+        // entry point for a call that used none)
+        if (requested == NMG_KERNEL_AUTO && sp_layout_supported(L) &&
+            sp_args_supported(L->dtype, L->M, L->K, ldx, N) && sp_preferred(L, kernel, epi, N)) {
+            const int64_t need = sp_stream_bytes(L->dtype, L->M, L->K, N);
+            const bool own = scratch.workspace && need <= scratch.workspace_bytes;
+            const bool instead = kernel == NMG_KERNEL_MFMA_EXPAND &&
+                                 (!scratch.source || need <= scratch.source_bytes);
+            if (own || instead) kernel = NMG_KERNEL_SPARSE;
+        }
     }
     switch (kernel) {
         case NMG_KERNEL_MFMA_F16:
@@ -372,6 +400,20 @@ nmg_status nmg_internal::spmm_epilogue_ws(const nmg_layout *L, nmg_kernel kernel
                                       Y, ldy, stream, scratch);
             return give_back_scratch(scratch, ws, stream, st);
         }
+        case NMG_KERNEL_SPARSE: {
+            if (!sp_layout_supported(L) || !sp_args_supported(L->dtype, L->M, L->K, ldx, N))
+                return NMG_ERR_UNSUPPORTED;
+            // the weight stream lives for this call only; ADD is folded in
+            a.epi = epi;
+            a.R = R;
+            a.ldr = ldr;
+            void *ws = take_scratch(scratch, sp_stream_bytes(L->dtype, L->M, L->K, N), stream, &st);
+            if (!ws) return st;
+            st = spmm_sp(a, ws);
+            st = give_back_scratch(scratch, ws, stream, st);
+            if (epi == NMG_EPILOGUE_ADD) return st;
+            break;
+        }
         default:
             return NMG_ERR_PARAM;
     }
@@ -427,9 +469,10 @@ nmg_status nmg_p_refine(const nmg_p_layout *L, const void *W, int64_t ldw, void 
     return launch_p_refine(L, W, ldw, values, index, stream);
 }
 
-nmg_status nmg_p_spmm_with(const nmg_p_layout *L, nmg_kernel kernel, const void *values,
-                           const uint8_t *index, const void *X, int64_t ldx, int64_t N, void *Y,
-                           int64_t ldy, hipStream_t stream) {
+namespace {
+nmg_status p_spmm_checked(const nmg_p_layout *L, nmg_kernel kernel, const void *values,
+                          const uint8_t *index, const void *X, int64_t ldx, int64_t N, void *Y,
+                          int64_t ldy, void *ws, int64_t ws_bytes, hipStream_t stream) {
     nmg_status st = check_p_layout(L);
     if (st != NMG_OK) return st;
     if (kernel != NMG_KERNEL_AUTO && kernel != NMG_KERNEL_VALU && kernel != NMG_KERNEL_MFMA)
@@ -439,13 +482,64 @@ nmg_status nmg_p_spmm_with(const nmg_p_layout *L, nmg_kernel kernel, const void 
     const size_t es = elem_size(L->dtype);
     if (!aligned(X, es) || !aligned(values, es) || !aligned(Y, es)) return NMG_ERR_ALIGN;
     prelaunch();
-    return launch_p_spmm(L, kernel, values, index, X, ldx, (int)N, Y, ldy, stream);
+    return launch_p_spmm(L, kernel, values, index, X, ldx, (int)N, Y, ldy, ws, ws_bytes, stream);
+}
+}  // namespace
+
+nmg_status nmg_p_spmm_with(const nmg_p_layout *L, nmg_kernel kernel, const void *values,
+                           const uint8_t *index, const void *X, int64_t ldx, int64_t N, void *Y,
+                           int64_t ldy, hipStream_t stream) {
+    return p_spmm_checked(L, kernel, values, index, X, ldx, N, Y, ldy, nullptr, 0, stream);
 }
 
 nmg_status nmg_p_spmm(const nmg_p_layout *L, const void *values, const uint8_t *index,
                       const void *X, int64_t ldx, int64_t N, void *Y, int64_t ldy,
                       hipStream_t stream) {
     return nmg_p_spmm_with(L, NMG_KERNEL_AUTO, values, index, X, ldx, N, Y, ldy, stream);
+}
+
+nmg_status nmg_p_spmm_ws(const nmg_p_layout *L, nmg_kernel kernel, const void *values,
+                         const uint8_t *index, const void *X, int64_t ldx, int64_t N, void *Y,
+                         int64_t ldy, void *workspace, int64_t workspace_bytes,
+                         hipStream_t stream) {
+    if (workspace_bytes < 0) return NMG_ERR_PARAM;
+    if (workspace && !aligned(workspace, 256)) return NMG_ERR_ALIGN;
+    return p_spmm_checked(L, kernel, values, index, X, ldx, N, Y, ldy, workspace,
+                          workspace ? workspace_bytes : 0, stream);
+}
+
+int64_t nmg_p_spmm_workspace_bytes(const nmg_p_layout *L, nmg_kernel kernel, int64_t N) {
+    if (check_p_layout(L) != NMG_OK || N < 1) return 0;
+    return p_workspace_bytes(L, kernel, N);
+}
+
+int64_t nmg_spmm_workspace_bytes(const nmg_layout *L, nmg_kernel kernel, int64_t N) {
+    if (check_layout(L) != NMG_OK || N < 1) return 0;
+    nmg_layout dense;
+    L = effective_layout(L, &dense);
+    const bool sp = sp_layout_supported(L) && sp_args_supported(L->dtype, L->M, L->K, N, N);
+    switch (kernel) {
+        case NMG_KERNEL_AUTO: {
+            // the most that aligned and merely element-aligned buffers lead to
+            int64_t b = 0;
+            for (const uintptr_t at : {(uintptr_t)0, (uintptr_t)elem_size(L->dtype)}) {
+                const uint8_t *p = reinterpret_cast<const uint8_t *>(at);
+                const nmg_kernel f = auto_family(L, kernel, p, p, p, N, N);
+                if (sp && sp_preferred(L, f, NMG_EPILOGUE_NONE, N))
+                    b = std::max(b, sp_stream_bytes(L->dtype, L->M, L->K, N));
+                else if (f == NMG_KERNEL_MFMA_EXPAND)
+                    b = std::max(b, expand_scratch_bytes(L));
+            }
+            return b;
+        }
+        case NMG_KERNEL_MFMA_WIDE:
+        case NMG_KERNEL_MFMA_SPLIT:
+            return (kernel == NMG_KERNEL_MFMA_SPLIT) == (L->dtype == NMG_F32)
+                       ? std::max<int64_t>(x16_prepared_bytes(L), 0) : 0;
+        case NMG_KERNEL_MFMA_EXPAND: return expand_supported(L, N) ? expand_scratch_bytes(L) : 0;
+        case NMG_KERNEL_SPARSE: return sp ? sp_stream_bytes(L->dtype, L->M, L->K, N) : 0;
+        default: return 0;
+    }
 }
 
 nmg_status nmg_p_densify(const nmg_p_layout *L, const void *values, const uint8_t *index,

@@ -2,10 +2,11 @@
 // allocate device memory (code under HIP graph capture, serving loops,
 // harnesses that forbid allocation).
 //
-// The library's products have scratch memory in two families: the prepared
+// The library's products have scratch memory in these families: the prepared
 // operands that the 16 x 16 x 32 products (NMG_KERNEL_MFMA_WIDE / _SPLIT) make
 // from the packed weight, and the dense weight of the expanded product
-// (NMG_KERNEL_MFMA_EXPAND, also an NMG_KERNEL_AUTO choice), made on every
+// (NMG_KERNEL_MFMA_EXPAND, also an NMG_KERNEL_AUTO choice, or the weight stream
+// of NMG_KERNEL_SPARSE that AUTO takes in its place), made on every
 // nmg_spmm_epilogue call in a stream-ordered allocation.  Here they go to one
 // fixed array in device memory instead, a copy of it on every GPU the library
 // runs on, held until the process ends.  Each family writes every byte of the
@@ -90,5 +91,5 @@ nmg_status nmg_spmm_epilogue_noalloc(const nmg_layout *L, nmg_kernel kernel, nmg
                                      int64_t ldx, int64_t N, const void *R, int64_t ldr, void *Y,
                                      int64_t ldy, hipStream_t stream) {
     return spmm_epilogue_ws(L, kernel, epi, values, indices, X, ldx, N, R, ldr, Y, ldy, stream,
-                            fixed_scratch);
+                            Scratch{fixed_scratch, nullptr, 0, kScratchBytes});
 }

@@ -129,13 +129,19 @@ const nmg_layout *effective_layout(const nmg_layout *L, nmg_layout *tmp);
 // stream is done, or NULL with *st set (NMG_ERR_CAPACITY when the request is
 // too large for it).
 typedef void *(*scratch_source)(int64_t bytes, hipStream_t stream, nmg_status *st);
+struct Scratch {
+    scratch_source source = nullptr;  // else a stream-ordered allocation
+    void *workspace = nullptr;        // the caller's, taken first when it is large enough
+    int64_t workspace_bytes = 0;
+    int64_t source_bytes = 0;         // what `source` can give
+};
 // nmg_spmm_epilogue; the families with scratch memory (the 16 x 16 x 32
-// products' prepared operands, the expanded weight) take it from `scratch`,
-// or from a stream-ordered allocation when scratch is NULL
+// products' prepared operands, the expanded weight, the weight stream) take
+// it from `scratch`
 nmg_status spmm_epilogue_ws(const nmg_layout *L, nmg_kernel kernel, nmg_epilogue epi,
                             const void *values, const uint8_t *indices, const void *X, int64_t ldx,
                             int64_t N, const void *R, int64_t ldr, void *Y, int64_t ldy,
-                            hipStream_t stream, scratch_source scratch);
+                            hipStream_t stream, const Scratch &scratch);
 // The expanded product: W_s written out dense (zeros elsewhere) as a layout
 // of one group with one-column chunks, multiplied by the binary32 /
 // widened-binary16 matrix-core kernel.  Scratch bytes it needs; whether it
@@ -160,6 +166,20 @@ nmg_status x16_product(const nmg_layout *L, const void *prepared, const void *X,
                        int N, void *Y, int64_t ldy, int epi, const void *R, int64_t ldr,
                        hipStream_t stream);
 
+// the product on the sparse matrix instructions (k_spmm_sp.hip): layouts and
+// arguments it takes, bytes of scratch memory for its weight stream, the
+// preparation and product
+bool sp_layout_supported(const nmg_layout *L);
+bool sp_p_layout_supported(const nmg_p_layout *L);
+bool sp_args_supported(nmg_dtype dtype, int64_t M, int64_t K, int64_t ldx, int64_t N);
+int64_t sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int64_t N);
+// whether AUTO takes it in place of `family` (its choice without workspace)
+bool sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epilogue epi, int64_t N);
+bool sp_p_preferred(const nmg_p_layout *L, int64_t N);
+nmg_status spmm_sp(const SpmmArgs &a, void *ws);
+nmg_status p_spmm_sp(const nmg_p_layout *L, const void *values, const uint8_t *index, const void *X,
+                     int64_t ldx, int N, void *Y, int64_t ldy, void *ws, hipStream_t stream);
+
 nmg_status check_p_layout(const nmg_p_layout *L);
 int p_pattern_count(int m, int n);
 nmg_status launch_p_compress(const nmg_p_layout *L, const void *W, int64_t ldw, void *values,
@@ -173,9 +193,11 @@ nmg_status launch_p_densify(const nmg_p_layout *L, const void *values, const uin
                             void *W_out, int64_t ldw, hipStream_t stream);
 nmg_status launch_p_refine(const nmg_p_layout *L, const void *W, int64_t ldw, void *values,
                            uint8_t *index, hipStream_t stream);
+// ws: `ws_bytes` of workspace (may be NULL)
 nmg_status launch_p_spmm(const nmg_p_layout *L, nmg_kernel kernel, const void *values,
                          const uint8_t *index, const void *X, int64_t ldx, int N, void *Y,
-                         int64_t ldy, hipStream_t stream);
+                         int64_t ldy, void *ws, int64_t ws_bytes, hipStream_t stream);
+int64_t p_workspace_bytes(const nmg_p_layout *L, nmg_kernel kernel, int64_t N);
 nmg_status spmm_half(const SpmmArgs &a);
 
 }  // namespace nmg_internal

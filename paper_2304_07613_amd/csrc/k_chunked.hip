@@ -831,10 +831,20 @@ nmg_status launch_p_densify(const nmg_p_layout *L, const void *values, const uin
     return launched();
 }
 
+int64_t p_workspace_bytes(const nmg_p_layout *L, nmg_kernel kernel, int64_t N) {
+    if (kernel != NMG_KERNEL_AUTO || !p_fits(L) || !sp_p_layout_supported(L) ||
+        !sp_args_supported(L->dtype, L->M, L->K, N, N) || !sp_p_preferred(L, N))
+        return 0;
+    return sp_stream_bytes(L->dtype, L->M, L->K, N);
+}
+
 nmg_status launch_p_spmm(const nmg_p_layout *L, nmg_kernel kernel, const void *values,
                          const uint8_t *index, const void *X, int64_t ldx, int N, void *Y,
-                         int64_t ldy, hipStream_t stream) {
+                         int64_t ldy, void *ws, int64_t ws_bytes, hipStream_t stream) {
     if (!p_fits(L)) return NMG_ERR_UNSUPPORTED;
+    if (kernel == NMG_KERNEL_AUTO && ws && p_workspace_bytes(L, kernel, N) > 0 &&
+        ws_bytes >= p_workspace_bytes(L, kernel, N) && sp_args_supported(L->dtype, L->M, L->K, ldx, N))
+        return p_spmm_sp(L, values, index, X, ldx, N, Y, ldy, ws, stream);
     const size_t es = elem_size(L->dtype);
     const bool xvec = aligned(X, 4 * es) && ldx % 4 == 0;
     // matrix cores when a quarter or more of the expanded products are useful

@@ -1,0 +1,907 @@
+// k_spmm_sp.hip -- Y = W_s X for weights whose aligned groups of 4 columns
+// keep at most 2 (n = 1, or n = 2 with m % 4 == 0), whatever rows share a
+// pattern: group layouts with any g and the paper's chunked layout alike, on
+// gfx950's sparse matrix instructions v_smfmac_f32_16x16x64_{f16,bf16}.
+//
+// Two kernels.  k_sp_prepare / k_sp_prepare_chunked write the weight once per
+// call as a stream of instruction operands ("weight stream") in scratch
+// memory, and (binary32) the scale of every token of X beside it; k_spmm_sp
+// multiplies.
+//
+// Binary32.  Every entry, scaled by a power of two (per 16 rows of W, per
+// token of X: the largest magnitude goes to [2^14, 2^15)), is carried as two
+// binary16 numbers, h = f16(v) and l = f16(v - h), and the product is summed
+// in binary32 from h h (one accumulator) and h l + l h (another).  h + l is
+// within 2^-24 |v| of v (each rounding to nearest leaves 12 bits), or within
+// 2^-40 of the largest entry for entries below 2^-16 of it; l l, left out, is
+// below 2^-24 |w x| and of either sign.  The
+// binary32 families round once per kept column on the running sum; here the
+// running sum of h h is rounded once per 8 stored columns, so the error
+// against 64 bits is smaller: 1.2e-7 to 2.7e-7 (2-norm, K = 768 to 3072)
+// where the binary32 matrix instructions give 2.5e-7 to 7e-7 on the same
+// inputs.  Three sparse binary16 products count half of K's columns each at
+// 16 times the rate of v_mfma_f32_16x16x4f32.  (Three exact bfloat16 parts
+// need no scales, but six products: 65 against 30 us at 3072 x 768 x 4096.)
+// Outputs that are not finite are recomputed by plain binary32 multiply-adds
+// of the kept columns in ascending order, so that infinities and NaN in X
+// reach only the outputs whose kept columns select them.
+//
+// Binary16.  One part, products exact in binary32, as the other binary16
+// kernels (and the same recomputation for results that are not finite).
+//
+// Weight stream, for every tile of 16 rows and step of 64 columns: PARTS
+// operands of 64 lanes x 16 bytes, then 64 position words of 4 bytes.  Lane l
+// holds row l % 16 and columns 16 (l / 16) .. + 15: stored value 2 q + j is
+// the j-th kept one of columns 4 q .. 4 q + 3, its offset in bits 4 q + 2 j;
+// places without a kept column hold 0.
+//
+// X.  The other operand wants, per lane, 8 consecutive columns of one token
+// side by side.  A thread loads 8 rows x 4 tokens of X, splits and packs them
+// along the columns and writes 16-byte units to LDS, unit (column / 8, token)
+// -- so the operand is two plain 16-byte LDS reads, X may have any alignment
+// and any token count, and no transposing read or bank conflict is left
+// (tokens are permuted within fours, sp_unit, for the 4-token writes).
+// Four waves (2 x 2) share a tile of 32 RT rows x 128 tokens; two workgroups
+// per CU.  X goes through two LDS buffers: step s + 1 is split and written
+// between the products of step s, while step s + 2 is loaded.
+#include "chunked.hpp"
+
+namespace {
+
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u8v __attribute__((ext_vector_type(8)));
+
+constexpr int kSpTok = 128;            // tokens per workgroup
+constexpr int kSpK = 64;               // columns per step
+constexpr int kSpWaves = 8;            // 4 row x 2 token blocks of 16 RT rows x 64 tokens
+constexpr int kSpThreads = 64 * kSpWaves;
+
+template <typename T> constexpr int sp_parts() { return std::is_same<T, float>::value ? 2 : 1; }
+__host__ __device__ constexpr int sp_tile_bytes(int parts) { return parts * 1024 + 256; }
+
+// the two parts of two binary32 numbers times `scale` (a power of two), packed
+// (first in the low half): the scaled number and its remainder are exact, each
+// rounded once to binary16.  (Vector conversions, so that the remainders stay
+// v_fma_mix_f32 + v_cvt_pk_f16_f32: v_fma_mixlo_f16 issues at half the rate.)
+struct SpPair {
+    uint32_t h, l;
+};
+__device__ __forceinline__ SpPair sp_split(float a, float b, float scale) {
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const h2 h = __builtin_convertvector(f2{a * scale, b * scale}, h2);
+    const h2 l = __builtin_convertvector(f2{__builtin_fmaf(a, scale, -(float)h[0]),
+                                            __builtin_fmaf(b, scale, -(float)h[1])}, h2);
+    return SpPair{__builtin_bit_cast(uint32_t, h), __builtin_bit_cast(uint32_t, l)};
+}
+// Exponent that brings the largest magnitude (as bits) to [2^14, 2^15); none
+// for zeros, infinities and NaN.  At most 2^126, so that the scale itself is a
+// binary32 number.
+__device__ __forceinline__ int sp_scale_exp(uint32_t max_bits) {
+    if (max_bits == 0 || max_bits >= 0x7f800000u) return 0;
+    const int e = (int)(max_bits >> 23) - 127;   // (subnormal: below every normal one)
+    return min(14 - e, 126);
+}
+
+// One lane's stored values (8, binary32 or binary16) and positions to the stream
+template <typename T>
+__device__ __forceinline__ void sp_store(char *tile, int lane, const T (&v)[8], uint32_t pos, float scale) {
+    if constexpr (sp_parts<T>() == 2) {
+        u4 h, l;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const SpPair p = sp_split(v[2 * k], v[2 * k + 1], scale);
+            h[k] = p.h;
+            l[k] = p.l;
+        }
+        reinterpret_cast<u4 *>(tile)[lane] = h;
+        reinterpret_cast<u4 *>(tile + 1024)[lane] = l;
+    } else {
+        reinterpret_cast<h8 *>(tile)[lane] = h8{v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
+    }
+    reinterpret_cast<uint32_t *>(tile + sp_parts<T>() * 1024)[lane] = pos;
+}
+
+// Largest |value| (as bits) of `count` consecutive binary32 numbers, by a
+// workgroup of TH threads; red: TH / 64 words of LDS
+template <int TH>
+__device__ __forceinline__ uint32_t sp_block_max(const float *p, int64_t count, uint32_t *red) {
+    uint32_t mx = 0;
+    const int tid = threadIdx.x;
+    // 16 bytes a load where the numbers allow, 4 loads in flight (past the
+    // end: the last one again)
+    if ((reinterpret_cast<uintptr_t>(p) & 15) == 0 && count % 4 == 0) {
+        const u4 *v = reinterpret_cast<const u4 *>(p);
+        const int64_t nv = count / 4;
+        for (int64_t i = tid; i < nv; i += 4 * TH) {
+            u4 u[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = v[min(i + k * TH, nv - 1)];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mx = max(mx, u[k][e] & 0x7fffffffu);
+        }
+    } else {
+        for (int64_t i = tid; i < count; i += 8 * TH) {
+            uint32_t u[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) u[k] = __builtin_bit_cast(uint32_t, p[min(i + k * TH, count - 1)]);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) mx = max(mx, u[k] & 0x7fffffffu);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o));
+    if ((tid & 63) == 0) red[tid >> 6] = mx;
+    __syncthreads();
+    mx = 0;
+#pragma unroll
+    for (int k = 0; k < TH / 64; ++k) mx = max(mx, red[k]);
+    return mx;
+}
+
+// Largest |entry| (as bits) of 64 tokens of X over kSpXRows rows, by a
+// workgroup of TH threads: part `rb` of the tokens' maxima
+constexpr int kSpXRows = 192;
+template <int TH>
+__device__ __forceinline__ void sp_token_max(const float *X, int64_t ldx, int K, int N, int t0, int rb,
+                                             uint32_t *xmax, uint32_t *red) {
+    const int tid = threadIdx.x, c = tid & 63, r0 = tid >> 6;
+    constexpr int RG = TH / 64, IT = kSpXRows / RG;
+    const float *xc = X + min(t0 + c, N - 1);
+    uint32_t u[IT], mx = 0;
+#pragma unroll
+    for (int j = 0; j < IT; ++j)
+        u[j] = __builtin_bit_cast(uint32_t, xc[(int64_t)min(rb * kSpXRows + r0 + j * RG, K - 1) * ldx]);
+#pragma unroll
+    for (int j = 0; j < IT; ++j) mx = max(mx, u[j] & 0x7fffffffu);
+    red[tid] = mx;
+    __syncthreads();
+    if (tid < 64 && t0 + tid < N) {
+#pragma unroll
+        for (int w = 1; w < RG; ++w) mx = max(mx, red[w * 64 + tid]);
+        xmax[(int64_t)rb * N + t0 + tid] = mx;
+    }
+}
+__device__ __forceinline__ int sp_token_exp(const uint32_t *xmax, int parts, int N, int tok) {
+    uint32_t mx = 0;
+    for (int p = 0; p < parts; p += 8) {
+        uint32_t u[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) u[j] = xmax[(int64_t)min(p + j, parts - 1) * N + tok];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) mx = max(mx, u[j]);
+    }
+    return sp_scale_exp(mx);
+}
+
+// Scratch memory: the weight stream, then (binary32) the scale exponents of
+// the 16-row tiles and the partial maxima of the tokens
+struct SpScratch {
+    char *stream;
+    int *wexp;
+    uint32_t *xmax;
+    int xparts;
+};
+inline int64_t sp_xparts(int64_t K) { return (K + kSpXRows - 1) / kSpXRows; }
+inline int64_t sp_tiles(int64_t M) { return (M + 15) / 16; }
+// (binary16: whole passes of two steps, the last one's columns past K empty)
+inline int64_t sp_steps(int64_t K, int parts) {
+    return parts == 2 ? (K + kSpK - 1) / kSpK : (K + 2 * kSpK - 1) / (2 * kSpK) * 2;
+}
+inline int64_t sp_scale_offset(int64_t M, int64_t K, int parts) {
+    return sp_tiles(M) * sp_steps(K, parts) * sp_tile_bytes(parts);     // a multiple of 256
+}
+inline SpScratch sp_scratch(void *ws, int64_t M, int64_t K, int parts) {
+    char *p = static_cast<char *>(ws);
+    int *e = reinterpret_cast<int *>(p + sp_scale_offset(M, K, parts));
+    return SpScratch{p, e, reinterpret_cast<uint32_t *>(e + sp_tiles(M)), (int)sp_xparts(K)};
+}
+
+// Kept values of one 16-column range, gathered column by column
+template <typename T> struct SpLane {
+    T v[8];
+    uint32_t pos = 0, filled = 0;
+    __device__ __forceinline__ SpLane() {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = (T)0;
+    }
+    // `col` in 0 .. 15, ascending over the calls
+    __device__ __forceinline__ void put(int col, T w, bool ok) {
+        const int q = col >> 2;
+        const int e = 2 * q + ((filled >> q) & 1);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = ok && e == i ? w : v[i];
+        if (ok) {
+            pos |= (uint32_t)(col & 3) << (2 * e);
+            filled |= 1u << q;
+        }
+    }
+};
+
+// MC: m when it is 4, 8 or 16 (a lane's 16 columns are whole chunks), else 0
+template <typename T, int MC>
+__device__ __forceinline__ void sp_gather(const T *__restrict__ values, const uint8_t *__restrict__ indices,
+                                          int row, int k0, int M, int K, int n, int m, int g, int C,
+                                          SpLane<T> &a) {
+    if (row >= M || k0 >= K) return;
+    const int64_t ldv = (int64_t)C * n;
+    const T *vr = values + row * ldv;
+    const uint8_t *ir = indices + (row / g) * ldv;
+    if constexpr (MC > 0) {
+        constexpr int CH = 16 / MC;      // whole chunks, at most 8 slots
+        T w[2 * CH];
+        int o[2 * CH];
+        const int c0 = k0 / MC;
+        typedef T TV __attribute__((ext_vector_type(2 * CH)));
+        typedef uint8_t IV __attribute__((ext_vector_type(2 * CH)));
+        const T *v0 = vr + 2 * c0;
+        const uint8_t *i0 = ir + 2 * c0;
+        if (n == 2 && c0 + CH <= C && (reinterpret_cast<uintptr_t>(v0) & (sizeof(T) * 2 * CH > 16 ? 15 : sizeof(TV) - 1)) == 0 &&
+            (reinterpret_cast<uintptr_t>(i0) & (2 * CH - 1)) == 0) {
+            // two of every chunk, all of them there: whole vectors
+            IV iv = *reinterpret_cast<const IV *>(i0);
+            if constexpr (sizeof(TV) > 16) {
+                typedef T HV __attribute__((ext_vector_type(CH)));
+                const HV a0 = reinterpret_cast<const HV *>(v0)[0], a1 = reinterpret_cast<const HV *>(v0)[1];
+#pragma unroll
+                for (int k = 0; k < CH; ++k) {
+                    w[k] = a0[k];
+                    w[CH + k] = a1[k];
+                }
+            } else {
+                const TV tv = *reinterpret_cast<const TV *>(v0);
+#pragma unroll
+                for (int k = 0; k < 2 * CH; ++k) w[k] = tv[k];
+            }
+#pragma unroll
+            for (int k = 0; k < 2 * CH; ++k) o[k] = iv[k];
+        } else {
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const bool ok = t < n && c0 + c < C;
+                    const int64_t ks = ok ? (int64_t)(c0 + c) * n + t : 0;
+                    w[2 * c + t] = vr[ks];
+                    o[2 * c + t] = ir[ks];
+                }
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                a.put(min(c * MC + min(o[2 * c + t], MC - 1), 15), w[2 * c + t], t < n && c0 + c < C);
+    } else {
+        for (int c = k0 / m; c < C && c * m < k0 + 16; ++c)
+            for (int t = 0; t < n; ++t) {
+                const int64_t ks = (int64_t)c * n + t;
+                const int col = c * m + min((int)ir[ks], m - 1) - k0;
+                a.put(min(max(col, 0), 15), vr[ks], col >= 0 && col < 16);
+            }
+    }
+}
+
+// Binary16: one wave per (16-row tile, step).
+template <int MC>
+__global__ __launch_bounds__(kBlock) void k_sp_prepare_f16(const _Float16 *__restrict__ values,
+                                                           const uint8_t *__restrict__ indices,
+                                                           char *__restrict__ stream, int M, int K,
+                                                           int n, int m, int g, int C, int nsteps,
+                                                           int total) {
+    const int lane = threadIdx.x & 63;
+    const int id = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (id >= total) return;
+    const int rt = id / nsteps, s = id - rt * nsteps;
+    SpLane<_Float16> a;
+    sp_gather<_Float16, MC>(values, indices, 16 * rt + (lane & 15), kSpK * s + 16 * (lane >> 4), M, K, n, m,
+                            g, C, a);
+    sp_store<_Float16>(stream + (int64_t)id * sp_tile_bytes(1), lane, a.v, a.pos, 1.f);
+}
+
+// Binary32: a workgroup per 16-row tile and 8 steps (the tile's scale from the
+// largest of its kept weights, found again by each of them, then a step per
+// wave), and one per 64 tokens and 192 rows of X (part of the tokens' maxima).
+constexpr int kSpPrep = 512;
+template <int MC>
+__global__ __launch_bounds__(kSpPrep) void k_sp_prepare(const float *__restrict__ values,
+                                                        const uint8_t *__restrict__ indices,
+                                                        const float *__restrict__ X, int64_t ldx,
+                                                        SpScratch ws, int M, int K, int N, int n, int m,
+                                                        int g, int C, int nsteps, int sgroups, int wblocks) {
+    __shared__ uint32_t red[kSpPrep];
+    const int lane = threadIdx.x & 63;
+    if ((int)blockIdx.x >= wblocks) {
+        const int i = blockIdx.x - wblocks;
+        sp_token_max<kSpPrep>(X, ldx, K, N, 64 * (i / ws.xparts), i % ws.xparts, ws.xmax, red);
+        return;
+    }
+    const int rt = blockIdx.x / sgroups, s = ((int)blockIdx.x - rt * sgroups) * (kSpPrep / 64) + (threadIdx.x >> 6);
+    const int64_t ldv = (int64_t)C * n;
+    SpLane<float> a;   // gathered while the maximum is found
+    if (s < nsteps)
+        sp_gather<float, MC>(values, indices, 16 * rt + (lane & 15), kSpK * s + 16 * (lane >> 4), M, K, n, m,
+                             g, C, a);
+    const int e = sp_scale_exp(sp_block_max<kSpPrep>(values + 16 * rt * ldv, min(16, M - 16 * rt) * ldv, red));
+    if (threadIdx.x == 0) ws.wexp[rt] = e;   // (the same from each of the tile's workgroups)
+    if (s < nsteps)
+        sp_store<float>(ws.stream + ((int64_t)rt * nsteps + s) * sp_tile_bytes(2), lane, a.v, a.pos,
+                        __builtin_ldexpf(1.f, e));
+}
+
+constexpr int kSpcRows = 256;          // chunk rows per workgroup, at most (S <= 256)
+constexpr int kSpcSteps = 4;           // steps per workgroup
+constexpr int kSpcThreads = 1024;
+
+// The chunked layout (m in {4, 8, 16}, n <= 2): a workgroup takes `cpw` chunks
+// (whole 16-row tiles, at most 256 rows) of 4 steps' block columns, inverts
+// their index in LDS and gathers every row's blocks.  Binary32: its rows share
+// one scale, from the largest of their kept weights (found again by each
+// workgroup of the same chunks: they lie side by side in memory).  One
+// workgroup per 64 tokens and 192 rows of X finds part of the tokens' maxima.
+template <typename T>
+__global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
+    const T *__restrict__ values, const uint8_t *__restrict__ index, const T *__restrict__ X, int64_t ldx,
+    SpScratch ws, int M, int M16, int K, int N, int n, int m, int g, int P, int S, int B, int cpw,
+    int nsteps, int groups, int sblocks) {
+    __shared__ uint8_t inv[kSpcSteps * 16 * kSpcRows];    // position of (block column, chunk row)
+    __shared__ uint8_t pat[256 * 2];
+    __shared__ uint32_t red[kSpcThreads];
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= groups * sblocks) {
+        const int i = (int)blockIdx.x - groups * sblocks;
+        if constexpr (sp_parts<T>() == 2)
+            sp_token_max<kSpcThreads>(X, ldx, K, N, 64 * (i / ws.xparts), i % ws.xparts, ws.xmax, red);
+        return;
+    }
+    const int grp = blockIdx.x / sblocks, s0 = ((int)blockIdx.x - grp * sblocks) * kSpcSteps;
+    const int r0 = grp * cpw * S;
+    const int rows = min(cpw * S, M - r0);    // whole chunks
+    const int bps = kSpK / m;                 // block columns of a step
+    const int b0 = s0 * bps, ns = min(kSpcSteps, nsteps - s0);
+    const int nb = min(ns * bps, B - b0);
+    const int64_t ldv = (int64_t)B * n;
+    for (int p = tid; p < P; p += kSpcThreads) p_unrank(m, n, p, pat + p * n);
+    for (int i = tid; i < ns * bps * kSpcRows / 4; i += kSpcThreads) reinterpret_cast<uint32_t *>(inv)[i] = 0;
+    float scale = 1.f;
+    if constexpr (sp_parts<T>() == 2) {
+        const int e = sp_scale_exp(sp_block_max<kSpcThreads>(values + (int64_t)r0 * ldv, (int64_t)rows * ldv, red));
+        scale = __builtin_ldexpf(1.f, e);
+        if (s0 == 0)
+            for (int t = tid; 16 * t < rows; t += kSpcThreads) ws.wexp[r0 / 16 + t] = e;
+    }
+    __syncthreads();
+    for (int i = tid; i < rows * nb; i += kSpcThreads) {
+        const int j = i / nb, w = i - j * nb;
+        const int ch = j / S;
+        const int r = min((int)index[(int64_t)(r0 + j) * B + b0 + w], S - 1);
+        inv[w * kSpcRows + ch * S + r] = (uint8_t)(j - ch * S);
+    }
+    __syncthreads();
+    const int bpl = 16 / m;                   // blocks per lane
+    // 4 column ranges of every row and step, rows fastest
+    for (int i = tid; i < rows * 4 * ns; i += kSpcThreads) {
+        const int sq = i / rows, rr = i - sq * rows;   // chunk row
+        const int sl = sq >> 2, q = sq & 3;            // step, 16-column range
+        const int base = rr / S * S;
+        SpLane<T> a;
+        for (int k = 0; k < bpl; ++k) {
+            const int w = (4 * sl + q) * bpl + k;
+            if (w >= nb) break;
+            const int j = inv[w * kSpcRows + rr];
+            const T *v = values + (int64_t)(r0 + base + j) * ldv + (int64_t)(b0 + w) * n;
+            const uint8_t *off = pat + (j / g) * n;
+            a.put(k * m + off[0], v[0], true);
+            if (n == 2) a.put(k * m + off[1], v[1], true);
+        }
+        const int row = r0 + rr;
+        sp_store<T>(ws.stream + ((int64_t)(row >> 4) * nsteps + s0 + sl) * sp_tile_bytes(sp_parts<T>()),
+                    (row & 15) + 16 * q, a.v, a.pos, scale);
+    }
+    // rows past M in the last tile
+    if (r0 + rows == M)
+        for (int i = tid; i < (M16 - M) * 4 * ns; i += kSpcThreads) {
+            const int row = M + i / (4 * ns), sq = i % (4 * ns);
+            const SpLane<T> a;
+            sp_store<T>(ws.stream + ((int64_t)(row >> 4) * nsteps + s0 + (sq >> 2)) * sp_tile_bytes(sp_parts<T>()),
+                        (row & 15) + 16 * (sq & 3), a.v, a.pos, 1.f);
+        }
+}
+
+// ---------------------------------------------------------------- the product
+
+// this wave's LDS operations are done, then the workgroup barrier; loads from
+// global memory stay in flight
+__device__ __forceinline__ void sp_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
+}
+
+// one output as a chain of binary32 multiply-adds over the kept columns
+template <typename T>
+__device__ __attribute__((noinline)) float sp_chain(const char *stream, const T *X, int64_t ldx, int row,
+                                                    int tok, int K, int nsteps, int wexp) {
+    constexpr int PARTS = sp_parts<T>(), TB = sp_tile_bytes(PARTS);
+    float acc = 0.f;
+    for (int s = 0; s < nsteps; ++s) {
+        const char *tile = stream + ((int64_t)(row >> 4) * nsteps + s) * TB;
+        for (int q = 0; q < 4; ++q) {
+            const int lane = (row & 15) + 16 * q;
+            const uint32_t pos = reinterpret_cast<const uint32_t *>(tile + PARTS * 1024)[lane];
+            for (int e = 0; e < 8; ++e) {
+                float w = (float)reinterpret_cast<const _Float16 *>(tile)[8 * lane + e];
+                if constexpr (PARTS == 2) {
+                    // (an infinite weight's low part is NaN: not added)
+                    const float l = (float)reinterpret_cast<const _Float16 *>(tile + 1024)[8 * lane + e];
+                    w = fabsf(w) < __builtin_inff() ? w + l : w;
+                    w = __builtin_ldexpf(w, -wexp);
+                }
+                if (w == 0.f) continue;      // no kept column
+                const int k = kSpK * s + 16 * q + 4 * (e >> 1) + (int)((pos >> (2 * e)) & 3u);
+                if (k < K) acc = fmaf(w, (float)X[k * ldx + tok], acc);
+            }
+        }
+    }
+    return acc;
+}
+
+// RT 16-row tiles per wave; VEC: X rows on 2-element boundaries and N even
+template <typename T, int RT, bool VEC>
+__global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *__restrict__ X, int64_t ldx,
+                                                        T *__restrict__ Y, int64_t ldy, int M, int K,
+                                                        const T *__restrict__ R, int64_t ldr, int N,
+                                                        int nsteps, int tiles16, int row_blocks,
+                                                        bool yvec) {
+    constexpr int PARTS = sp_parts<T>(), TB = sp_tile_bytes(PARTS);
+    constexpr int SUB = 2 / PARTS;                 // 64-column steps per pass of the pipeline
+    constexpr int ES = (int)sizeof(T);
+    constexpr int UNITS = 8 * kSpTok;              // 16-byte units per plane (8 column groups)
+    constexpr int OPITCH = 64 * ES + 16;           // output rows in LDS
+    constexpr int OTILE = 16 * OPITCH;             // one wave's 16 x 64 outputs
+    static_assert(kSpWaves * OTILE <= 2 * 2 * UNITS * 16, "outputs fit the staging buffers");
+    // two buffers of two planes: the parts of one step (binary32), two steps (binary16)
+    __shared__ __attribute__((aligned(16))) char xs[2 * 2 * UNITS * 16];
+    __shared__ int texp[PARTS == 2 ? kSpTok : 1];  // the tokens' scale exponents
+
+    const char *const stream = ws.stream;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int rb = tile % row_blocks, tt0 = tile / row_blocks;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave & 3, wt = wave >> 2;
+    const int t0 = tt0 * kSpTok;
+    const int rt0 = rb * (4 * RT) + wr * RT;       // this wave's first 16-row tile
+    const int npass = nsteps / SUB;                // host: whole passes
+
+    // ---- the weight stream, one pass ahead (two sets)
+    struct AOps {
+        h8 a[RT][2];                               // parts, or the two steps' operands
+        int ix[RT][SUB];
+    };
+    AOps aops[2];
+    const char *arow[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) arow[i] = stream + (int64_t)min(rt0 + i, tiles16 - 1) * nsteps * TB;
+    const uint32_t alane = (uint32_t)lane * 16;
+    auto load_a = [&](int p, AOps &o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            const char *tp = arow[i] + (int64_t)p * (SUB * TB);
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                o.a[i][k] = *reinterpret_cast<const h8 *>(tp + (SUB == 2 ? k * TB : k * 1024) + alane);
+#pragma unroll
+            for (int k = 0; k < SUB; ++k)
+                o.ix[i][k] = *reinterpret_cast<const int *>(tp + k * TB + PARTS * 1024 + lane * 4);
+        }
+    };
+
+    // ---- X, one to two passes ahead: wave w takes column group w of each
+    // step, every lane 8 rows x 2 tokens
+    constexpr int XR = 8 * SUB;
+    typedef T X2 __attribute__((ext_vector_type(2)));
+    X2 x[XR];
+    int xt[2];                                      // this lane's tokens within the tile
+    uint32_t xoff[2];                               // bytes
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        xt[j] = VEC ? 2 * lane + j : lane + 64 * j;
+        xoff[j] = (uint32_t)min(t0 + xt[j], VEC ? N - 2 + j : N - 1) * ES;
+    }
+    float xscale[2] = {1.f, 1.f};
+    auto load_x = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < XR; ++r) {
+            // rows past K: the last one (zero weights)
+            const int k = min((p * SUB + r / 8) * kSpK + 8 * wave + r % 8, K - 1);   // uniform
+            const char *xb = reinterpret_cast<const char *>(X) + (int64_t)k * ldx * ES;
+            if constexpr (VEC) {
+                x[r] = *reinterpret_cast<const X2 *>(xb + xoff[0]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) x[r][j] = *reinterpret_cast<const T *>(xb + xoff[j]);
+            }
+        }
+    };
+    u4 *const units = reinterpret_cast<u4 *>(xs);
+    // token j of this lane's 2 into buffer `buf`
+    auto write_x = [&](int buf, int j) __attribute__((always_inline)) {
+        u4 *dst = units + buf * (2 * UNITS) + wave * kSpTok + xt[j];
+        if constexpr (PARTS == 2) {
+            u4 h, l;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const SpPair p = sp_split(x[2 * k][j], x[2 * k + 1][j], xscale[j]);
+                h[k] = p.h;
+                l[k] = p.l;
+            }
+            dst[0] = h;
+            dst[UNITS] = l;
+        } else {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                dst[q * UNITS] = __builtin_bit_cast(
+                    u4, h8{x[8 * q][j], x[8 * q + 1][j], x[8 * q + 2][j], x[8 * q + 3][j], x[8 * q + 4][j],
+                           x[8 * q + 5][j], x[8 * q + 6][j], x[8 * q + 7][j]});
+        }
+    };
+
+    // ---- operands of a 16-token tile: columns 8 (lane / 16) .. + 7 and 32 more
+    h16 b[2][2];                                    // [tile parity][plane]
+    const u4 *const bsrc = units + (lane >> 4) * kSpTok + 64 * wt + (lane & 15);
+    auto read_b = [&](int buf, int t, int p) __attribute__((always_inline)) {
+        const u4 *src = bsrc + (buf * 2 + p) * UNITS + 16 * t;
+        const u4 lo = src[0], hi = src[4 * kSpTok];
+        b[t & 1][p] = __builtin_bit_cast(h16, u8v{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+    };
+
+    // acc: h h (binary16: the product); low: h l + l h
+    v4f acc[RT][4], low[PARTS == 2 ? RT : 1][4];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            acc[i][t] = v4f{0.f, 0.f, 0.f, 0.f};
+            if constexpr (PARTS == 2) low[i][t] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+    // C[.][t] += plane `pa` of the weights times plane `pb` of X's tile t
+    auto mul = [&](const AOps &o, auto &c, int t, int pa, int pb, int px) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+            c[i][t] = __builtin_amdgcn_smfmac_f32_16x16x64_f16(o.a[i][pa], b[t & 1][pb], c[i][t], o.ix[i][px], 0, 0);
+    };
+
+    // pass p from buffer `buf` with operand set `buf`: X of pass p + 1 (in
+    // registers) goes to the other buffer between the products and its
+    // registers take pass p + 2, the weights of pass p + 1 are loaded
+    auto pass = [&](int p, auto bc) __attribute__((always_inline)) {
+        constexpr int buf = decltype(bc)::value;
+        const AOps &o = aops[buf];
+        sp_barrier();   // buffer `buf` is complete, the other one no longer read
+        read_b(buf, 0, 0);
+        read_b(buf, 0, 1);
+        load_a(min(p + 1, npass - 1), aops[buf ^ 1]);
+        if constexpr (PARTS == 2) {
+            // two tiles at a time, so that the three products of one
+            // accumulator lie 2 RT instructions apart
+            read_b(buf, 1, 0);
+            read_b(buf, 1, 1);
+#pragma unroll
+            for (int t = 0; t < 4; t += 2) {
+                mul(o, low, t, 0, 1, 0);                 // h l
+                mul(o, low, t + 1, 0, 1, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (t == 0) write_x(buf ^ 1, 0);
+                mul(o, low, t, 1, 0, 0);                 // l h
+                mul(o, low, t + 1, 1, 0, 0);
+                mul(o, acc, t, 0, 0, 0);                 // h h
+                mul(o, acc, t + 1, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (t == 0) {
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        read_b(buf, 2, 1 - q);
+                        read_b(buf, 3, 1 - q);
+                    }
+                    write_x(buf ^ 1, 1);
+                    load_x(min(p + 2, npass - 1));
+                }
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (t < 3) {
+                    read_b(buf, t + 1, 0);
+                    read_b(buf, t + 1, 1);
+                }
+                mul(o, acc, t, 0, 0, 0);
+                mul(o, acc, t, 1, 1, SUB - 1);
+                if (t < 2) write_x(buf ^ 1, t);
+                if (t == 1) load_x(min(p + 2, npass - 1));
+            }
+            // the order of issue: the next tile's LDS reads, then its products
+            // with the packing of X in between
+            __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x020, 2 * RT + RT * SUB, 0);
+            static_for<4>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if constexpr (t < 3) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+                static_for<2 * RT>([&](auto) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    if constexpr (t < 2) __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                });
+                if constexpr (t < 2) __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);
+                if constexpr (t == 1) __builtin_amdgcn_sched_group_barrier(0x020, XR * (VEC ? 1 : 2), 0);
+            });
+        }
+    };
+    load_x(0);
+    load_a(0, aops[0]);
+    if constexpr (PARTS == 2) {
+        if (tid < kSpTok) texp[tid] = sp_token_exp(ws.xmax, ws.xparts, N, min(t0 + tid, N - 1));
+        sp_barrier();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) xscale[j] = __builtin_ldexpf(1.f, texp[xt[j]]);
+    }
+    write_x(0, 0);
+    write_x(0, 1);
+    load_x(min(1, npass - 1));
+    for (int p = 0; p < npass; p += 2) {
+        pass(p, std::integral_constant<int, 0>{});
+        if (p + 1 < npass) pass(p + 1, std::integral_constant<int, 1>{});
+    }
+
+    // ---- outputs: register r of (i, t) is row 16 (rt0 + i) + 4 (lane / 16) +
+    // r, token t0 + 64 wt + 16 t + lane % 16; through this wave's share of LDS
+    // so that every store writes whole runs of a row
+    sp_barrier();
+    char *const ob = xs + wave * OTILE;
+    constexpr int EPL = 16 / ES;                    // elements per lane
+    constexpr int LPR = 64 / EPL;                   // lanes per row
+    constexpr int RPI = 64 / LPR;                   // rows per store instruction
+    typedef T OV __attribute__((ext_vector_type(EPL)));
+    int xe[4] = {0, 0, 0, 0};
+    if constexpr (PARTS == 2) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) xe[t] = texp[64 * wt + 16 * t + (lane & 15)];
+    }
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        const int we = PARTS == 2 ? ws.wexp[min(rt0 + i, tiles16 - 1)] : 0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float y = acc[i][t][r];
+                if constexpr (PARTS == 2)
+                    y = __builtin_ldexpf(y + low[i][t][r], -(we + xe[t]));
+                const int row = 16 * (rt0 + i) + 4 * (lane >> 4) + r, tok = t0 + 64 * wt + 16 * t + (lane & 15);
+                if (__builtin_expect(!(fabsf(y) < __builtin_inff()) && row < M && tok < N, 0))
+                    y = sp_chain<T>(stream, X, ldx, row, tok, K, nsteps, we);
+                *reinterpret_cast<T *>(ob + (4 * (lane >> 4) + r) * OPITCH + (16 * t + (lane & 15)) * ES) = (T)y;
+            }
+        p_wave_sync();
+#pragma unroll
+        for (int r0 = 0; r0 < 16; r0 += RPI) {
+            const int r = r0 + lane / LPR, c = (lane % LPR) * EPL;
+            const int row = 16 * (rt0 + i) + r, tok = t0 + 64 * wt + c;
+            OV v = *reinterpret_cast<const OV *>(ob + r * OPITCH + c * ES);
+            if (row >= M || rt0 + i >= tiles16) continue;
+            T *y = Y + (int64_t)row * ldy + tok;
+            if (R != nullptr) {   // the sum in binary32 of the rounded product and R, rounded again
+                const T *res = R + (int64_t)row * ldr + tok;
+                OV rv = {};
+                if (yvec && tok + EPL <= N) {
+                    rv = *reinterpret_cast<const OV *>(res);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e)
+                        if (tok + e < N) rv[e] = res[e];
+                }
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) v[e] = (T)((float)v[e] + (float)rv[e]);
+            }
+            if (yvec && tok + EPL <= N) {
+                __builtin_nontemporal_store(v, reinterpret_cast<OV *>(y));
+            } else {
+#pragma unroll
+                for (int e = 0; e < EPL; ++e)
+                    if (tok + e < N) y[e] = v[e];
+            }
+        }
+        p_wave_sync();
+    }
+}
+
+// --------------------------------------------------------------- launchers
+
+// Row tiles per wave (1 .. 3, binary16 .. 4): rounds of workgroups (one per
+// CU) times the rows of one plus a fixed share for its X.
+int sp_row_tiles(int64_t M, int64_t N, int most) {
+    const int64_t cus = device_cus(), tt = (N + kSpTok - 1) / kSpTok;
+    int best = 1;
+    int64_t cost = -1;
+    for (int rt = most; rt >= 1; --rt) {
+        const int64_t wgs = (M + 64 * rt - 1) / (64 * rt) * tt;
+        const int64_t c = (wgs + cus - 1) / cus * (64 * rt + 64);
+        if (cost < 0 || c < cost) {
+            cost = c;
+            best = rt;
+        }
+    }
+    return best;
+}
+
+struct SpOut {
+    void *Y;
+    int64_t ldy;
+    const void *R;   // residual to add, or NULL
+    int64_t ldr;
+};
+
+template <typename T, int RT>
+void sp_launch(const SpScratch &ws, const void *X, int64_t ldx, int M, int K, int N, const SpOut &o,
+               hipStream_t stream) {
+    const int nsteps = (int)sp_steps(K, sp_parts<T>()), tiles16 = (int)sp_tiles(M);
+    const int row_blocks = (tiles16 + 4 * RT - 1) / (4 * RT);
+    const int tok_tiles = (N + kSpTok - 1) / kSpTok;
+    const bool vec = aligned(X, 2 * sizeof(T)) && ldx % 2 == 0 && N % 2 == 0;
+    constexpr int EPL = 16 / (int)sizeof(T);
+    const bool yvec = aligned(o.Y, 16) && o.ldy % EPL == 0 && (!o.R || (aligned(o.R, 16) && o.ldr % EPL == 0));
+    const dim3 grid((unsigned)(row_blocks * tok_tiles)), block(kSpThreads);
+    if (vec)
+        hipLaunchKernelGGL((k_spmm_sp<T, RT, true>), grid, block, 0, stream, ws, (const T *)X, ldx,
+                           (T *)o.Y, o.ldy, M, K, (const T *)o.R, o.ldr, N, nsteps, tiles16, row_blocks, yvec);
+    else
+        hipLaunchKernelGGL((k_spmm_sp<T, RT, false>), grid, block, 0, stream, ws, (const T *)X, ldx,
+                           (T *)o.Y, o.ldy, M, K, (const T *)o.R, o.ldr, N, nsteps, tiles16, row_blocks, yvec);
+}
+
+template <typename T>
+nmg_status sp_product(const SpScratch &ws, const void *X, int64_t ldx, int M, int K, int N, const SpOut &o,
+                      hipStream_t stream) {
+    switch (sp_row_tiles(M, N, sp_parts<T>() == 2 ? 3 : 4)) {
+        case 4:
+            if constexpr (sp_parts<T>() == 1) sp_launch<T, 4>(ws, X, ldx, M, K, N, o, stream);
+            break;
+        case 3: sp_launch<T, 3>(ws, X, ldx, M, K, N, o, stream); break;
+        case 2: sp_launch<T, 2>(ws, X, ldx, M, K, N, o, stream); break;
+        default: sp_launch<T, 1>(ws, X, ldx, M, K, N, o, stream); break;
+    }
+    return launched();
+}
+
+// chunks per workgroup of k_sp_prepare_chunked: whole 16-row tiles, 64 rows or
+// more, at most 256; 0 if there is no such number
+int spc_chunks(int S) {
+    int cpw = 1;
+    while (cpw * S % 16 != 0) ++cpw;
+    const int unit = cpw;
+    while (cpw * S < 64) cpw += unit;
+    return cpw * S <= kSpcRows ? cpw : 0;
+}
+
+}  // namespace
+
+int64_t nmg_internal::sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int64_t N) {
+    const bool f32 = dtype == NMG_F32;
+    return sp_scale_offset(M, K, f32 ? 2 : 1) + (f32 ? 4 * (sp_tiles(M) + sp_xparts(K) * N) : 0);
+}
+
+bool nmg_internal::sp_args_supported(nmg_dtype dtype, int64_t M, int64_t K, int64_t ldx, int64_t N) {
+    const int64_t es = (int64_t)elem_size(dtype), lim = (int64_t)1 << 31;
+    return ldx * es < lim && sp_tiles(M) * sp_steps(K, 1) < lim && sp_tiles(M) * ((K + 511) / 512) + (N + 63) / 64 * sp_xparts(K) < lim &&
+           ((M + 31) / 32) * ((N + kSpTok - 1) / kSpTok) < lim;
+}
+
+// at most 2 kept of every aligned 4 columns: one of m >= 2 (a chunk ends
+// between any two kept columns), or two of whole fours
+bool nmg_internal::sp_layout_supported(const nmg_layout *L) {
+    return (L->n == 1 && L->m >= 2) || (L->n == 2 && L->m % 4 == 0);
+}
+
+// AUTO's rule, over its choice without a workspace (us a call, that choice /
+// this one; 3072 x 768 unless said otherwise):
+//  - Binary32 needs 64 kept columns a row: below that a chain of multiply-adds
+//    rounds as rarely as this product does (1:20 of 768 columns: error 1.14e-7
+//    against 1.22e-7; 1:10: 1.58e-7 against 1.45e-7).
+//  - The expanded product and the vector kernels lose everywhere: 2:4:1
+//    79 / 23 at one token, 188 / 56 at 4096 (177 with the start's allocation
+//    amortised), 768 x 3072 262 / 55 and 286 / 72; 1:10:1 135 / 23 and 162 / 53.
+//  - mfma_scalar, binary32: its X goes through registers when the tokens do
+//    not fill its tiles (1:4:8 at 1021 tokens 44 / 34); at half density it
+//    loses at every size it is chosen for (2:4:8 31 / 25 at 512 tokens,
+//    104 / 56 at 4096); else from about 10^9 kept products (1:4:8 19 / 27 at
+//    512 tokens, 36 / 34 at 2048, 60 / 56 at 4096).  Binary16 goes there only
+//    for token counts off 8: 2:8:8 31 / 15 at one token, 55 / 26 at 1021.
+//  - mfma_direct keeps its layouts (few kept columns, few rows or tokens),
+//    where its partial sums also round less.
+//  - The binary16 kernels with the epilogue folded in: smfmac from 3 10^9
+//    expanded products (2:4:1 11 / 16 at 512 tokens, 30 / 21 at 2048) or 2048
+//    columns (768 x 3072 50 / 30 at 16 tokens), mfma_f16 at half density from
+//    4 10^9 (2:4:8 13 / 16 at 512 tokens, 35 / 21 at 2048; 1:4:8 27 / 35 at
+//    4096); GELU stays with them.
+bool nmg_internal::sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epilogue epi, int64_t N) {
+    const double kept = (double)L->M * L->C * L->n * (double)N, dense = (double)L->M * L->K * (double)N;
+    const bool f32 = L->dtype == NMG_F32, half = 2 * L->n >= L->m;
+    if (f32 && (int64_t)L->C * L->n < 64) return false;
+    switch (family) {
+        case NMG_KERNEL_MFMA_EXPAND:
+        case NMG_KERNEL_VALU_STAGED:
+        case NMG_KERNEL_VALU: return true;
+        case NMG_KERNEL_MFMA_SCALAR: return !f32 || half || N % 64 != 0 || kept >= 1e9;
+        case NMG_KERNEL_SMFMAC_F16: return epi != NMG_EPILOGUE_GELU && (dense >= 3e9 || L->K >= 2048);
+        case NMG_KERNEL_MFMA_F16: return epi != NMG_EPILOGUE_GELU && half && dense >= 4e9;
+        default: return false;
+    }
+}
+
+bool nmg_internal::sp_p_preferred(const nmg_p_layout *L, int64_t N) {
+    (void)N;
+    return L->dtype == NMG_F16 || (int64_t)L->B * L->n >= 64;
+}
+
+nmg_status nmg_internal::spmm_sp(const SpmmArgs &a, void *ws_) {
+    const nmg_layout *L = a.L;
+    const SpOut out{a.Y, a.ldy, a.epi == NMG_EPILOGUE_ADD ? a.R : nullptr, a.ldr};
+    const int parts = L->dtype == NMG_F32 ? 2 : 1;
+    const int nsteps = (int)sp_steps(L->K, parts), tiles = (int)sp_tiles(L->M);
+    const SpScratch ws = sp_scratch(ws_, L->M, L->K, parts);
+    if (L->dtype == NMG_F32) {
+        const int sgroups = (nsteps + kSpPrep / 64 - 1) / (kSpPrep / 64), wblocks = tiles * sgroups;
+        const dim3 grid((unsigned)(wblocks + (a.N + 63) / 64 * ws.xparts));
+#define NMG_SP_PREP(MC)                                                                                hipLaunchKernelGGL((k_sp_prepare<MC>), grid, dim3(kSpPrep), 0, a.stream, (const float *)a.values,                        a.indices, (const float *)a.X, a.ldx, ws, L->M, L->K, a.N, L->n, L->m, L->g,                         L->C, nsteps, sgroups, wblocks)
+        switch (L->m) {
+            case 4: NMG_SP_PREP(4); break;
+            case 8: NMG_SP_PREP(8); break;
+            case 16: NMG_SP_PREP(16); break;
+            default: NMG_SP_PREP(0); break;
+        }
+#undef NMG_SP_PREP
+        const nmg_status st = launched();
+        if (st != NMG_OK) return st;
+        return sp_product<float>(ws, a.X, a.ldx, L->M, L->K, a.N, out, a.stream);
+    }
+    const int total = tiles * nsteps;
+    const dim3 grid((unsigned)((total + kBlock / 64 - 1) / (kBlock / 64)));
+#define NMG_SP_PREP(MC)                                                                                hipLaunchKernelGGL((k_sp_prepare_f16<MC>), grid, dim3(kBlock), 0, a.stream,                                            (const _Float16 *)a.values, a.indices, ws.stream, L->M, L->K, L->n, L->m, L->g,                        L->C, nsteps, total)
+    switch (L->m) {
+        case 4: NMG_SP_PREP(4); break;
+        case 8: NMG_SP_PREP(8); break;
+        case 16: NMG_SP_PREP(16); break;
+        default: NMG_SP_PREP(0); break;
+    }
+#undef NMG_SP_PREP
+    const nmg_status st = launched();
+    if (st != NMG_OK) return st;
+    return sp_product<_Float16>(ws, a.X, a.ldx, L->M, L->K, a.N, out, a.stream);
+}
+
+bool nmg_internal::sp_p_layout_supported(const nmg_p_layout *L) {
+    return L->n <= 2 && (L->m == 4 || L->m == 8 || L->m == 16) && L->P <= 256 && L->S <= kSpcRows &&
+           spc_chunks(L->S) > 0;
+}
+
+nmg_status nmg_internal::p_spmm_sp(const nmg_p_layout *L, const void *values, const uint8_t *index,
+                                   const void *X, int64_t ldx, int N, void *Y, int64_t ldy, void *ws_,
+                                   hipStream_t stream) {
+    const bool f32 = L->dtype == NMG_F32;
+    const int nsteps = (int)sp_steps(L->K, f32 ? 2 : 1), cpw = spc_chunks(L->S);
+    const int groups = (L->M / L->S + cpw - 1) / cpw, sblocks = (nsteps + kSpcSteps - 1) / kSpcSteps;
+    const SpScratch ws = sp_scratch(ws_, L->M, L->K, f32 ? 2 : 1);
+    const SpOut out{Y, ldy, nullptr, 0};
+    const int64_t blocks = (int64_t)groups * sblocks + (f32 ? (int64_t)(N + 63) / 64 * ws.xparts : 0);
+    if (blocks > INT32_MAX) return NMG_ERR_PARAM;
+#define NMG_SPC(T)                                                                                      hipLaunchKernelGGL((k_sp_prepare_chunked<T>), dim3((unsigned)blocks), dim3(kSpcThreads), 0, stream,                        (const T *)values, index, (const T *)X, ldx, ws, L->M, (L->M + 15) / 16 * 16,                         L->K, N, L->n, L->m, L->g, L->P, L->S, L->B, cpw, nsteps, groups, sblocks)
+    if (f32) NMG_SPC(float);
+    else NMG_SPC(_Float16);
+#undef NMG_SPC
+    const nmg_status st = launched();
+    if (st != NMG_OK) return st;
+    if (f32) return sp_product<float>(ws, X, ldx, L->M, L->K, N, out, stream);
+    return sp_product<_Float16>(ws, X, ldx, L->M, L->K, N, out, stream);
+}

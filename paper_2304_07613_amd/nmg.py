@@ -24,7 +24,7 @@ F32, F16 = 0, 1
 _DTYPE_CODE = {torch.float32: F32, torch.float16: F16}
 KERNELS = {"auto": 0, "valu": 1, "mfma": 2, "mfma_general": 3, "mfma_scalar": 4, "mfma_f16": 5,
            "mfma_direct": 6, "smfmac_f16": 7, "valu_staged": 8, "mfma_wide": 9, "mfma_split": 10,
-           "mfma_expand": 11}
+           "mfma_expand": 11, "sparse": 12}
 _KERNEL_NAME = {v: k for k, v in KERNELS.items()}
 EPILOGUES = {"none": 0, "gelu": 1, "add": 2}
 
@@ -84,6 +84,12 @@ def lib():
                                i64, vp], ctypes.c_int),
         "nmg_spmm_epilogue_noalloc": ([lp, ctypes.c_int, ctypes.c_int, vp, vp, vp, i64, i64, vp,
                                        i64, vp, i64, vp], ctypes.c_int),
+        "nmg_spmm_epilogue_ws": ([lp, ctypes.c_int, ctypes.c_int, vp, vp, vp, i64, i64, vp, i64, vp,
+                                  i64, vp, i64, vp], ctypes.c_int),
+        "nmg_spmm_workspace_bytes": ([lp, ctypes.c_int, i64], i64),
+        "nmg_p_spmm_ws": ([pp, ctypes.c_int, vp, vp, vp, i64, i64, vp, i64, vp, i64, vp],
+                          ctypes.c_int),
+        "nmg_p_spmm_workspace_bytes": ([pp, ctypes.c_int, i64], i64),
         "nmg_spmm_auto_kernel": ([lp, i64], ctypes.c_int),
         "nmg_densify": ([lp, vp, vp, vp, i64, vp], ctypes.c_int),
         "nmg_gelu": ([ctypes.c_int, vp, vp, i64, vp], ctypes.c_int),
@@ -183,6 +189,16 @@ def _rows(t: torch.Tensor, name: str):
     return t.stride(0)
 
 
+def _workspace(nbytes: int, like: torch.Tensor):
+    """Scratch memory of one call from torch's allocator: (tensor, pointer,
+    bytes).  Freed after the call returns; the allocator hands it out again in
+    stream order on the current stream only."""
+    if nbytes <= 0:
+        return None, ctypes.c_void_p(0), 0
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+    return ws, _ptr(ws), nbytes
+
+
 def compress_into(layout: Layout, W: torch.Tensor, values: torch.Tensor, indices: torch.Tensor):
     """``nmg_compress`` into caller-allocated ``values`` / ``indices``."""
     _need_cuda(W, values, indices)
@@ -280,7 +296,8 @@ def spmm_x16_epilogue(layout: Layout, prepared, X, epilogue: str = "none", R=Non
 
 
 def spmm_into(layout: Layout, values, indices, X, Y, kernel: str = "auto"):
-    """``nmg_spmm_with`` into a caller-allocated Y (M x N)."""
+    """``nmg_spmm_epilogue_ws`` without an epilogue into a caller-allocated Y
+    (M x N), scratch memory from torch's allocator."""
     _need_cuda(values, indices, X, Y)
     if X.dtype != layout.dtype or Y.dtype != layout.dtype or values.dtype != layout.dtype:
         raise TypeError("dtype mismatch")
@@ -290,9 +307,12 @@ def spmm_into(layout: Layout, values, indices, X, Y, kernel: str = "auto"):
         raise ValueError(f"values must be contiguous {layout.values_shape}")
     if tuple(indices.shape) != layout.indices_shape or not indices.is_contiguous():
         raise ValueError(f"indices must be contiguous {layout.indices_shape}")
-    _check(lib().nmg_spmm_with(ctypes.byref(layout.c), KERNELS[kernel], _ptr(values),
-                               _ptr(indices), _ptr(X), _rows(X, "X"), X.shape[1], _ptr(Y),
-                               _rows(Y, "Y"), _stream(X)), "nmg_spmm")
+    L = lib()
+    N, code = X.shape[1], KERNELS[kernel]
+    ws, wp, wb = _workspace(L.nmg_spmm_workspace_bytes(ctypes.byref(layout.c), code, N), X)
+    _check(L.nmg_spmm_epilogue_ws(ctypes.byref(layout.c), code, 0, _ptr(values), _ptr(indices),
+                                  _ptr(X), _rows(X, "X"), N, None, 0, _ptr(Y), _rows(Y, "Y"),
+                                  wp, wb, _stream(X)), "nmg_spmm")
 
 
 def spmm(values, indices, X, layout: Layout, kernel: str = "auto"):
@@ -306,14 +326,17 @@ def spmm_epilogue(values, indices, X, layout: Layout, epilogue: str = "none", R=
                   kernel: str = "auto", Y=None):
     """Y = epilogue(W_s X): "none", "gelu" (GELU of the product) or "add"
     (product + R), bit for bit what spmm followed by gelu or add gives."""
-    return _spmm_epilogue("nmg_spmm_epilogue", values, indices, X, layout, epilogue, R, kernel, Y)
+    return _spmm_epilogue("nmg_spmm_epilogue_ws", values, indices, X, layout, epilogue, R, kernel, Y)
 
 
 def spmm_epilogue_noalloc(values, indices, X, layout: Layout, epilogue: str = "none", R=None,
                           kernel: str = "auto", Y=None):
     """``nmg_spmm_epilogue_noalloc``: spmm_epilogue without device allocation
     in the library (the prepared operands of mfma_wide / mfma_split go to the
-    library's fixed per-GPU array; overlapping calls on one GPU race).  Y is
+    library's fixed per-GPU array; overlapping calls on one GPU race).  "auto"
+    never puts a layout into that array whose choice without a workspace has no
+    scratch memory, so there spmm_epilogue, which brings a workspace, may take
+    "sparse" where this call does not.  Y is
     allocated here when not given: pass Y to allocate nothing at all."""
     return _spmm_epilogue("nmg_spmm_epilogue_noalloc", values, indices, X, layout, epilogue, R,
                           kernel, Y)
@@ -343,9 +366,14 @@ def _spmm_epilogue(fn, values, indices, X, layout, epilogue, R, kernel, Y):
         if R.dtype != layout.dtype or tuple(R.shape) != (layout.M, N):
             raise ValueError("R must be M x N of the layout's dtype")
         rp, ldr = _ptr(R), _rows(R, "R")
-    _check(getattr(lib(), fn)(ctypes.byref(layout.c), KERNELS[kernel], EPILOGUES[epilogue],
-                              _ptr(values), _ptr(indices), _ptr(X), _rows(X, "X"), N, rp, ldr,
-                              _ptr(Y), _rows(Y, "Y"), _stream(X)), fn)
+    L = lib()
+    args = [ctypes.byref(layout.c), KERNELS[kernel], EPILOGUES[epilogue], _ptr(values),
+            _ptr(indices), _ptr(X), _rows(X, "X"), N, rp, ldr, _ptr(Y), _rows(Y, "Y")]
+    if fn == "nmg_spmm_epilogue_ws":
+        nbytes = L.nmg_spmm_workspace_bytes(args[0], args[1], N)
+        ws, wp, wb = _workspace(nbytes, X)
+        args += [wp, wb]
+    _check(getattr(L, fn)(*args, _stream(X)), fn)
     return Y
 
 
@@ -443,10 +471,12 @@ def p_spmm(values, index, X, layout: PLayout, kernel: str = "auto"):
     if kernel not in ("auto", "valu", "mfma"):
         raise ValueError(f"unknown chunked-layout kernel {kernel!r}")
     Y = torch.empty((layout.M, X.shape[1]), dtype=X.dtype, device=X.device)
-    _check(lib().nmg_p_spmm_with(ctypes.byref(layout.c), KERNELS[kernel], _ptr(values),
-                                 _ptr(index), _ptr(X), _rows(X, "X"), X.shape[1], _ptr(Y),
-                                 _rows(Y, "Y"), _stream(X)),
-           "nmg_p_spmm_with")
+    L = lib()
+    N, code = X.shape[1], KERNELS[kernel]
+    ws, wp, wb = _workspace(L.nmg_p_spmm_workspace_bytes(ctypes.byref(layout.c), code, N), X)
+    _check(L.nmg_p_spmm_ws(ctypes.byref(layout.c), code, _ptr(values), _ptr(index), _ptr(X),
+                           _rows(X, "X"), N, _ptr(Y), _rows(Y, "Y"), wp, wb, _stream(X)),
+           "nmg_p_spmm_ws")
     return Y
 
 

@@ -936,3 +936,124 @@ def test_chunked_few_patterns(nmg, n, m, g, kind):
     torch.cuda.synchronize()
     rv, ridx, _ = oracle.p_refine(W, ridx, n, m, g)
     assert np.array_equal(np_of(idx), ridx) and np.array_equal(bits(np_of(v)), bits(rv))
+
+
+# ------------------------------------------- the sparse matrix instructions
+
+# edges of the 16-row tiles, of 64- and 128-column steps, of one to four row
+# tiles a wave and of 128-token tiles; every way n of m falls on 4 columns; X
+# rows the 8-byte loads do not take (odd N), one token, one step, odd step counts
+SPARSE = [
+    (16, 64, 1, 2, 4, 1), (17, 65, 3, 1, 4, 1), (200, 130, 129, 2, 8, 1), (72, 72, 128, 2, 4, 8),
+    (130, 1000, 77, 1, 10, 2), (66, 660, 130, 1, 33, 1), (68, 130, 33, 1, 2, 4), (96, 300, 257, 1, 3, 3),
+    (64, 144, 256, 2, 16, 2), (40, 120, 66, 2, 12, 1), (384, 192, 1030, 1, 5, 8), (3072, 64, 1025, 2, 4, 4),
+    (1056, 100, 2050, 1, 20, 16), (260, 510, 126, 1, 255, 1),
+]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("M,K,N,n,m,g", SPARSE)
+def test_sparse_product(nmg, M, K, N, n, m, g, dtype):
+    W = synth.normal((M, K), 900 + M + K, 0.02, dtype)
+    X = synth.normal((K, N), 901 + N, 1.0, dtype)
+    v, idx, L = nmg.compress(W.to(DEV), n, m, g)
+    rv, ridx = np_of(v), np_of(idx)
+    assert spmm_full(nmg, v, idx, L, X, rv, ridx, "sparse", "sparse product") is not None
+    # rows of a wider buffer, the residual added in the stores, GELU after them
+    Xb = torch.zeros((K, N + 3), dtype=dtype, device=DEV)
+    Xb[:, :N] = X.to(DEV)
+    Rb = synth.normal((M, N + 5), 902 + N, 1.0, dtype).to(DEV)
+    Yb = torch.zeros((M, N + 7), dtype=dtype, device=DEV)
+    P = nmg.spmm(v, idx, X.to(DEV), L, "sparse")
+    nmg.spmm_epilogue(v, idx, Xb[:, :N], L, "add", Rb[:, :N], "sparse", Y=Yb[:, :N])
+    Yg = nmg.spmm_epilogue(v, idx, X.to(DEV), L, "gelu", kernel="sparse")
+    torch.cuda.synchronize()
+    assert torch.equal(Yb[:, :N].contiguous().view(torch.uint8),
+                       nmg.add(P, Rb[:, :N].contiguous()).view(torch.uint8))
+    assert (Yb[:, N:] == 0).all()
+    assert torch.equal(Yg.view(torch.uint8), nmg.gelu(P).view(torch.uint8))
+
+
+@pytest.mark.parametrize("wexp,xexp", [(0, 0), (-60, 0), (0, -100), (40, 60), (-120, 100)])
+def test_sparse_product_precision(nmg, wexp, xexp):
+    """Binary32 by binary16 parts: no further from the 64-bit product than a
+    chain of binary32 multiply-adds (the vector kernel), at any magnitude."""
+    M, K, N = 128, 1536, 130
+    W = torch.ldexp(synth.normal((M, K), 911, 0.02), torch.tensor(wexp))
+    X = torch.ldexp(synth.normal((K, N), 912, 1.0), torch.tensor(xexp))
+    X[:, 3] *= 2.0 ** -20          # tokens of very different magnitude
+    X[7, 5] *= 1000.0
+    v, idx, L = nmg.compress(W.to(DEV), 1, 8, 1)
+    dense = nmg.densify(v, idx, L).double()
+    ref = dense @ X.to(DEV).double()
+    err = {}
+    for kernel in ("valu", "sparse"):
+        Y = nmg.spmm(v, idx, X.to(DEV), L, kernel).double()
+        err[kernel] = ((Y - ref).norm(dim=0) / ref.norm(dim=0))
+    torch.cuda.synchronize()
+    print("[sparse precision]", {k: float(e.mean()) for k, e in err.items()}, flush=True)
+    assert err["sparse"].mean() <= err["valu"].mean()
+    assert err["sparse"].max() <= 1.5 * err["valu"].max()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+def test_sparse_product_non_finite(nmg, dtype):
+    """Infinities, NaN and overflow come out as from the multiply-adds over
+    the kept columns: only where a kept column selects them."""
+    M, K, N = 80, 96, 40
+    W = synth.normal((M, K), 921, 0.5, dtype)
+    X = synth.normal((K, N), 922, 1.0, dtype)
+    X[5, 2], X[17, 3], X[40, 4] = float("inf"), float("-inf"), float("nan")
+    if dtype == torch.float32:
+        X[8:12, 6] = 3e38          # sums past the largest binary32 number
+    v, idx, L = nmg.compress(W.to(DEV), 1, 4, 2)
+    a = nmg.spmm(v, idx, X.to(DEV), L, "valu").float()
+    b = nmg.spmm(v, idx, X.to(DEV), L, "sparse").float()
+    torch.cuda.synchronize()
+    fin = torch.isfinite(a)
+    assert torch.equal(fin, torch.isfinite(b)) and not fin.all()
+    assert torch.equal(torch.isnan(a), torch.isnan(b))
+    assert torch.equal(a[torch.isinf(a)], b[torch.isinf(b)])
+    assert ((a - b)[fin].abs() <= 2e-3 * a[fin].abs() + (1e-5 if dtype == torch.float32 else 2e-2)).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("M,K,N,n,m,g", [(6, 4, 1, 2, 4, 1), (30, 68, 3, 2, 4, 5), (96, 132, 129, 2, 4, 16),
+                                         (192, 1000, 260, 2, 4, 32), (28, 72, 70, 2, 8, 1), (240, 64, 33, 1, 16, 15),
+                                         (512, 776, 131, 1, 8, 32)])
+def test_chunked_sparse_product(nmg, M, K, N, n, m, g, dtype):
+    """The chunked layout on the sparse matrix instructions (AUTO through the
+    binding, which brings a workspace): chunks that share 16-row tiles, rows
+    past M in the last tile, block columns past the last step."""
+    W = synth.normal((M, K), 931 + M, 0.02, dtype)
+    X = synth.normal((K, N), 932 + N, 1.0, dtype)
+    v, idx, L = nmg.p_compress(W.to(DEV), n, m, g)
+    Y = nmg.p_spmm(v, idx, X.to(DEV), L)
+    Yv = nmg.p_spmm(v, idx, X.to(DEV), L, "valu")
+    torch.cuda.synchronize()
+    Yref, B = oracle.p_spmm(np_of(v), np_of(idx), np_of(X), K, n, m, g)
+    check_product(Y, Yref, B, dtype, "chunked sparse", (K // m) * n)
+    check_product(Yv, Yref, B, dtype, "chunked valu", (K // m) * n)
+
+
+def test_sparse_product_capture(nmg):
+    """AUTO with torch's workspace captured in a graph: replays on new X give
+    the eager bits, with eager work in between."""
+    W = synth.normal((768, 768), 941, 0.02).to(DEV)
+    v, idx, L = nmg.compress(W, 2, 4, 1)
+    X = synth.normal((768, 300), 942).to(DEV)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        nmg.spmm(v, idx, X, L)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        Y = nmg.spmm(v, idx, X, L)
+    for rep in range(3):
+        X.copy_(synth.normal((768, 300), 950 + rep))
+        graph.replay()
+        eager = nmg.spmm(v, idx, X, L)
+        torch.cuda.synchronize()
+        assert torch.equal(Y.view(torch.int32), eager.view(torch.int32)), f"replay {rep}"
