@@ -64,9 +64,11 @@ def header_functions() -> list:
 
 def lib():
     """The loaded library; raises if it has not been built."""
+    return _lib if _lib is not None else _load()
+
+
+def _load():
     global _lib
-    if _lib is not None:
-        return _lib
     if not os.path.exists(LIB_PATH):
         raise RuntimeError(f"{LIB_PATH} is not built; run __graft_entry__.build()")
     L = ctypes.CDLL(LIB_PATH)
@@ -139,54 +141,60 @@ class Layout:
         _check(lib().nmg_layout_init(ctypes.byref(self.c), M, K, n, m, g, _DTYPE_CODE[dtype]),
                "nmg_layout_init")
         self.dtype = dtype
+        self._derive()
 
-    M = property(lambda s: s.c.M)
-    K = property(lambda s: s.c.K)
-    n = property(lambda s: s.c.n)
-    m = property(lambda s: s.c.m)
-    g = property(lambda s: s.c.g)
-    C = property(lambda s: s.c.C)
+    def _derive(self):
+        c = self.c
+        self.M, self.K, self.n, self.m, self.g, self.C = c.M, c.K, c.n, c.m, c.g, c.C
+        self.values_shape = (self.M, self.C * self.n)
+        self.indices_shape = (self.M // self.g, self.C * self.n)
+        self._ws = (None, 0)     # (kernel, N) of the last product and its workspace bytes
 
-    @property
-    def values_shape(self):
-        return (self.M, self.C * self.n)
+    def __getstate__(self):
+        return {"c": self.c, "dtype": self.dtype}
 
-    @property
-    def indices_shape(self):
-        return (self.M // self.g, self.C * self.n)
+    def __setstate__(self, state):
+        self.c, self.dtype = state["c"], state["dtype"]
+        self._derive()
 
     def __repr__(self):
         return (f"Layout(M={self.M}, K={self.K}, n={self.n}, m={self.m}, g={self.g}, "
                 f"C={self.C}, dtype={self.dtype})")
 
 
-def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
-
-
-def _ptr(t: torch.Tensor):
-    return ctypes.c_void_p(t.data_ptr())
+def _stream(t: torch.Tensor) -> int:
+    """The raw handle of the current stream of t's device."""
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 def _need_cuda(*ts):
     """Every tensor on the current GPU: the library launches on the current
     HIP device, on that device's current stream."""
-    cur = None
+    cur = -1
     for t in ts:
-        if not t.is_cuda:
+        dev = t.get_device()
+        if dev < 0 or not t.is_cuda:
             raise ValueError("libnmg works on GPU tensors only")
-        if cur is None:
-            cur = torch.cuda.current_device()
-        if t.device.index != cur:
+        if cur < 0:
+            cur = torch._C._cuda_getDevice()
+        if dev != cur:
             raise ValueError(f"tensor on {t.device}, but the current device is cuda:{cur} "
                              "(select it with torch.cuda.device)")
 
 
-def _rows(t: torch.Tensor, name: str):
+def _rows(t: torch.Tensor, name: str) -> int:
     """Leading dimension of a 2-D row-major tensor (unit stride along rows)."""
-    if t.dim() != 2 or t.stride(1) != 1:
+    st = t.stride()
+    if len(st) != 2 or st[1] != 1:
         raise ValueError(f"{name} must be a 2-D tensor with unit column stride")
-    return t.stride(0)
+    return st[0]
+
+
+def _packed_ok(layout, values, indices):
+    if values.shape != layout.values_shape or not values.is_contiguous():
+        raise ValueError(f"values must be contiguous {layout.values_shape}")
+    if indices.shape != layout.indices_shape or not indices.is_contiguous():
+        raise ValueError(f"indices must be contiguous {layout.indices_shape}")
 
 
 def _workspace(nbytes: int, like: torch.Tensor):
@@ -194,9 +202,18 @@ def _workspace(nbytes: int, like: torch.Tensor):
     bytes).  Freed after the call returns; the allocator hands it out again in
     stream order on the current stream only."""
     if nbytes <= 0:
-        return None, ctypes.c_void_p(0), 0
+        return None, None, 0
     ws = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
-    return ws, _ptr(ws), nbytes
+    return ws, ws.data_ptr(), nbytes
+
+
+def _workspace_bytes(layout, code: int, N: int) -> int:
+    """nmg_spmm_workspace_bytes (a function of the layout, kernel and N)."""
+    key, nbytes = layout._ws
+    if key != (code, N):
+        nbytes = lib().nmg_spmm_workspace_bytes(layout.c, code, N)
+        layout._ws = ((code, N), nbytes)
+    return nbytes
 
 
 def compress_into(layout: Layout, W: torch.Tensor, values: torch.Tensor, indices: torch.Tensor):
@@ -204,20 +221,17 @@ def compress_into(layout: Layout, W: torch.Tensor, values: torch.Tensor, indices
     _need_cuda(W, values, indices)
     if W.dtype != layout.dtype or values.dtype != layout.dtype or indices.dtype != torch.uint8:
         raise TypeError("dtype mismatch")
-    if tuple(W.shape) != (layout.M, layout.K):
+    if W.shape != (layout.M, layout.K):
         raise ValueError(f"W must be {layout.M} x {layout.K}")
-    if tuple(values.shape) != layout.values_shape or not values.is_contiguous():
-        raise ValueError(f"values must be contiguous {layout.values_shape}")
-    if tuple(indices.shape) != layout.indices_shape or not indices.is_contiguous():
-        raise ValueError(f"indices must be contiguous {layout.indices_shape}")
-    _check(lib().nmg_compress(ctypes.byref(layout.c), _ptr(W), _rows(W, "W"), _ptr(values),
-                              _ptr(indices), _stream(W)), "nmg_compress")
+    _packed_ok(layout, values, indices)
+    _check(lib().nmg_compress(layout.c, W.data_ptr(), _rows(W, "W"), values.data_ptr(),
+                              indices.data_ptr(), _stream(W)), "nmg_compress")
 
 
 def compress(W: torch.Tensor, n: int, m: int, g: int):
     """Dense W (M x K, GPU) -> (values, indices, layout)."""
     layout = Layout(W.shape[0], W.shape[1], n, m, g, W.dtype)
-    values = torch.empty(layout.values_shape, dtype=W.dtype, device=W.device)
+    values = W.new_empty(layout.values_shape)
     indices = torch.empty(layout.indices_shape, dtype=torch.uint8, device=W.device)
     compress_into(layout, W, values, indices)
     return values, indices, layout
@@ -229,13 +243,13 @@ def repack(W: torch.Tensor, indices: torch.Tensor, layout: Layout) -> torch.Tens
     _need_cuda(W, indices)
     if W.dtype != layout.dtype or indices.dtype != torch.uint8:
         raise TypeError("dtype mismatch")
-    if tuple(W.shape) != (layout.M, layout.K):
+    if W.shape != (layout.M, layout.K):
         raise ValueError(f"W must be {layout.M} x {layout.K}")
-    if tuple(indices.shape) != layout.indices_shape or not indices.is_contiguous():
+    if indices.shape != layout.indices_shape or not indices.is_contiguous():
         raise ValueError(f"indices must be contiguous {layout.indices_shape}")
-    values = torch.empty(layout.values_shape, dtype=W.dtype, device=W.device)
-    _check(lib().nmg_repack(ctypes.byref(layout.c), _ptr(W), _rows(W, "W"), _ptr(indices),
-                            _ptr(values), _stream(W)), "nmg_repack")
+    values = W.new_empty(layout.values_shape)
+    _check(lib().nmg_repack(layout.c, W.data_ptr(), _rows(W, "W"), indices.data_ptr(),
+                            values.data_ptr(), _stream(W)), "nmg_repack")
     return values
 
 
@@ -248,12 +262,12 @@ X16_KERNELS = {"mfma_wide": torch.float16, "mfma_split": torch.float32}
 def x16_prepare(values, indices, layout: Layout) -> torch.Tensor:
     """``nmg_x16_prepare``: the prepared operands of a packed weight (bytes)."""
     _need_cuda(values, indices)
-    nbytes = lib().nmg_x16_prepared_bytes(ctypes.byref(layout.c))
+    nbytes = lib().nmg_x16_prepared_bytes(layout.c)
     if nbytes < 0:
         raise NmgError(ERR_UNSUPPORTED, "nmg_x16_prepared_bytes")
     prepared = torch.empty(int(nbytes), dtype=torch.uint8, device=values.device)
-    _check(lib().nmg_x16_prepare(ctypes.byref(layout.c), _ptr(values), _ptr(indices),
-                                 _ptr(prepared), _stream(values)), "nmg_x16_prepare")
+    _check(lib().nmg_x16_prepare(layout.c, values.data_ptr(), indices.data_ptr(),
+                                 prepared.data_ptr(), _stream(values)), "nmg_x16_prepare")
     return prepared
 
 
@@ -264,8 +278,8 @@ def spmm_x16_into(layout: Layout, prepared, X, Y):
         raise TypeError("dtype mismatch")
     if X.shape[0] != layout.K or Y.shape[0] != layout.M or Y.shape[1] != X.shape[1]:
         raise ValueError("X must be K x N and Y M x N")
-    _check(lib().nmg_spmm_x16(ctypes.byref(layout.c), _ptr(prepared), _ptr(X), _rows(X, "X"),
-                              X.shape[1], _ptr(Y), _rows(Y, "Y"), _stream(X)), "nmg_spmm_x16")
+    _check(lib().nmg_spmm_x16(layout.c, prepared.data_ptr(), X.data_ptr(), _rows(X, "X"),
+                              X.shape[1], Y.data_ptr(), _rows(Y, "Y"), _stream(X)), "nmg_spmm_x16")
 
 
 def spmm_x16_epilogue(layout: Layout, prepared, X, epilogue: str = "none", R=None, Y=None):
@@ -276,21 +290,21 @@ def spmm_x16_epilogue(layout: Layout, prepared, X, epilogue: str = "none", R=Non
         raise ValueError("X must be K x N of the layout's dtype")
     N = X.shape[1]
     if Y is None:
-        Y = torch.empty((layout.M, N), dtype=X.dtype, device=X.device)
+        Y = X.new_empty((layout.M, N))
     _need_cuda(Y)
-    if Y.dtype != layout.dtype or tuple(Y.shape) != (layout.M, N):
+    if Y.dtype != layout.dtype or Y.shape != (layout.M, N):
         raise ValueError("Y must be M x N of the layout's dtype")
-    rp, ldr = ctypes.c_void_p(0), 0
+    rp, ldr = None, 0
     if epilogue == "add":
         if R is None:
             raise ValueError("the add epilogue needs R")
         _need_cuda(R)
-        if R.dtype != layout.dtype or tuple(R.shape) != (layout.M, N):
+        if R.dtype != layout.dtype or R.shape != (layout.M, N):
             raise ValueError("R must be M x N of the layout's dtype")
-        rp, ldr = _ptr(R), _rows(R, "R")
-    _check(lib().nmg_spmm_x16_epilogue(ctypes.byref(layout.c), _ptr(prepared),
-                                       EPILOGUES[epilogue], _ptr(X), _rows(X, "X"), N, rp, ldr,
-                                       _ptr(Y), _rows(Y, "Y"), _stream(X)),
+        rp, ldr = R.data_ptr(), _rows(R, "R")
+    _check(lib().nmg_spmm_x16_epilogue(layout.c, prepared.data_ptr(),
+                                       EPILOGUES[epilogue], X.data_ptr(), _rows(X, "X"), N, rp, ldr,
+                                       Y.data_ptr(), _rows(Y, "Y"), _stream(X)),
            "nmg_spmm_x16_epilogue")
     return Y
 
@@ -303,21 +317,18 @@ def spmm_into(layout: Layout, values, indices, X, Y, kernel: str = "auto"):
         raise TypeError("dtype mismatch")
     if X.shape[0] != layout.K or Y.shape[0] != layout.M or Y.shape[1] != X.shape[1]:
         raise ValueError("X must be K x N and Y M x N")
-    if tuple(values.shape) != layout.values_shape or not values.is_contiguous():
-        raise ValueError(f"values must be contiguous {layout.values_shape}")
-    if tuple(indices.shape) != layout.indices_shape or not indices.is_contiguous():
-        raise ValueError(f"indices must be contiguous {layout.indices_shape}")
+    _packed_ok(layout, values, indices)
     L = lib()
     N, code = X.shape[1], KERNELS[kernel]
-    ws, wp, wb = _workspace(L.nmg_spmm_workspace_bytes(ctypes.byref(layout.c), code, N), X)
-    _check(L.nmg_spmm_epilogue_ws(ctypes.byref(layout.c), code, 0, _ptr(values), _ptr(indices),
-                                  _ptr(X), _rows(X, "X"), N, None, 0, _ptr(Y), _rows(Y, "Y"),
+    ws, wp, wb = _workspace(_workspace_bytes(layout, code, N), X)
+    _check(L.nmg_spmm_epilogue_ws(layout.c, code, 0, values.data_ptr(), indices.data_ptr(),
+                                  X.data_ptr(), _rows(X, "X"), N, None, 0, Y.data_ptr(), _rows(Y, "Y"),
                                   wp, wb, _stream(X)), "nmg_spmm")
 
 
 def spmm(values, indices, X, layout: Layout, kernel: str = "auto"):
     """Y = W_s X for the packed weight (values, indices)."""
-    Y = torch.empty((layout.M, X.shape[1]), dtype=X.dtype, device=X.device)
+    Y = X.new_empty((layout.M, X.shape[1]))
     spmm_into(layout, values, indices, X, Y, kernel)
     return Y
 
@@ -348,44 +359,40 @@ def _spmm_epilogue(fn, values, indices, X, layout, epilogue, R, kernel, Y):
         raise TypeError("dtype mismatch")
     if X.shape[0] != layout.K:
         raise ValueError("X must be K x N")
-    if tuple(values.shape) != layout.values_shape or not values.is_contiguous():
-        raise ValueError(f"values must be contiguous {layout.values_shape}")
-    if tuple(indices.shape) != layout.indices_shape or not indices.is_contiguous():
-        raise ValueError(f"indices must be contiguous {layout.indices_shape}")
+    _packed_ok(layout, values, indices)
     N = X.shape[1]
     if Y is None:
-        Y = torch.empty((layout.M, N), dtype=X.dtype, device=X.device)
+        Y = X.new_empty((layout.M, N))
     _need_cuda(Y)
-    if Y.dtype != layout.dtype or tuple(Y.shape) != (layout.M, N):
+    if Y.dtype != layout.dtype or Y.shape != (layout.M, N):
         raise ValueError("Y must be M x N of the layout's dtype")
-    rp, ldr = ctypes.c_void_p(0), 0
+    rp, ldr = None, 0
     if epilogue == "add":
         if R is None:
             raise ValueError("the add epilogue needs R")
         _need_cuda(R)
-        if R.dtype != layout.dtype or tuple(R.shape) != (layout.M, N):
+        if R.dtype != layout.dtype or R.shape != (layout.M, N):
             raise ValueError("R must be M x N of the layout's dtype")
-        rp, ldr = _ptr(R), _rows(R, "R")
+        rp, ldr = R.data_ptr(), _rows(R, "R")
     L = lib()
-    args = [ctypes.byref(layout.c), KERNELS[kernel], EPILOGUES[epilogue], _ptr(values),
-            _ptr(indices), _ptr(X), _rows(X, "X"), N, rp, ldr, _ptr(Y), _rows(Y, "Y")]
+    args = [layout.c, KERNELS[kernel], EPILOGUES[epilogue], values.data_ptr(),
+            indices.data_ptr(), X.data_ptr(), _rows(X, "X"), N, rp, ldr, Y.data_ptr(), _rows(Y, "Y")]
     if fn == "nmg_spmm_epilogue_ws":
-        nbytes = L.nmg_spmm_workspace_bytes(args[0], args[1], N)
-        ws, wp, wb = _workspace(nbytes, X)
+        ws, wp, wb = _workspace(_workspace_bytes(layout, args[1], N), X)
         args += [wp, wb]
     _check(getattr(L, fn)(*args, _stream(X)), fn)
     return Y
 
 
 def auto_kernel(layout: Layout, N: int) -> str:
-    return _KERNEL_NAME[lib().nmg_spmm_auto_kernel(ctypes.byref(layout.c), N)]
+    return _KERNEL_NAME[lib().nmg_spmm_auto_kernel(layout.c, N)]
 
 
 def densify(values, indices, layout: Layout):
     """(values, indices) -> dense M x K weight (zeros at dropped positions)."""
     _need_cuda(values, indices)
-    out = torch.empty((layout.M, layout.K), dtype=layout.dtype, device=values.device)
-    _check(lib().nmg_densify(ctypes.byref(layout.c), _ptr(values), _ptr(indices), _ptr(out),
+    out = values.new_empty((layout.M, layout.K), dtype=layout.dtype)
+    _check(lib().nmg_densify(layout.c, values.data_ptr(), indices.data_ptr(), out.data_ptr(),
                              layout.K, _stream(values)), "nmg_densify")
     return out
 
@@ -395,7 +402,7 @@ def gelu(x: torch.Tensor, out: torch.Tensor | None = None):
     if not x.is_contiguous():
         raise ValueError("x must be contiguous")
     out = torch.empty_like(x) if out is None else out
-    _check(lib().nmg_gelu(_DTYPE_CODE[x.dtype], _ptr(x), _ptr(out), x.numel(), _stream(x)),
+    _check(lib().nmg_gelu(_DTYPE_CODE[x.dtype], x.data_ptr(), out.data_ptr(), x.numel(), _stream(x)),
            "nmg_gelu")
     return out
 
@@ -405,7 +412,7 @@ def add(a: torch.Tensor, b: torch.Tensor, out: torch.Tensor | None = None):
     if a.shape != b.shape or a.dtype != b.dtype or not (a.is_contiguous() and b.is_contiguous()):
         raise ValueError("a and b must be contiguous tensors of one shape and dtype")
     out = torch.empty_like(a) if out is None else out
-    _check(lib().nmg_add(_DTYPE_CODE[a.dtype], _ptr(a), _ptr(b), _ptr(out), a.numel(),
+    _check(lib().nmg_add(_DTYPE_CODE[a.dtype], a.data_ptr(), b.data_ptr(), out.data_ptr(), a.numel(),
                          _stream(a)), "nmg_add")
     return out
 
@@ -422,33 +429,31 @@ class PLayout:
         _check(lib().nmg_p_layout_init(ctypes.byref(self.c), M, K, n, m, g, _DTYPE_CODE[dtype]),
                "nmg_p_layout_init")
         self.dtype = dtype
+        self._derive()
 
-    M = property(lambda s: s.c.M)
-    K = property(lambda s: s.c.K)
-    n = property(lambda s: s.c.n)
-    m = property(lambda s: s.c.m)
-    g = property(lambda s: s.c.g)
-    P = property(lambda s: s.c.P)
-    S = property(lambda s: s.c.S)
-    B = property(lambda s: s.c.B)
+    def _derive(self):
+        c = self.c
+        self.M, self.K, self.n, self.m, self.g = c.M, c.K, c.n, c.m, c.g
+        self.P, self.S, self.B = c.P, c.S, c.B
+        self.values_shape = (self.M, self.B * self.n)
+        self.index_shape = (self.M, self.B)
 
-    @property
-    def values_shape(self):
-        return (self.M, self.B * self.n)
+    def __getstate__(self):
+        return {"c": self.c, "dtype": self.dtype}
 
-    @property
-    def index_shape(self):
-        return (self.M, self.B)
+    def __setstate__(self, state):
+        self.c, self.dtype = state["c"], state["dtype"]
+        self._derive()
 
 
 def p_compress(W: torch.Tensor, n: int, m: int, g: int):
     """Dense W (M x K, GPU) -> (values, index, layout) in the chunked layout."""
     _need_cuda(W)
     layout = PLayout(W.shape[0], W.shape[1], n, m, g, W.dtype)
-    values = torch.empty(layout.values_shape, dtype=W.dtype, device=W.device)
+    values = W.new_empty(layout.values_shape)
     index = torch.empty(layout.index_shape, dtype=torch.uint8, device=W.device)
-    _check(lib().nmg_p_compress(ctypes.byref(layout.c), _ptr(W), _rows(W, "W"), _ptr(values),
-                                _ptr(index), _stream(W)), "nmg_p_compress")
+    _check(lib().nmg_p_compress(layout.c, W.data_ptr(), _rows(W, "W"), values.data_ptr(),
+                                index.data_ptr(), _stream(W)), "nmg_p_compress")
     return values, index, layout
 
 
@@ -456,9 +461,9 @@ def _p_check(layout: PLayout, values, index):
     _need_cuda(values, index)
     if values.dtype != layout.dtype or index.dtype != torch.uint8:
         raise TypeError("dtype mismatch")
-    if tuple(values.shape) != layout.values_shape or not values.is_contiguous():
+    if values.shape != layout.values_shape or not values.is_contiguous():
         raise ValueError(f"values must be contiguous {layout.values_shape}")
-    if tuple(index.shape) != layout.index_shape or not index.is_contiguous():
+    if index.shape != layout.index_shape or not index.is_contiguous():
         raise ValueError(f"index must be contiguous {layout.index_shape}")
 
 
@@ -470,12 +475,12 @@ def p_spmm(values, index, X, layout: PLayout, kernel: str = "auto"):
         raise ValueError("X must be K x N of the layout's dtype")
     if kernel not in ("auto", "valu", "mfma"):
         raise ValueError(f"unknown chunked-layout kernel {kernel!r}")
-    Y = torch.empty((layout.M, X.shape[1]), dtype=X.dtype, device=X.device)
+    Y = X.new_empty((layout.M, X.shape[1]))
     L = lib()
     N, code = X.shape[1], KERNELS[kernel]
-    ws, wp, wb = _workspace(L.nmg_p_spmm_workspace_bytes(ctypes.byref(layout.c), code, N), X)
-    _check(L.nmg_p_spmm_ws(ctypes.byref(layout.c), code, _ptr(values), _ptr(index), _ptr(X),
-                           _rows(X, "X"), N, _ptr(Y), _rows(Y, "Y"), wp, wb, _stream(X)),
+    ws, wp, wb = _workspace(L.nmg_p_spmm_workspace_bytes(layout.c, code, N), X)
+    _check(L.nmg_p_spmm_ws(layout.c, code, values.data_ptr(), index.data_ptr(), X.data_ptr(),
+                           _rows(X, "X"), N, Y.data_ptr(), _rows(Y, "Y"), wp, wb, _stream(X)),
            "nmg_p_spmm_ws")
     return Y
 
@@ -483,8 +488,8 @@ def p_spmm(values, index, X, layout: PLayout, kernel: str = "auto"):
 def p_densify(values, index, layout: PLayout):
     """Chunked layout -> dense M x K weight."""
     _p_check(layout, values, index)
-    out = torch.empty((layout.M, layout.K), dtype=layout.dtype, device=values.device)
-    _check(lib().nmg_p_densify(ctypes.byref(layout.c), _ptr(values), _ptr(index), _ptr(out),
+    out = values.new_empty((layout.M, layout.K), dtype=layout.dtype)
+    _check(lib().nmg_p_densify(layout.c, values.data_ptr(), index.data_ptr(), out.data_ptr(),
                                layout.K, _stream(values)), "nmg_p_densify")
     return out
 
@@ -495,12 +500,12 @@ def p_refine(W: torch.Tensor, index: torch.Tensor, layout: PLayout):
     _need_cuda(W, index)
     if W.dtype != layout.dtype or index.dtype != torch.uint8:
         raise TypeError("dtype mismatch")
-    if tuple(W.shape) != (layout.M, layout.K):
+    if W.shape != (layout.M, layout.K):
         raise ValueError(f"W must be {layout.M} x {layout.K}")
-    if tuple(index.shape) != layout.index_shape:
+    if index.shape != layout.index_shape:
         raise ValueError(f"index must be {layout.index_shape}")
     idx = index.contiguous().clone()
-    values = torch.empty(layout.values_shape, dtype=W.dtype, device=W.device)
-    _check(lib().nmg_p_refine(ctypes.byref(layout.c), _ptr(W), _rows(W, "W"), _ptr(values),
-                              _ptr(idx), _stream(W)), "nmg_p_refine")
+    values = W.new_empty(layout.values_shape)
+    _check(lib().nmg_p_refine(layout.c, W.data_ptr(), _rows(W, "W"), values.data_ptr(),
+                              idx.data_ptr(), _stream(W)), "nmg_p_refine")
     return values, idx
