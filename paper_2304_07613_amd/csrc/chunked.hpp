@@ -35,6 +35,15 @@ __host__ __device__ inline void p_unrank(int m, int n, int idx, uint8_t *out) {
     }
 }
 
+// Division of e < 2^16 by 1 <= d < 2^16 through a multiply-high: with
+// mul = ceil(2^32 / d), floor(e mul / 2^32) = floor(e / d) since e d < 2^32.
+__device__ __forceinline__ uint32_t magic_u16(uint32_t d) {
+    return d > 1 ? (uint32_t)(0xffffffffu / d + 1u) : 0u;
+}
+__device__ __forceinline__ uint32_t div_u16(uint32_t e, uint32_t mul, uint32_t d) {
+    return d > 1 ? __umulhi(e, mul) : e;
+}
+
 __device__ __forceinline__ void p_wave_sync() {
     // this wave's LDS writes are done before its later LDS reads
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

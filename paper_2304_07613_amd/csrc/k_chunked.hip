@@ -505,15 +505,6 @@ constexpr int kPmLdr = kPmKw + 4;         // row path, A[row][k]: 16 rows' 16-by
                                           // reads cover the 256 bytes of banks once
 constexpr int kPmPre = 8;                 // kept weights prefetched per thread and window
 
-// Division of e < 2^16 by 1 <= d < 2^16 through a multiply-high: with
-// mul = ceil(2^32 / d), floor(e mul / 2^32) = floor(e / d) since e d < 2^32.
-__device__ __forceinline__ uint32_t magic_u16(uint32_t d) {
-    return d > 1 ? (uint32_t)(0xffffffffu / d + 1u) : 0u;
-}
-__device__ __forceinline__ uint32_t div_u16(uint32_t e, uint32_t mul, uint32_t d) {
-    return d > 1 ? __umulhi(e, mul) : e;
-}
-
 // N4 > 0: m = 4 and n = N4 <= 3 with whole windows (B % 8 == 0), values on
 // 16-byte and the index on 4-byte boundaries, and at most 256 stored rows per
 // tile: thread j owns stored row j of the tile's chunks for the whole K loop

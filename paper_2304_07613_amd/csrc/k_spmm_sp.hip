@@ -36,14 +36,16 @@
 // places without a kept column hold 0.
 //
 // X.  The other operand wants, per lane, 8 consecutive columns of one token
-// side by side.  A thread loads 8 rows x 4 tokens of X, splits and packs them
+// side by side.  A lane loads 8 rows x 2 tokens of X, splits and packs them
 // along the columns and writes 16-byte units to LDS, unit (column / 8, token)
 // -- so the operand is two plain 16-byte LDS reads, X may have any alignment
-// and any token count, and no transposing read or bank conflict is left
-// (tokens are permuted within fours, sp_unit, for the 4-token writes).
-// Four waves (2 x 2) share a tile of 32 RT rows x 128 tokens; two workgroups
-// per CU.  X goes through two LDS buffers: step s + 1 is split and written
-// between the products of step s, while step s + 2 is loaded.
+// and any token count, and no transposing read is left.  X and Y move as
+// vectors that are only element-aligned (the hardware takes unaligned global
+// accesses): rows of an odd number of tokens cost the same instructions
+// (binary16 3072 x 768 x 2047: 28 us with element-wise loads and stores).
+// Eight waves (4 x 2) share a tile of 64 RT rows x 128 tokens, one workgroup
+// per CU.  X goes through two LDS buffers: pass p + 1 is split and written
+// between the products of pass p, while pass p + 2 is loaded.
 #include "chunked.hpp"
 
 namespace {
@@ -333,11 +335,18 @@ __global__ __launch_bounds__(kSpPrep) void k_sp_prepare(const float *__restrict_
 }
 
 constexpr int kSpcRows = 256;          // chunk rows per workgroup, at most (S <= 256)
-constexpr int kSpcSteps = 4;           // steps per workgroup
-constexpr int kSpcThreads = 1024;
+constexpr int kSpcSteps = 2;           // steps per workgroup
+constexpr int kSpcThreads = 512;
+
+// the offsets of at most 8 patterns, n each, worked out on the host (the
+// unranking divides 64-bit numbers: 2 us at the head of the kernel)
+constexpr int kSpFew = 8;
+struct SpPatterns {
+    uint8_t off[kSpFew * 2];
+};
 
 // The chunked layout (m in {4, 8, 16}, n <= 2): a workgroup takes `cpw` chunks
-// (whole 16-row tiles, at most 256 rows) of 4 steps' block columns, inverts
+// (whole 16-row tiles, at most 256 rows) of 2 steps' block columns, inverts
 // their index in LDS and gathers every row's blocks.  Binary32: its rows share
 // one scale, from the largest of their kept weights (found again by each
 // workgroup of the same chunks: they lie side by side in memory).  One
@@ -345,8 +354,8 @@ constexpr int kSpcThreads = 1024;
 template <typename T>
 __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
     const T *__restrict__ values, const uint8_t *__restrict__ index, const T *__restrict__ X, int64_t ldx,
-    SpScratch ws, int M, int M16, int K, int N, int n, int m, int g, int P, int S, int B, int cpw,
-    int nsteps, int groups, int sblocks) {
+    SpScratch ws, SpPatterns few, int M, int M16, int K, int N, int n, int m, int g, int P, int S, int B,
+    int cpw, int nsteps, int groups, int sblocks) {
     __shared__ uint8_t inv[kSpcSteps * 16 * kSpcRows];    // position of (block column, chunk row)
     __shared__ uint8_t pat[256 * 2];
     __shared__ uint32_t red[kSpcThreads];
@@ -364,7 +373,11 @@ __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
     const int b0 = s0 * bps, ns = min(kSpcSteps, nsteps - s0);
     const int nb = min(ns * bps, B - b0);
     const int64_t ldv = (int64_t)B * n;
-    for (int p = tid; p < P; p += kSpcThreads) p_unrank(m, n, p, pat + p * n);
+    if (P <= kSpFew) {
+        if (tid < kSpFew * 2) pat[tid] = few.off[tid];
+    } else {
+        for (int p = tid; p < P; p += kSpcThreads) p_unrank(m, n, p, pat + p * n);
+    }
     for (int i = tid; i < ns * bps * kSpcRows / 4; i += kSpcThreads) reinterpret_cast<uint32_t *>(inv)[i] = 0;
     float scale = 1.f;
     if constexpr (sp_parts<T>() == 2) {
@@ -374,28 +387,57 @@ __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
             for (int t = tid; 16 * t < rows; t += kSpcThreads) ws.wexp[r0 / 16 + t] = e;
     }
     __syncthreads();
-    for (int i = tid; i < rows * nb; i += kSpcThreads) {
-        const int j = i / nb, w = i - j * nb;
-        const int ch = j / S;
-        const int r = min((int)index[(int64_t)(r0 + j) * B + b0 + w], S - 1);
-        inv[w * kSpcRows + ch * S + r] = (uint8_t)(j - ch * S);
+    // stored row j's index bytes of the block columns, 4 at a time where its
+    // rows are whole words
+    const uint32_t ms = magic_u16(S);
+    if (B % 4 == 0 && nb % 4 == 0 && b0 % 4 == 0 && (reinterpret_cast<uintptr_t>(index) & 3) == 0) {
+        const int nw = nb >> 2;
+        const uint32_t mw = magic_u16(nw);
+        for (int i = tid; i < rows * nw; i += kSpcThreads) {
+            const int j = (int)div_u16(i, mw, nw), w = 4 * (i - j * nw);
+            const int ch = (int)div_u16(j, ms, S);
+            const uint32_t v = *reinterpret_cast<const uint32_t *>(index + (int64_t)(r0 + j) * B + b0 + w);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                inv[(w + k) * kSpcRows + ch * S + min((int)((v >> (8 * k)) & 0xffu), S - 1)] = (uint8_t)(j - ch * S);
+        }
+    } else {
+        const uint32_t mb = magic_u16(nb);
+        for (int i = tid; i < rows * nb; i += kSpcThreads) {
+            const int j = (int)div_u16(i, mb, nb), w = i - j * nb;
+            const int ch = (int)div_u16(j, ms, S);
+            const int r = min((int)index[(int64_t)(r0 + j) * B + b0 + w], S - 1);
+            inv[w * kSpcRows + ch * S + r] = (uint8_t)(j - ch * S);
+        }
     }
     __syncthreads();
     const int bpl = 16 / m;                   // blocks per lane
     // 4 column ranges of every row and step, rows fastest
+    const uint32_t mr = magic_u16(rows), mg = magic_u16(g);
     for (int i = tid; i < rows * 4 * ns; i += kSpcThreads) {
-        const int sq = i / rows, rr = i - sq * rows;   // chunk row
-        const int sl = sq >> 2, q = sq & 3;            // step, 16-column range
-        const int base = rr / S * S;
-        SpLane<T> a;
-        for (int k = 0; k < bpl; ++k) {
-            const int w = (4 * sl + q) * bpl + k;
-            if (w >= nb) break;
+        const int sq = (int)div_u16(i, mr, rows), rr = i - sq * rows;   // chunk row
+        const int sl = sq >> 2, q = sq & 3;                             // step, 16-column range
+        const int base = (int)div_u16(rr, ms, S) * S;
+        // the row's 1 to 4 blocks: every load in flight together
+        T w0[4], w1[4];
+        int o0[4], o1[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int w = min((4 * sl + q) * bpl + min(k, bpl - 1), nb - 1);
             const int j = inv[w * kSpcRows + rr];
             const T *v = values + (int64_t)(r0 + base + j) * ldv + (int64_t)(b0 + w) * n;
-            const uint8_t *off = pat + (j / g) * n;
-            a.put(k * m + off[0], v[0], true);
-            if (n == 2) a.put(k * m + off[1], v[1], true);
+            const uint8_t *off = pat + div_u16(j, mg, g) * n;
+            w0[k] = v[0];
+            w1[k] = n == 2 ? v[1] : v[0];
+            o0[k] = off[0];
+            o1[k] = off[n - 1];
+        }
+        SpLane<T> a;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool in = k < bpl && (4 * sl + q) * bpl + k < nb;
+            a.put(min(k * m + o0[k], 15), w0[k], in);
+            a.put(min(k * m + o1[k], 15), w1[k], in && n == 2);
         }
         const int row = r0 + rr;
         sp_store<T>(ws.stream + ((int64_t)(row >> 4) * nsteps + s0 + sl) * sp_tile_bytes(sp_parts<T>()),
@@ -418,6 +460,22 @@ __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
 __device__ __forceinline__ void sp_barrier() {
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
+}
+
+// A pointer the same in every lane, in scalar registers: loads at it plus a
+// lane's 32-bit offset then need no 64-bit vector arithmetic (the compiler
+// otherwise folds the row's offset into the lane's: three vector instructions
+// a load)
+typedef __attribute__((address_space(1))) const char sp_global;
+__device__ __forceinline__ sp_global *sp_uniform(const char *p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return reinterpret_cast<sp_global *>(((uint64_t)hi << 32) | lo);
+#else
+    return (sp_global *)p;
 #endif
 }
 
@@ -449,7 +507,7 @@ __device__ __attribute__((noinline)) float sp_chain(const char *stream, const T 
     return acc;
 }
 
-// RT 16-row tiles per wave; VEC: X rows on 2-element boundaries and N even
+// RT 16-row tiles per wave; VEC: two tokens a load (N >= 2)
 template <typename T, int RT, bool VEC>
 __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *__restrict__ X, int64_t ldx,
                                                         T *__restrict__ Y, int64_t ldy, int M, int K,
@@ -504,6 +562,7 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
     // step, every lane 8 rows x 2 tokens
     constexpr int XR = 8 * SUB;
     typedef T X2 __attribute__((ext_vector_type(2)));
+    typedef X2 X2u __attribute__((aligned(sizeof(T))));   // element-aligned
     X2 x[XR];
     int xt[2];                                      // this lane's tokens within the tile
     uint32_t xoff[2];                               // bytes
@@ -512,18 +571,31 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
         xt[j] = VEC ? 2 * lane + j : lane + 64 * j;
         xoff[j] = (uint32_t)min(t0 + xt[j], VEC ? N - 2 + j : N - 1) * ES;
     }
+    // a pair that starts with the last token is loaded one token earlier, and
+    // written with its two places exchanged
+    if (VEC && t0 + xt[0] == N - 1) {
+        xt[1] = xt[0];
+        xt[0] ^= 1;
+    }
     float xscale[2] = {1.f, 1.f};
+    const uint32_t ldb = (uint32_t)(ldx * ES);      // host: ldx ES < 2^31
     auto load_x = [&](int p) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < XR; ++r) {
-            // rows past K: the last one (zero weights)
-            const int k = min((p * SUB + r / 8) * kSpK + 8 * wave + r % 8, K - 1);   // uniform
-            const char *xb = reinterpret_cast<const char *>(X) + (int64_t)k * ldx * ES;
-            if constexpr (VEC) {
-                x[r] = *reinterpret_cast<const X2 *>(xb + xoff[0]);
-            } else {
+        for (int q = 0; q < SUB; ++q) {
+            // row by row from a scalar pointer; past K the last row again
+            // (zero weights)
+            const int k = (p * SUB + q) * kSpK + 8 * wave;
+            sp_global *xb = sp_uniform(reinterpret_cast<const char *>(X) + (uint64_t)(uint32_t)min(k, K - 1) * ldb);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) x[r][j] = *reinterpret_cast<const T *>(xb + xoff[j]);
+            for (int r = 0; r < 8; ++r) {
+                X2 &d = x[8 * q + r];
+                if constexpr (VEC) {
+                    d = *(__attribute__((address_space(1))) const X2u *)(xb + xoff[0]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) d[j] = *(__attribute__((address_space(1))) const T *)(xb + xoff[j]);
+                }
+                xb += k + r + 1 < K ? ldb : 0u;
             }
         }
     };
@@ -664,6 +736,7 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
     constexpr int LPR = 64 / EPL;                   // lanes per row
     constexpr int RPI = 64 / LPR;                   // rows per store instruction
     typedef T OV __attribute__((ext_vector_type(EPL)));
+    typedef OV OVu __attribute__((aligned(sizeof(T))));   // element-aligned
     int xe[4] = {0, 0, 0, 0};
     if constexpr (PARTS == 2) {
 #pragma unroll
@@ -695,8 +768,8 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
             if (R != nullptr) {   // the sum in binary32 of the rounded product and R, rounded again
                 const T *res = R + (int64_t)row * ldr + tok;
                 OV rv = {};
-                if (yvec && tok + EPL <= N) {
-                    rv = *reinterpret_cast<const OV *>(res);
+                if (tok + EPL <= N) {
+                    rv = *reinterpret_cast<const OVu *>(res);
                 } else {
 #pragma unroll
                     for (int e = 0; e < EPL; ++e)
@@ -705,8 +778,11 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) v[e] = (T)((float)v[e] + (float)rv[e]);
             }
-            if (yvec && tok + EPL <= N) {
-                __builtin_nontemporal_store(v, reinterpret_cast<OV *>(y));
+            if (tok + EPL <= N) {
+                // whole aligned rows past the caches; unaligned runs share
+                // lines with their neighbours, which the caches merge
+                if (yvec) __builtin_nontemporal_store(v, reinterpret_cast<OV *>(y));
+                else *reinterpret_cast<OVu *>(y) = v;
             } else {
 #pragma unroll
                 for (int e = 0; e < EPL; ++e)
@@ -749,9 +825,9 @@ void sp_launch(const SpScratch &ws, const void *X, int64_t ldx, int M, int K, in
     const int nsteps = (int)sp_steps(K, sp_parts<T>()), tiles16 = (int)sp_tiles(M);
     const int row_blocks = (tiles16 + 4 * RT - 1) / (4 * RT);
     const int tok_tiles = (N + kSpTok - 1) / kSpTok;
-    const bool vec = aligned(X, 2 * sizeof(T)) && ldx % 2 == 0 && N % 2 == 0;
+    const bool vec = N >= 2;
     constexpr int EPL = 16 / (int)sizeof(T);
-    const bool yvec = aligned(o.Y, 16) && o.ldy % EPL == 0 && (!o.R || (aligned(o.R, 16) && o.ldr % EPL == 0));
+    const bool yvec = aligned(o.Y, 16) && o.ldy % EPL == 0;
     const dim3 grid((unsigned)(row_blocks * tok_tiles)), block(kSpThreads);
     if (vec)
         hipLaunchKernelGGL((k_spmm_sp<T, RT, true>), grid, block, 0, stream, ws, (const T *)X, ldx,
@@ -894,9 +970,11 @@ nmg_status nmg_internal::p_spmm_sp(const nmg_p_layout *L, const void *values, co
     const int groups = (L->M / L->S + cpw - 1) / cpw, sblocks = (nsteps + kSpcSteps - 1) / kSpcSteps;
     const SpScratch ws = sp_scratch(ws_, L->M, L->K, f32 ? 2 : 1);
     const SpOut out{Y, ldy, nullptr, 0};
+    SpPatterns few = {};
+    for (int p = 0; L->P <= kSpFew && p < L->P; ++p) p_unrank(L->m, L->n, p, few.off + p * L->n);
     const int64_t blocks = (int64_t)groups * sblocks + (f32 ? (int64_t)(N + 63) / 64 * ws.xparts : 0);
     if (blocks > INT32_MAX) return NMG_ERR_PARAM;
-#define NMG_SPC(T)                                                                                      hipLaunchKernelGGL((k_sp_prepare_chunked<T>), dim3((unsigned)blocks), dim3(kSpcThreads), 0, stream,                        (const T *)values, index, (const T *)X, ldx, ws, L->M, (L->M + 15) / 16 * 16,                         L->K, N, L->n, L->m, L->g, L->P, L->S, L->B, cpw, nsteps, groups, sblocks)
+#define NMG_SPC(T)                                                                                      hipLaunchKernelGGL((k_sp_prepare_chunked<T>), dim3((unsigned)blocks), dim3(kSpcThreads), 0, stream,                        (const T *)values, index, (const T *)X, ldx, ws, few, L->M, (L->M + 15) / 16 * 16,                         L->K, N, L->n, L->m, L->g, L->P, L->S, L->B, cpw, nsteps, groups, sblocks)
     if (f32) NMG_SPC(float);
     else NMG_SPC(_Float16);
 #undef NMG_SPC
