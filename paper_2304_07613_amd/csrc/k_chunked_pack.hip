@@ -163,17 +163,28 @@ __device__ __forceinline__ void cp_write(const CpLane<SL> &ln, const CpRow<T, MM
     }
 }
 
-// maximum / minimum of a 32-bit key over the wave
-__device__ __forceinline__ uint32_t cp_wave_max(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o));
-    return v;
+// maximum / minimum of a 32-bit key over the wave (in every lane): lane
+// exchanges inside rows of 16 by DPP, then gfx950's row and half-wave swaps --
+// an LDS shuffle a step would put 12 LDS round trips into every phase
+template <bool MAX> __device__ __forceinline__ uint32_t cp_pick(uint32_t a, uint32_t b) {
+    return MAX ? max(a, b) : min(a, b);
 }
-__device__ __forceinline__ uint32_t cp_wave_min(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o));
+template <bool MAX> __device__ __forceinline__ uint32_t cp_wave_pick(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    v = cp_pick<MAX>(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xf, 0xf, false));   // ^ 1
+    v = cp_pick<MAX>(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xf, 0xf, false));   // ^ 2
+    v = cp_pick<MAX>(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xf, 0xf, false));  // 8 mirrored
+    v = cp_pick<MAX>(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xf, 0xf, false));  // 16 mirrored
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = cp_pick<MAX>(r[0], r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return cp_pick<MAX>(h[0], h[1]);
+#else
     return v;
+#endif
 }
+__device__ __forceinline__ uint32_t cp_wave_max(uint32_t v) { return cp_wave_pick<true>(v); }
+__device__ __forceinline__ uint32_t cp_wave_min(uint32_t v) { return cp_wave_pick<false>(v); }
 
 // SL rows a lane; PACKED: several chunks on the wave (SL = 1)
 template <typename T, int MM, int PM, int SL, bool PACKED, bool VEC>
@@ -528,12 +539,16 @@ __global__ __launch_bounds__(64 * kCpWaves) void k_p_swaps(const T *__restrict__
         auto rounds = [&](auto wc) __attribute__((always_inline)) {
             constexpr bool WIDE = decltype(wc)::value;
             constexpr double kUnit = WIDE ? 1.0 : 256.0;
+            bool moved[SL];   // a row of these 64 places changed: its patterns' best changes do too
+#pragma unroll
+            for (int i = 0; i < SL; ++i) moved[i] = true;
             for (int round = 0; round < 8 * S; ++round) {
 #pragma unroll
-                for (int p = 0; p < PM; ++p) {
-                    if (p >= P) break;
+                for (int i = 0; i < SL; ++i) {
+                    if (!moved[i]) continue;   // uniform across the wave
 #pragma unroll
-                    for (int i = 0; i < SL; ++i) {
+                    for (int p = 0; p < PM; ++p) {
+                        if (p >= P) break;
                         // (places past S hold no row: kept out by -inf)
                         const double x = WIDE ? D[i][p] : __builtin_fma(D[i][p], 256.0, (double)(255 - at[i]));
                         const double v = live[i] ? x : -__builtin_inf();
@@ -577,11 +592,14 @@ __global__ __launch_bounds__(64 * kCpWaves) void k_p_swaps(const T *__restrict__
                 if (!__any(found)) break;  // uniform across the wave
                 p_wave_sync();
 #pragma unroll
-                for (int i = 0; i < SL; ++i)
-                    if (bq[i] >= 0 && best[base + bq[i]] == at[i]) {   // mutual: disjoint pairs
+                for (int i = 0; i < SL; ++i) {
+                    const bool swap = bq[i] >= 0 && best[base + bq[i]] == at[i];   // mutual: disjoint pairs
+                    if (swap) {
                         at[i] = bq[i];
                         take_row(i);
                     }
+                    moved[i] = __any(swap);
+                }
                 p_wave_sync();   // tables and partners are read before they are rewritten
             }
         };
