@@ -180,13 +180,17 @@ __device__ __forceinline__ int sp_token_exp(const uint32_t *xmax, int parts, int
     return sp_scale_exp(mx);
 }
 
-// Scratch memory: the weight stream, then (binary32) the scale exponents of
-// the 16-row tiles and the partial maxima of the tokens
+// Scratch memory: the weight stream, the partial sums of a product whose
+// columns are split over workgroups, and (binary32) the scale exponents of the
+// 16-row tiles and tokens and the partial maxima of the tokens
 struct SpScratch {
     char *stream;
     int *wexp;
     uint32_t *xmax;
     int xparts;
+    int *xexp;
+    float *part;     // splits x M x N, or NULL
+    int splits;
 };
 inline int64_t sp_xparts(int64_t K) { return (K + kSpXRows - 1) / kSpXRows; }
 inline int64_t sp_tiles(int64_t M) { return (M + 15) / 16; }
@@ -197,10 +201,37 @@ inline int64_t sp_steps(int64_t K, int parts) {
 inline int64_t sp_scale_offset(int64_t M, int64_t K, int parts) {
     return sp_tiles(M) * sp_steps(K, parts) * sp_tile_bytes(parts);     // a multiple of 256
 }
-inline SpScratch sp_scratch(void *ws, int64_t M, int64_t K, int parts) {
+// Passes a workgroup makes, and workgroups the columns are split over.  A
+// layer whose 64-row tiles leave half of the compute units idle and whose
+// columns make many passes is split, 6 passes a workgroup or more; a second
+// kernel adds the parts in order.  768 x 3072: binary32 at 16 tokens 53 -> 19
+// us, binary16 30 -> 15; binary16 at 1000 tokens 36 -> 29.  At 768 columns
+// (12 passes, 6 in binary16) the second kernel costs what the split saves.
+inline int sp_passes(int64_t K, int parts) { return (int)(sp_steps(K, parts) / (3 - parts)); }
+inline int sp_splits(int64_t M, int64_t K, int64_t N, int parts) {
+    const int64_t wgs = (M + 63) / 64 * ((N + kSpTok - 1) / kSpTok), cus = device_cus();
+    const int np = sp_passes(K, parts);
+    if (2 * wgs > cus || np < 16) return 1;
+    const int64_t s = std::min<int64_t>(std::min<int64_t>(cus / wgs, np / 6), 8);
+    if (s < 2) return 1;
+    const int per = (int)((np + s - 1) / s);
+    return (np + per - 1) / per;     // none empty
+}
+inline SpScratch sp_scratch(void *ws, int64_t M, int64_t K, int64_t N, int parts) {
     char *p = static_cast<char *>(ws);
-    int *e = reinterpret_cast<int *>(p + sp_scale_offset(M, K, parts));
-    return SpScratch{p, e, reinterpret_cast<uint32_t *>(e + sp_tiles(M)), (int)sp_xparts(K)};
+    SpScratch r = {};
+    r.stream = p;
+    p += sp_scale_offset(M, K, parts);
+    r.xparts = (int)sp_xparts(K);
+    r.splits = sp_splits(M, K, N, parts);
+    if (r.splits > 1) {
+        r.part = reinterpret_cast<float *>(p);
+        p += r.splits * M * N * 4;
+    }
+    r.wexp = reinterpret_cast<int *>(p);
+    r.xexp = r.wexp + sp_tiles(M);
+    r.xmax = reinterpret_cast<uint32_t *>(r.xexp + N);
+    return r;
 }
 
 // Kept values of one 16-column range, gathered column by column
@@ -507,8 +538,9 @@ __device__ __attribute__((noinline)) float sp_chain(const char *stream, const T 
     return acc;
 }
 
-// RT 16-row tiles per wave; VEC: two tokens a load (N >= 2)
-template <typename T, int RT, bool VEC>
+// RT 16-row tiles per wave; VEC: two tokens a load (N >= 2); SPLIT: the
+// columns are split over gridDim.y workgroups, whose sums go to ws.part
+template <typename T, int RT, bool VEC, bool SPLIT>
 __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *__restrict__ X, int64_t ldx,
                                                         T *__restrict__ Y, int64_t ldy, int M, int K,
                                                         const T *__restrict__ R, int64_t ldr, int N,
@@ -533,7 +565,10 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
     const int wr = wave & 3, wt = wave >> 2;
     const int t0 = tt0 * kSpTok;
     const int rt0 = rb * (4 * RT) + wr * RT;       // this wave's first 16-row tile
-    const int npass = nsteps / SUB;                // host: whole passes
+    // this workgroup's passes (host: whole passes, none empty)
+    const int per = SPLIT ? (nsteps / SUB + (int)gridDim.y - 1) / (int)gridDim.y : 0;
+    const int p0 = SPLIT ? (int)blockIdx.y * per : 0;
+    const int npass = SPLIT ? min(nsteps / SUB, p0 + per) : nsteps / SUB;
 
     // ---- the weight stream, one pass ahead (two sets)
     struct AOps {
@@ -711,18 +746,22 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
             });
         }
     };
-    load_x(0);
-    load_a(0, aops[0]);
+    load_x(p0);
+    load_a(p0, aops[0]);
     if constexpr (PARTS == 2) {
-        if (tid < kSpTok) texp[tid] = sp_token_exp(ws.xmax, ws.xparts, N, min(t0 + tid, N - 1));
+        if (tid < kSpTok) {
+            const int e = sp_token_exp(ws.xmax, ws.xparts, N, min(t0 + tid, N - 1));
+            texp[tid] = e;
+            if (SPLIT && rb == 0 && blockIdx.y == 0 && t0 + tid < N) ws.xexp[t0 + tid] = e;
+        }
         sp_barrier();
 #pragma unroll
         for (int j = 0; j < 2; ++j) xscale[j] = __builtin_ldexpf(1.f, texp[xt[j]]);
     }
     write_x(0, 0);
     write_x(0, 1);
-    load_x(min(1, npass - 1));
-    for (int p = 0; p < npass; p += 2) {
+    load_x(min(p0 + 1, npass - 1));
+    for (int p = p0; p < npass; p += 2) {
         pass(p, std::integral_constant<int, 0>{});
         if (p + 1 < npass) pass(p + 1, std::integral_constant<int, 1>{});
     }
@@ -730,6 +769,21 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
     // ---- outputs: register r of (i, t) is row 16 (rt0 + i) + 4 (lane / 16) +
     // r, token t0 + 64 wt + 16 t + lane % 16; through this wave's share of LDS
     // so that every store writes whole runs of a row
+    if constexpr (SPLIT) {
+        // a part of the sum, still scaled: k_sp_reduce adds them up
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * (rt0 + i) + 4 * (lane >> 4) + r, tok = t0 + 64 * wt + 16 * t + (lane & 15);
+                    float y = acc[i][t][r];
+                    if constexpr (PARTS == 2) y += low[i][t][r];
+                    if (row < M && tok < N) ws.part[((int64_t)blockIdx.y * M + row) * N + tok] = y;
+                }
+        return;
+    }
     sp_barrier();
     char *const ob = xs + wave * OTILE;
     constexpr int EPL = 16 / ES;                    // elements per lane
@@ -793,6 +847,34 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
     }
 }
 
+// The parts of a split product added in order, scaled back (or recomputed
+// where not finite), the residual added: one thread per output
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_sp_reduce(SpScratch ws, const T *__restrict__ X, int64_t ldx,
+                                                      T *__restrict__ Y, int64_t ldy, int M, int K,
+                                                      const T *__restrict__ R, int64_t ldr, int N,
+                                                      int nsteps) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x, mn = (int64_t)M * N;
+    if (i >= mn) return;
+    const int row = (int)(i / N), tok = (int)(i - (int64_t)row * N);
+    float u[8];   // splits <= 8: every load in flight
+#pragma unroll
+    for (int z = 0; z < 8; ++z) u[z] = ws.part[min(z, ws.splits - 1) * mn + i];
+    float y = u[0];
+#pragma unroll
+    for (int z = 1; z < 8; ++z) y = z < ws.splits ? y + u[z] : y;
+    int we = 0;
+    if constexpr (sp_parts<T>() == 2) {
+        we = ws.wexp[row >> 4];
+        y = __builtin_ldexpf(y, -(we + ws.xexp[tok]));
+    }
+    if (__builtin_expect(!(fabsf(y) < __builtin_inff()), 0))
+        y = sp_chain<T>(ws.stream, X, ldx, row, tok, K, nsteps, we);
+    T v = (T)y;
+    if (R != nullptr) v = (T)((float)v + (float)R[(int64_t)row * ldr + tok]);
+    Y[(int64_t)row * ldy + tok] = v;
+}
+
 // --------------------------------------------------------------- launchers
 
 // Row tiles per wave (1 .. 3, binary16 .. 4): rounds of workgroups (one per
@@ -828,19 +910,31 @@ void sp_launch(const SpScratch &ws, const void *X, int64_t ldx, int M, int K, in
     const bool vec = N >= 2;
     constexpr int EPL = 16 / (int)sizeof(T);
     const bool yvec = aligned(o.Y, 16) && o.ldy % EPL == 0;
-    const dim3 grid((unsigned)(row_blocks * tok_tiles)), block(kSpThreads);
-    if (vec)
-        hipLaunchKernelGGL((k_spmm_sp<T, RT, true>), grid, block, 0, stream, ws, (const T *)X, ldx,
-                           (T *)o.Y, o.ldy, M, K, (const T *)o.R, o.ldr, N, nsteps, tiles16, row_blocks, yvec);
-    else
-        hipLaunchKernelGGL((k_spmm_sp<T, RT, false>), grid, block, 0, stream, ws, (const T *)X, ldx,
-                           (T *)o.Y, o.ldy, M, K, (const T *)o.R, o.ldr, N, nsteps, tiles16, row_blocks, yvec);
+    const dim3 grid((unsigned)(row_blocks * tok_tiles), (unsigned)ws.splits), block(kSpThreads);
+#define NMG_SP(VEC, SPLIT)                                                                         \
+    hipLaunchKernelGGL((k_spmm_sp<T, RT, VEC, SPLIT>), grid, block, 0, stream, ws, (const T *)X, ldx, \
+                       (T *)o.Y, o.ldy, M, K, (const T *)o.R, o.ldr, N, nsteps, tiles16, row_blocks, yvec)
+    if constexpr (RT == 1) {   // split products have one row tile a wave
+        if (ws.splits > 1) {
+            if (vec) NMG_SP(true, true);
+            else NMG_SP(false, true);
+        }
+    }
+    if (ws.splits <= 1) {
+        if (vec) NMG_SP(true, false);
+        else NMG_SP(false, false);
+    }
+#undef NMG_SP
+    if (ws.splits > 1)
+        hipLaunchKernelGGL((k_sp_reduce<T>), dim3((unsigned)(((int64_t)M * N + kBlock - 1) / kBlock)),
+                           dim3(kBlock), 0, stream, ws, (const T *)X, ldx, (T *)o.Y, o.ldy, M, K,
+                           (const T *)o.R, o.ldr, N, nsteps);
 }
 
 template <typename T>
 nmg_status sp_product(const SpScratch &ws, const void *X, int64_t ldx, int M, int K, int N, const SpOut &o,
                       hipStream_t stream) {
-    switch (sp_row_tiles(M, N, sp_parts<T>() == 2 ? 3 : 4)) {
+    switch (ws.splits > 1 ? 1 : sp_row_tiles(M, N, sp_parts<T>() == 2 ? 3 : 4)) {
         case 4:
             if constexpr (sp_parts<T>() == 1) sp_launch<T, 4>(ws, X, ldx, M, K, N, o, stream);
             break;
@@ -865,7 +959,9 @@ int spc_chunks(int S) {
 
 int64_t nmg_internal::sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int64_t N) {
     const bool f32 = dtype == NMG_F32;
-    return sp_scale_offset(M, K, f32 ? 2 : 1) + (f32 ? 4 * (sp_tiles(M) + sp_xparts(K) * N) : 0);
+    const int splits = sp_splits(M, K, N, f32 ? 2 : 1);
+    return sp_scale_offset(M, K, f32 ? 2 : 1) + (splits > 1 ? splits * M * N * 4 : 0) +
+           (f32 ? 4 * (sp_tiles(M) + N + sp_xparts(K) * N) : 0);
 }
 
 bool nmg_internal::sp_args_supported(nmg_dtype dtype, int64_t M, int64_t K, int64_t ldx, int64_t N) {
@@ -895,12 +991,15 @@ bool nmg_internal::sp_layout_supported(const nmg_layout *L) {
 //    512 tokens, 36 / 34 at 2048, 60 / 56 at 4096).  Binary16 goes there only
 //    for token counts off 8: 2:8:8 31 / 15 at one token, 55 / 26 at 1021.
 //  - mfma_direct keeps its layouts (few kept columns, few rows or tokens),
-//    where its partial sums also round less.
+//    where its partial sums also round less, but for half density from 2048
+//    columns: 768 x 3072 2:4:4 40 / 19 at 16 tokens, 113 / 40 at 1021, 2:4:16
+//    28 / 19 and 74 / 41, errors 1.9e-7 to 2.6e-7 / 1.3e-7 to 2.0e-7.
 //  - The binary16 kernels with the epilogue folded in: smfmac from 3 10^9
 //    expanded products (2:4:1 11 / 16 at 512 tokens, 30 / 21 at 2048) or 2048
-//    columns (768 x 3072 50 / 30 at 16 tokens), mfma_f16 at half density from
+//    columns (768 x 3072 50 / 15 at 16 tokens), mfma_f16 at half density from
 //    4 10^9 (2:4:8 13 / 16 at 512 tokens, 35 / 21 at 2048; 1:4:8 27 / 35 at
-//    4096); GELU stays with them.
+//    4096) or 2048 columns (768 x 3072 2:4:8 29 / 16 at 16 tokens, 31 / 26 at
+//    1024; 2:4:16 24 / 21 at 512, 25 / 26 at 1024); GELU stays with them.
 bool nmg_internal::sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epilogue epi, int64_t N) {
     const double kept = (double)L->M * L->C * L->n * (double)N, dense = (double)L->M * L->K * (double)N;
     const bool f32 = L->dtype == NMG_F32, half = 2 * L->n >= L->m;
@@ -909,9 +1008,10 @@ bool nmg_internal::sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epil
         case NMG_KERNEL_MFMA_EXPAND:
         case NMG_KERNEL_VALU_STAGED:
         case NMG_KERNEL_VALU: return true;
+        case NMG_KERNEL_MFMA_DIRECT: return f32 && half && L->K >= 2048;
         case NMG_KERNEL_MFMA_SCALAR: return !f32 || half || N % 64 != 0 || kept >= 1e9;
         case NMG_KERNEL_SMFMAC_F16: return epi != NMG_EPILOGUE_GELU && (dense >= 3e9 || L->K >= 2048);
-        case NMG_KERNEL_MFMA_F16: return epi != NMG_EPILOGUE_GELU && half && dense >= 4e9;
+        case NMG_KERNEL_MFMA_F16: return epi != NMG_EPILOGUE_GELU && half && (dense >= 4e9 || (L->K >= 2048 && (L->g <= 8 || N <= 512)));
         default: return false;
     }
 }
@@ -926,7 +1026,7 @@ nmg_status nmg_internal::spmm_sp(const SpmmArgs &a, void *ws_) {
     const SpOut out{a.Y, a.ldy, a.epi == NMG_EPILOGUE_ADD ? a.R : nullptr, a.ldr};
     const int parts = L->dtype == NMG_F32 ? 2 : 1;
     const int nsteps = (int)sp_steps(L->K, parts), tiles = (int)sp_tiles(L->M);
-    const SpScratch ws = sp_scratch(ws_, L->M, L->K, parts);
+    const SpScratch ws = sp_scratch(ws_, L->M, L->K, a.N, parts);
     if (L->dtype == NMG_F32) {
         const int sgroups = (nsteps + kSpPrep / 64 - 1) / (kSpPrep / 64), wblocks = tiles * sgroups;
         const dim3 grid((unsigned)(wblocks + (a.N + 63) / 64 * ws.xparts));
@@ -968,7 +1068,7 @@ nmg_status nmg_internal::p_spmm_sp(const nmg_p_layout *L, const void *values, co
     const bool f32 = L->dtype == NMG_F32;
     const int nsteps = (int)sp_steps(L->K, f32 ? 2 : 1), cpw = spc_chunks(L->S);
     const int groups = (L->M / L->S + cpw - 1) / cpw, sblocks = (nsteps + kSpcSteps - 1) / kSpcSteps;
-    const SpScratch ws = sp_scratch(ws_, L->M, L->K, f32 ? 2 : 1);
+    const SpScratch ws = sp_scratch(ws_, L->M, L->K, N, f32 ? 2 : 1);
     const SpOut out{Y, ldy, nullptr, 0};
     SpPatterns few = {};
     for (int p = 0; L->P <= kSpFew && p < L->P; ++p) p_unrank(L->m, L->n, p, few.off + p * L->n);

@@ -948,6 +948,8 @@ SPARSE = [
     (130, 1000, 77, 1, 10, 2), (66, 660, 130, 1, 33, 1), (68, 130, 33, 1, 2, 4), (96, 300, 257, 1, 3, 3),
     (64, 144, 256, 2, 16, 2), (40, 120, 66, 2, 12, 1), (384, 192, 1030, 1, 5, 8), (3072, 64, 1025, 2, 4, 4),
     (1056, 100, 2050, 1, 20, 16), (260, 510, 126, 1, 255, 1),
+    # columns split over workgroups: 2 to 8 parts, ragged last ones
+    (80, 2100, 33, 2, 4, 1), (72, 2113, 1, 1, 5, 3), (130, 3072, 200, 1, 10, 1), (64, 2304, 4000, 2, 8, 8),
 ]
 
 
@@ -996,11 +998,12 @@ def test_sparse_product_precision(nmg, wexp, xexp):
     assert err["sparse"].max() <= 1.5 * err["valu"].max()
 
 
+@pytest.mark.parametrize("K", [96, 2176])      # one workgroup a tile; split columns
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
-def test_sparse_product_non_finite(nmg, dtype):
+def test_sparse_product_non_finite(nmg, dtype, K):
     """Infinities, NaN and overflow come out as from the multiply-adds over
     the kept columns: only where a kept column selects them."""
-    M, K, N = 80, 96, 40
+    M, N = 80, 40
     W = synth.normal((M, K), 921, 0.5, dtype)
     X = synth.normal((K, N), 922, 1.0, dtype)
     X[5, 2], X[17, 3], X[40, 4] = float("inf"), float("-inf"), float("nan")
@@ -1020,7 +1023,7 @@ def test_sparse_product_non_finite(nmg, dtype):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("M,K,N,n,m,g", [(6, 4, 1, 2, 4, 1), (30, 68, 3, 2, 4, 5), (96, 132, 129, 2, 4, 16),
                                          (192, 1000, 260, 2, 4, 32), (28, 72, 70, 2, 8, 1), (240, 64, 33, 1, 16, 15),
-                                         (512, 776, 131, 1, 8, 32)])
+                                         (512, 776, 131, 1, 8, 32), (96, 2176, 130, 2, 4, 4)])
 def test_chunked_sparse_product(nmg, M, K, N, n, m, g, dtype):
     """The chunked layout on the sparse matrix instructions (AUTO through the
     binding, which brings a workspace): chunks that share 16-row tiles, rows
