@@ -37,10 +37,11 @@
  *   - All data pointers are device pointers (HIP global memory) of the current
  *     device.  The caller allocates and owns every buffer; the library keeps
  *     no pointer after a call returns.  The only device memory it allocates
- *     is the scratch memory of three product families (NMG_KERNEL_MFMA_WIDE /
- *     _SPLIT and NMG_KERNEL_MFMA_EXPAND, the last also an NMG_KERNEL_AUTO
- *     choice), allocated and freed in stream order on the call's stream;
- *     nmg_spmm_epilogue_noalloc uses a fixed per-GPU array instead.
+ *     is the scratch memory of four product families (NMG_KERNEL_MFMA_WIDE /
+ *     _SPLIT, NMG_KERNEL_MFMA_EXPAND and NMG_KERNEL_SPARSE, the last two also
+ *     NMG_KERNEL_AUTO choices), allocated and freed in stream order on the
+ *     call's stream; nmg_spmm_epilogue_noalloc uses a fixed per-GPU array
+ *     instead, and nmg_spmm_epilogue_ws and nmg_p_spmm_ws the caller's.
  *   - Work is enqueued on `stream` (0 = the null stream) and runs
  *     asynchronously; a call returns after validation and launch.  Calls are
  *     thread-safe (nmg_spmm_epilogue_noalloc: see there).  The only mutable
@@ -158,17 +159,22 @@ typedef enum nmg_kernel {
                                     M K < 2^31                               */
     NMG_KERNEL_SPARSE = 12       /* gfx950's sparse matrix instructions on a
                                     weight stream made in scratch memory on
-                                    every call (stream-ordered; 3.25 bytes per
-                                    entry of W for binary32, 1.25 for
-                                    binary16): any g, any alignment, any N;
-                                    needs n = 1 (m >= 2) or n = 2 with m % 4
-                                    == 0.  Binary32 operands are carried
-                                    exactly as three bfloat16 numbers and
-                                    summed in binary32 from the six leading
-                                    part products; results that are not finite
-                                    or below 2^-80 in magnitude are recomputed
-                                    as binary32 multiply-adds over the kept
-                                    columns                                   */
+                                    every call (stream-ordered; 2.25 bytes per
+                                    entry of W and the scales of rows and
+                                    tokens for binary32, 1.25 for binary16,
+                                    and up to 8 M N partial sums where the
+                                    columns are split over workgroups): any
+                                    g, any alignment, any N; needs n = 1
+                                    (m >= 2) or n = 2 with m % 4 == 0.
+                                    Binary32 operands, scaled by a power of
+                                    two per 16 rows and per token, are carried
+                                    as two binary16 parts (24 bits down to
+                                    2^-28 of the largest entry of the rows or
+                                    token, an error within 2^-51 of that entry
+                                    below) and summed in binary32 from the
+                                    three leading part products.  Results that
+                                    are not finite are recomputed as binary32
+                                    multiply-adds over the kept columns      */
 } nmg_kernel;
 /* With n == m every column is kept and every index row is 0 .. m-1, so the
  * matrix-core kernels treat the weight as one group whatever g is. */
@@ -208,17 +214,19 @@ nmg_status nmg_repack(const nmg_layout *layout, const void *W, int64_t ldw,
  * strictly ascending in-chunk offsets per (group, chunk), as nmg_compress
  * writes them; other contents are not detected and give unspecified Y (the
  * kernels still never read outside X's K rows).  Uses NMG_KERNEL_AUTO, which
- * takes NMG_KERNEL_MFMA_EXPAND (scratch memory in stream order, dense-product
- * treatment of non-finite X) for binary32 layouts the grouped matrix-core
- * kernels cannot take when m <= 8 n. */
+ * takes NMG_KERNEL_SPARSE or, for layouts that kernel refuses or that keep
+ * fewer than 64 columns a row, NMG_KERNEL_MFMA_EXPAND (both scratch memory in
+ * stream order; the latter with a dense product's treatment of non-finite X)
+ * for binary32 layouts the grouped matrix-core kernels cannot take when
+ * m <= 8 n. */
 nmg_status nmg_spmm(const nmg_layout *layout, const void *values,
                     const uint8_t *indices, const void *X, int64_t ldx,
                     int64_t N, void *Y, int64_t ldy, hipStream_t stream);
 
 /* nmg_spmm with an explicit kernel family; NMG_ERR_UNSUPPORTED when that
  * family cannot run this layout.  NMG_KERNEL_MFMA_WIDE / _SPLIT (prepared
- * operands) and NMG_KERNEL_MFMA_EXPAND (the dense weight) keep their scratch
- * memory in device memory allocated and freed in stream order on `stream`
+ * operands), NMG_KERNEL_MFMA_EXPAND (the dense weight) and NMG_KERNEL_SPARSE
+ * (the weight stream) keep their scratch memory in device memory allocated and freed in stream order on `stream`
  * (hipMallocAsync / hipFreeAsync; NMG_ERR_LAUNCH when the allocation fails). */
 nmg_status nmg_spmm_with(const nmg_layout *layout, nmg_kernel kernel,
                          const void *values, const uint8_t *indices,
@@ -251,11 +259,13 @@ nmg_status nmg_spmm_epilogue(const nmg_layout *layout, nmg_kernel kernel, nmg_ep
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation): same arguments, same results bit for bit, and no allocation.
  * The families with scratch memory (NMG_KERNEL_MFMA_WIDE / _SPLIT, their
- * prepared operands; NMG_KERNEL_MFMA_EXPAND, chosen explicitly or by
- * NMG_KERNEL_AUTO, the dense weight) keep it in a fixed 16 MiB array in
+ * prepared operands; NMG_KERNEL_MFMA_EXPAND, the dense weight, and
+ * NMG_KERNEL_SPARSE, the weight stream, both chosen explicitly or by
+ * NMG_KERNEL_AUTO) keep it in a fixed 16 MiB array in
  * device memory instead of a stream-ordered allocation (one array per GPU,
  * held until the process ends; NMG_ERR_CAPACITY for a layout whose scratch
- * memory -- nmg_x16_prepared_bytes, or M K elements + K bytes -- exceeds it).  Every call on
+ * memory -- nmg_x16_prepared_bytes, M K elements + K bytes, or
+ * nmg_spmm_workspace_bytes -- exceeds it).  Every call on
  * a GPU shares that GPU's array: calls that overlap on one GPU (from several
  * threads or on several streams) race, so serialise them.  `stream` must
  * belong to the current device (NMG_ERR_PARAM).  The other families use no
@@ -272,7 +282,8 @@ nmg_status nmg_spmm_epilogue_noalloc(const nmg_layout *layout, nmg_kernel kernel
  * with scratch memory when it is large enough, in place of a stream-ordered
  * allocation.  With NMG_KERNEL_AUTO it also lets the library take
  * NMG_KERNEL_SPARSE for layouts whose choice without a workspace has no
- * scratch memory (other summation order, same error bounds). */
+ * scratch memory (other summation order, and the two parts of an operand as
+ * described there). */
 nmg_status nmg_spmm_epilogue_ws(const nmg_layout *layout, nmg_kernel kernel, nmg_epilogue epilogue,
                                 const void *values, const uint8_t *indices, const void *X,
                                 int64_t ldx, int64_t N, const void *R, int64_t ldr, void *Y,

@@ -34,7 +34,7 @@
 // Bound by the latency of each wave's chain of instructions (3 waves a SIMD;
 // the weights are 9 MB): 3072 x 768, binary32, 2:4, g = 32 has 3072 chunks of
 // 192 rows; greedy 341 -> 42 us (2000 vector and 3100 scalar instructions a
-// chunk), swap search 922 -> 73 us (5700 vector instructions a chunk).
+// chunk), swap search 922 -> 69 us (75 with every table recomputed each round).
 #include "chunked.hpp"
 
 namespace {

@@ -10,18 +10,21 @@
 //
 // Binary32.  Every entry, scaled by a power of two (per 16 rows of W, per
 // token of X: the largest magnitude goes to [2^14, 2^15)), is carried as two
-// binary16 numbers, h = f16(v) and l = f16(v - h), and the product is summed
-// in binary32 from h h (one accumulator) and h l + l h (another).  h + l is
-// within 2^-24 |v| of v (each rounding to nearest leaves 12 bits), or within
-// 2^-40 of the largest entry for entries below 2^-16 of it; l l, left out, is
-// below 2^-24 |w x| and of either sign.  The
+// binary16 numbers, h = f16(v) and l = f16(2^11 (v - h)), and the product is
+// summed in binary32 from h h (one accumulator) and h l + l h (another, scaled
+// back by 2^-11 at the end).  h + 2^-11 l is within 2^-24 |v| of v (each
+// rounding to nearest leaves 12 bits) down to 2^-28 of the largest entry, and
+// within 2^-51 of that entry below (without the factor l would lose bits from
+// 2^-16 on: outputs whose kept columns miss an entry 2^26 times the others had
+// errors of 4.5e-5, now 1.3e-7, for 2 us of 53 at 3072 x 768 x 4096); l l, left out, is below 2^-24 |w x| and of either sign.  The
 // binary32 families round once per kept column on the running sum; here the
 // running sum of h h is rounded once per 8 stored columns, so the error
-// against 64 bits is smaller: 1.2e-7 to 2.7e-7 (2-norm, K = 768 to 3072)
+// against 64 bits is smaller: 1.3e-7 to 2.6e-7 (2-norm, K = 768 to 3072)
 // where the binary32 matrix instructions give 2.5e-7 to 7e-7 on the same
 // inputs.  Three sparse binary16 products count half of K's columns each at
 // 16 times the rate of v_mfma_f32_16x16x4f32.  (Three exact bfloat16 parts
-// need no scales, but six products: 65 against 30 us at 3072 x 768 x 4096.)
+// need no scales, but six products: 65 us and 2.9e-7 against 50 us and 1.5e-7
+// at 3072 x 768 x 4096.)
 // Outputs that are not finite are recomputed by plain binary32 multiply-adds
 // of the kept columns in ascending order, so that infinities and NaN in X
 // reach only the outputs whose kept columns select them.
@@ -64,18 +67,22 @@ template <typename T> constexpr int sp_parts() { return std::is_same<T, float>::
 __host__ __device__ constexpr int sp_tile_bytes(int parts) { return parts * 1024 + 256; }
 
 // the two parts of two binary32 numbers times `scale` (a power of two), packed
-// (first in the low half): the scaled number and its remainder are exact, each
-// rounded once to binary16.  (Vector conversions, so that the remainders stay
-// v_fma_mix_f32 + v_cvt_pk_f16_f32: v_fma_mixlo_f16 issues at half the rate.)
+// (first in the low half): the scaled number and 2^11 times its remainder are
+// exact, each rounded once to binary16.  (Vector conversions, so that the
+// remainders stay v_fma_mix_f32 + v_cvt_pk_f16_f32: v_fma_mixlo_f16 issues at
+// half the rate.)
+constexpr float kSpLow = 2048.f, kSpLowInv = 1.f / 2048.f;
 struct SpPair {
     uint32_t h, l;
 };
 __device__ __forceinline__ SpPair sp_split(float a, float b, float scale) {
     typedef _Float16 h2 __attribute__((ext_vector_type(2)));
     typedef float f2 __attribute__((ext_vector_type(2)));
-    const h2 h = __builtin_convertvector(f2{a * scale, b * scale}, h2);
-    const h2 l = __builtin_convertvector(f2{__builtin_fmaf(a, scale, -(float)h[0]),
-                                            __builtin_fmaf(b, scale, -(float)h[1])}, h2);
+    a *= scale;
+    b *= scale;
+    const h2 h = __builtin_convertvector(f2{a, b}, h2);
+    const h2 l = __builtin_convertvector(f2{__builtin_fmaf((float)h[0], -kSpLow, a * kSpLow),
+                                            __builtin_fmaf((float)h[1], -kSpLow, b * kSpLow)}, h2);
     return SpPair{__builtin_bit_cast(uint32_t, h), __builtin_bit_cast(uint32_t, l)};
 }
 // Exponent that brings the largest magnitude (as bits) to [2^14, 2^15); none
@@ -526,7 +533,7 @@ __device__ __attribute__((noinline)) float sp_chain(const char *stream, const T 
                 if constexpr (PARTS == 2) {
                     // (an infinite weight's low part is NaN: not added)
                     const float l = (float)reinterpret_cast<const _Float16 *>(tile + 1024)[8 * lane + e];
-                    w = fabsf(w) < __builtin_inff() ? w + l : w;
+                    w = fabsf(w) < __builtin_inff() ? fmaf(l, kSpLowInv, w) : w;
                     w = __builtin_ldexpf(w, -wexp);
                 }
                 if (w == 0.f) continue;      // no kept column
@@ -666,7 +673,7 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
         b[t & 1][p] = __builtin_bit_cast(h16, u8v{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
     };
 
-    // acc: h h (binary16: the product); low: h l + l h
+    // acc: h h (binary16: the product); low: h l + l h, times 2^11
     v4f acc[RT][4], low[PARTS == 2 ? RT : 1][4];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
@@ -779,7 +786,7 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
                 for (int r = 0; r < 4; ++r) {
                     const int row = 16 * (rt0 + i) + 4 * (lane >> 4) + r, tok = t0 + 64 * wt + 16 * t + (lane & 15);
                     float y = acc[i][t][r];
-                    if constexpr (PARTS == 2) y += low[i][t][r];
+                    if constexpr (PARTS == 2) y = fmaf(low[i][t][r], kSpLowInv, y);
                     if (row < M && tok < N) ws.part[((int64_t)blockIdx.y * M + row) * N + tok] = y;
                 }
         return;
@@ -805,7 +812,7 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
             for (int r = 0; r < 4; ++r) {
                 float y = acc[i][t][r];
                 if constexpr (PARTS == 2)
-                    y = __builtin_ldexpf(y + low[i][t][r], -(we + xe[t]));
+                    y = __builtin_ldexpf(fmaf(low[i][t][r], kSpLowInv, y), -(we + xe[t]));
                 const int row = 16 * (rt0 + i) + 4 * (lane >> 4) + r, tok = t0 + 64 * wt + 16 * t + (lane & 15);
                 if (__builtin_expect(!(fabsf(y) < __builtin_inff()) && row < M && tok < N, 0))
                     y = sp_chain<T>(stream, X, ldx, row, tok, K, nsteps, we);

@@ -998,6 +998,25 @@ def test_sparse_product_precision(nmg, wexp, xexp):
     assert err["sparse"].max() <= 1.5 * err["valu"].max()
 
 
+@pytest.mark.parametrize("K", [768, 3072])     # one workgroup a tile; split columns
+@pytest.mark.parametrize("exp", [20, 26])
+def test_sparse_product_wide_range(nmg, K, exp):
+    """Outputs whose kept columns miss a token's largest entry, 2^exp above the
+    others (and likewise rows beside a weight that large): as precise as a
+    chain of binary32 multiply-adds over the same columns."""
+    M, N = 128, 130
+    W, X = synth.normal((M, K), 931, 0.02), synth.normal((K, N), 932, 1.0)
+    W[0, 8] = 0.02 * 2.0 ** exp     # beside rows 1 .. 15
+    W[::2, 0], W[1::2, 0] = 1.0, 0.0
+    X[0] = 3.0 * 2.0 ** exp         # kept by every other row
+    v, idx, L = nmg.compress(W.to(DEV), 1, 8, 1)
+    ref = (nmg.densify(v, idx, L).double() @ X.to(DEV).double())[1::2]
+    err = {k: (nmg.spmm(v, idx, X.to(DEV), L, k).double()[1::2] - ref).norm(dim=1) / ref.norm(dim=1)
+           for k in ("valu", "sparse")}
+    torch.cuda.synchronize()
+    assert (err["sparse"] <= 1.5 * err["valu"]).all()
+
+
 @pytest.mark.parametrize("K", [96, 2176])      # one workgroup a tile; split columns
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 def test_sparse_product_non_finite(nmg, dtype, K):
