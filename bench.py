@@ -419,6 +419,12 @@ def sweep(ctx, args):
         del res
 
 
+def binding_kernel(nmg, L, N):
+    """AUTO's family through the binding, which brings a workspace."""
+    need = [nmg.lib().nmg_spmm_workspace_bytes(L.c, nmg.KERNELS[k], N) for k in ("auto", "sparse")]
+    return "sparse" if need[0] == need[1] > 0 else nmg.auto_kernel(L, N)
+
+
 def chunked(ctx, args):
     """The paper's chunked layout beside the group layout on the sweep shapes
     it fits (K % m == 0, M % (C(m,n) * g) == 0): kept magnitude of the group
@@ -460,7 +466,7 @@ def chunked(ctx, args):
                "us_spmm_chunked": round(timed(lambda: nmg.p_spmm(pv, pidx, X, PL)), 2),
                "us_spmm_chunked_valu": round(timed(lambda: nmg.p_spmm(pv, pidx, X, PL, "valu")), 2),
                "us_spmm_chunked_mfma": round(timed(lambda: nmg.p_spmm(pv, pidx, X, PL, "mfma")), 2),
-               "group_kernel": nmg.auto_kernel(L, lin.N)}
+               "group_kernel": binding_kernel(nmg, L, lin.N)}
         rec["tflops_spmm_chunked"] = round(lin.useful_flop / rec["us_spmm_chunked"] / 1e6, 2)
         rec["tflops_spmm_group"] = round(lin.useful_flop / rec["us_spmm_group"] / 1e6, 2)
         print(json.dumps(rec), flush=True)
