@@ -200,10 +200,14 @@ def _packed_ok(layout, values, indices):
 def _workspace(nbytes: int, like: torch.Tensor):
     """Scratch memory of one call from torch's allocator: (tensor, pointer,
     bytes).  Freed after the call returns; the allocator hands it out again in
-    stream order on the current stream only."""
+    stream order on the current stream only.  None when the memory is not there:
+    the library then takes what it takes without a workspace."""
     if nbytes <= 0:
         return None, None, 0
-    ws = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+    try:
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+    except torch.OutOfMemoryError:
+        return None, None, 0
     return ws, ws.data_ptr(), nbytes
 
 

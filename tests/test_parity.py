@@ -1079,3 +1079,28 @@ def test_sparse_product_capture(nmg):
         eager = nmg.spmm(v, idx, X, L)
         torch.cuda.synchronize()
         assert torch.equal(Y.view(torch.int32), eager.view(torch.int32)), f"replay {rep}"
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+def test_sparse_product_without_workspace_memory(nmg, dtype, monkeypatch):
+    """No memory for the workspace: AUTO takes the families without one, the
+    group layout's and the chunked layout's, as nmg_spmm / nmg_p_spmm do."""
+    M, K, N = 96, 132, 129
+    W = synth.normal((M, K), 961, 0.02).to(dtype).to(DEV)
+    X = synth.normal((K, N), 962).to(dtype)
+    v, idx, L = nmg.compress(W, 2, 4, 8)
+    pv, pidx, PL = nmg.p_compress(W, 2, 4, 8)
+    Xd = X.to(DEV)
+
+    def none_left(*args, **kw):
+        raise torch.OutOfMemoryError("no memory")
+
+    with monkeypatch.context() as mp:
+        mp.setattr(torch, "empty", none_left)
+        Y, Yp = nmg.spmm(v, idx, Xd, L), nmg.p_spmm(pv, pidx, Xd, PL)
+    torch.cuda.synchronize()
+    Yref, B = oracle.spmm(v.cpu().numpy(), idx.cpu().numpy(), X.numpy(), K, 2, 4, 8)
+    check_product(Y, Yref, B, dtype, "group", L.C * 2)
+    dense = nmg.p_densify(pv, pidx, PL).double().cpu().numpy()
+    x = X.double().numpy()
+    check_product(Yp, dense @ x, np.abs(dense) @ np.abs(x), dtype, "chunked", (K // 4) * 2)
