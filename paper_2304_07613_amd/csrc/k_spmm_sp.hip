@@ -16,11 +16,11 @@
 // rounding to nearest leaves 12 bits) down to 2^-28 of the largest entry, and
 // within 2^-51 of that entry below (without the factor l would lose bits from
 // 2^-16 on: outputs whose kept columns miss an entry 2^26 times the others had
-// errors of 4.5e-5, now 1.3e-7, for 2 us of 53 at 3072 x 768 x 4096); l l, left out, is below 2^-24 |w x| and of either sign.  The
-// binary32 families round once per kept column on the running sum; here the
-// running sum of h h is rounded once per 8 stored columns, so the error
-// against 64 bits is smaller: 1.3e-7 to 2.6e-7 (2-norm, K = 768 to 3072)
-// where the binary32 matrix instructions give 2.5e-7 to 7e-7 on the same
+// errors of 4.5e-5, now 1.3e-7, for 2 us of 53 at 3072 x 768 x 4096); l l, left
+// out, is below 2^-24 |w x| and of either sign.  The binary32 families round
+// once per kept column on the running sum; here the sum of h h is rounded once
+// per 8 stored columns, so the error against 64 bits is smaller: 1.3e-7 to
+// 2.6e-7 (2-norm, K = 768 to 3072) where the binary32 matrix instructions give 2.5e-7 to 7e-7 on the same
 // inputs.  Three sparse binary16 products count half of K's columns each at
 // 16 times the rate of v_mfma_f32_16x16x4f32.  (Three exact bfloat16 parts
 // need no scales, but six products: 65 us and 2.9e-7 against 50 us and 1.5e-7
@@ -973,7 +973,8 @@ int64_t nmg_internal::sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int
 
 bool nmg_internal::sp_args_supported(nmg_dtype dtype, int64_t M, int64_t K, int64_t ldx, int64_t N) {
     const int64_t es = (int64_t)elem_size(dtype), lim = (int64_t)1 << 31;
-    return ldx * es < lim && sp_tiles(M) * sp_steps(K, 1) < lim && sp_tiles(M) * ((K + 511) / 512) + (N + 63) / 64 * sp_xparts(K) < lim &&
+    return ldx * es < lim && sp_tiles(M) * sp_steps(K, 1) < lim &&
+           sp_tiles(M) * ((K + 511) / 512) + (N + 63) / 64 * sp_xparts(K) < lim &&
            ((M + 31) / 32) * ((N + kSpTok - 1) / kSpTok) < lim;
 }
 
@@ -989,7 +990,7 @@ bool nmg_internal::sp_layout_supported(const nmg_layout *L) {
 //    rounds as rarely as this product does (1:20 of 768 columns: error 1.14e-7
 //    against 1.22e-7; 1:10: 1.58e-7 against 1.45e-7).
 //  - The expanded product and the vector kernels lose everywhere: 2:4:1
-//    79 / 23 at one token, 188 / 56 at 4096 (177 with the start's allocation
+//    79 / 23 at one token, 188 / 56 at 4096 (177 with its scratch allocation
 //    amortised), 768 x 3072 262 / 55 and 286 / 72; 1:10:1 135 / 23 and 162 / 53.
 //  - mfma_scalar, binary32: its X goes through registers when the tokens do
 //    not fill its tiles (1:4:8 at 1021 tokens 44 / 34); at half density it
@@ -1018,7 +1019,9 @@ bool nmg_internal::sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epil
         case NMG_KERNEL_MFMA_DIRECT: return f32 && half && L->K >= 2048;
         case NMG_KERNEL_MFMA_SCALAR: return !f32 || half || N % 64 != 0 || kept >= 1e9;
         case NMG_KERNEL_SMFMAC_F16: return epi != NMG_EPILOGUE_GELU && (dense >= 3e9 || L->K >= 2048);
-        case NMG_KERNEL_MFMA_F16: return epi != NMG_EPILOGUE_GELU && half && (dense >= 4e9 || (L->K >= 2048 && (L->g <= 8 || N <= 512)));
+        case NMG_KERNEL_MFMA_F16:
+            return epi != NMG_EPILOGUE_GELU && half &&
+                   (dense >= 4e9 || (L->K >= 2048 && (L->g <= 8 || N <= 512)));
         default: return false;
     }
 }
@@ -1037,7 +1040,10 @@ nmg_status nmg_internal::spmm_sp(const SpmmArgs &a, void *ws_) {
     if (L->dtype == NMG_F32) {
         const int sgroups = (nsteps + kSpPrep / 64 - 1) / (kSpPrep / 64), wblocks = tiles * sgroups;
         const dim3 grid((unsigned)(wblocks + (a.N + 63) / 64 * ws.xparts));
-#define NMG_SP_PREP(MC)                                                                                hipLaunchKernelGGL((k_sp_prepare<MC>), grid, dim3(kSpPrep), 0, a.stream, (const float *)a.values,                        a.indices, (const float *)a.X, a.ldx, ws, L->M, L->K, a.N, L->n, L->m, L->g,                         L->C, nsteps, sgroups, wblocks)
+#define NMG_SP_PREP(MC)                                                                             \
+    hipLaunchKernelGGL((k_sp_prepare<MC>), grid, dim3(kSpPrep), 0, a.stream,                        \
+        (const float *)a.values, a.indices, (const float *)a.X, a.ldx, ws, L->M, L->K, a.N, L->n, L->m,          \
+        L->g, L->C, nsteps, sgroups, wblocks)
         switch (L->m) {
             case 4: NMG_SP_PREP(4); break;
             case 8: NMG_SP_PREP(8); break;
@@ -1051,7 +1057,10 @@ nmg_status nmg_internal::spmm_sp(const SpmmArgs &a, void *ws_) {
     }
     const int total = tiles * nsteps;
     const dim3 grid((unsigned)((total + kBlock / 64 - 1) / (kBlock / 64)));
-#define NMG_SP_PREP(MC)                                                                                hipLaunchKernelGGL((k_sp_prepare_f16<MC>), grid, dim3(kBlock), 0, a.stream,                                            (const _Float16 *)a.values, a.indices, ws.stream, L->M, L->K, L->n, L->m, L->g,                        L->C, nsteps, total)
+#define NMG_SP_PREP(MC)                                                                             \
+    hipLaunchKernelGGL((k_sp_prepare_f16<MC>), grid, dim3(kBlock), 0, a.stream,                     \
+        (const _Float16 *)a.values, a.indices, ws.stream, L->M, L->K, L->n, L->m, L->g, L->C,              \
+        nsteps, total)
     switch (L->m) {
         case 4: NMG_SP_PREP(4); break;
         case 8: NMG_SP_PREP(8); break;
@@ -1081,7 +1090,10 @@ nmg_status nmg_internal::p_spmm_sp(const nmg_p_layout *L, const void *values, co
     for (int p = 0; L->P <= kSpFew && p < L->P; ++p) p_unrank(L->m, L->n, p, few.off + p * L->n);
     const int64_t blocks = (int64_t)groups * sblocks + (f32 ? (int64_t)(N + 63) / 64 * ws.xparts : 0);
     if (blocks > INT32_MAX) return NMG_ERR_PARAM;
-#define NMG_SPC(T)                                                                                      hipLaunchKernelGGL((k_sp_prepare_chunked<T>), dim3((unsigned)blocks), dim3(kSpcThreads), 0, stream,                        (const T *)values, index, (const T *)X, ldx, ws, few, L->M, (L->M + 15) / 16 * 16,                         L->K, N, L->n, L->m, L->g, L->P, L->S, L->B, cpw, nsteps, groups, sblocks)
+#define NMG_SPC(T)                                                                                  \
+    hipLaunchKernelGGL((k_sp_prepare_chunked<T>), dim3((unsigned)blocks), dim3(kSpcThreads),        \
+        0, stream, (const T *)values, index, (const T *)X, ldx, ws, few, L->M, (L->M + 15) /        \
+        16 * 16, L->K, N, L->n, L->m, L->g, L->P, L->S, L->B, cpw, nsteps, groups, sblocks)
     if (f32) NMG_SPC(float);
     else NMG_SPC(_Float16);
 #undef NMG_SPC
