@@ -85,11 +85,16 @@ __device__ __forceinline__ SpPair sp_split(float a, float b, float scale) {
                                             __builtin_fmaf((float)h[1], -kSpLow, b * kSpLow)}, h2);
     return SpPair{__builtin_bit_cast(uint32_t, h), __builtin_bit_cast(uint32_t, l)};
 }
-// Exponent that brings the largest magnitude (as bits) to [2^14, 2^15); none
-// for zeros, infinities and NaN.  At most 2^126, so that the scale itself is a
-// binary32 number.
+// |v| as bits, 0 for infinities and NaN: they take no part in a scale (and
+// come out of sp_split as such at any)
+__device__ __forceinline__ uint32_t sp_finite_bits(uint32_t u) {
+    u &= 0x7fffffffu;
+    return u < 0x7f800000u ? u : 0u;
+}
+// Exponent that brings the largest finite magnitude (as bits) to [2^14, 2^15);
+// none for zero.  At most 2^126, so that the scale itself is a binary32 number.
 __device__ __forceinline__ int sp_scale_exp(uint32_t max_bits) {
-    if (max_bits == 0 || max_bits >= 0x7f800000u) return 0;
+    if (max_bits == 0) return 0;
     const int e = (int)(max_bits >> 23) - 127;   // (subnormal: below every normal one)
     return min(14 - e, 126);
 }
@@ -113,7 +118,7 @@ __device__ __forceinline__ void sp_store(char *tile, int lane, const T (&v)[8], 
     reinterpret_cast<uint32_t *>(tile + sp_parts<T>() * 1024)[lane] = pos;
 }
 
-// Largest |value| (as bits) of `count` consecutive binary32 numbers, by a
+// Largest finite |value| (as bits) of `count` consecutive binary32 numbers, by a
 // workgroup of TH threads; red: TH / 64 words of LDS
 template <int TH>
 __device__ __forceinline__ uint32_t sp_block_max(const float *p, int64_t count, uint32_t *red) {
@@ -131,7 +136,7 @@ __device__ __forceinline__ uint32_t sp_block_max(const float *p, int64_t count, 
 #pragma unroll
             for (int k = 0; k < 4; ++k)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) mx = max(mx, u[k][e] & 0x7fffffffu);
+                for (int e = 0; e < 4; ++e) mx = max(mx, sp_finite_bits(u[k][e]));
         }
     } else {
         for (int64_t i = tid; i < count; i += 8 * TH) {
@@ -139,7 +144,7 @@ __device__ __forceinline__ uint32_t sp_block_max(const float *p, int64_t count, 
 #pragma unroll
             for (int k = 0; k < 8; ++k) u[k] = __builtin_bit_cast(uint32_t, p[min(i + k * TH, count - 1)]);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) mx = max(mx, u[k] & 0x7fffffffu);
+            for (int k = 0; k < 8; ++k) mx = max(mx, sp_finite_bits(u[k]));
         }
     }
 #pragma unroll
@@ -152,7 +157,7 @@ __device__ __forceinline__ uint32_t sp_block_max(const float *p, int64_t count, 
     return mx;
 }
 
-// Largest |entry| (as bits) of 64 tokens of X over kSpXRows rows, by a
+// Largest finite |entry| (as bits) of 64 tokens of X over kSpXRows rows, by a
 // workgroup of TH threads: part `rb` of the tokens' maxima
 constexpr int kSpXRows = 192;
 template <int TH>
@@ -166,7 +171,7 @@ __device__ __forceinline__ void sp_token_max(const float *X, int64_t ldx, int K,
     for (int j = 0; j < IT; ++j)
         u[j] = __builtin_bit_cast(uint32_t, xc[(int64_t)min(rb * kSpXRows + r0 + j * RG, K - 1) * ldx]);
 #pragma unroll
-    for (int j = 0; j < IT; ++j) mx = max(mx, u[j] & 0x7fffffffu);
+    for (int j = 0; j < IT; ++j) mx = max(mx, sp_finite_bits(u[j]));
     red[tid] = mx;
     __syncthreads();
     if (tid < 64 && t0 + tid < N) {

@@ -1104,3 +1104,60 @@ def test_sparse_product_without_workspace_memory(nmg, dtype, monkeypatch):
     dense = nmg.p_densify(pv, pidx, PL).double().cpu().numpy()
     x = X.double().numpy()
     check_product(Yp, dense @ x, np.abs(dense) @ np.abs(x), dtype, "chunked", (K // 4) * 2)
+
+
+# ---- products whose operands hold non-finite entries, zeros, wide ranges
+
+def packed_kinds(nmg, W, group, chunked):
+    """The weight packed both ways: (name, product of kernel, kept-column mask
+    and dense weight in 64 bits)."""
+    n, m, g = group
+    v, idx, L = nmg.compress(W.to(DEV), n, m, g)
+    yield ("group", L.C * n, lambda X, k: nmg.spmm(v, idx, X, L, k),
+           nmg.densify(torch.ones_like(v), idx, L).double(), nmg.densify(v, idx, L).double())
+    n, m, g = chunked
+    pv, pidx, PL = nmg.p_compress(W.to(DEV), n, m, g)
+    assert nmg.lib().nmg_p_spmm_workspace_bytes(PL.c, 0, 130) > 0      # AUTO takes the kernel
+    yield ("chunked", PL.B * n, lambda X, k: nmg.p_spmm(pv, pidx, X, PL, "auto" if k == "sparse" else k),
+           nmg.p_densify(torch.ones_like(pv), pidx, PL).double(), nmg.p_densify(pv, pidx, PL).double())
+
+
+def check_kept_only(product, X, keff, mask, Wd, dtype, what):
+    """Outputs that select no infinity or NaN are within the product's bound of
+    the 64-bit one; the others have the class and sign of the multiply-adds
+    over the kept columns (the vector kernel)."""
+    Xd = X.to(DEV)
+    Y, ref = product(Xd, "sparse"), product(Xd, "valu").float()
+    torch.cuda.synchronize()
+    bad_x, bad_w = ~torch.isfinite(Xd), ~torch.isfinite(Wd)
+    hit = ((mask @ bad_x.double()) > 0) | bad_w.any(1)[:, None]
+    W0, X0 = Wd.masked_fill(bad_w, 0.0), Xd.double().masked_fill(bad_x, 0.0)
+    Yref, B = W0 @ X0, W0.abs() @ X0.abs()
+    keep = ~hit
+    clean = torch.where(keep, Y, torch.zeros_like(Y))
+    assert torch.isfinite(clean).all(), what
+    zero = torch.zeros_like(Yref)
+    worst = check_product(clean, np_of(torch.where(keep, Yref, zero)), np_of(torch.where(keep, B, zero)),
+                          dtype, what, keff)
+    a, b = ref[hit], Y.float()[hit]
+    assert torch.equal(torch.isnan(a), torch.isnan(b)), what
+    assert torch.equal(a[torch.isinf(a)], b[torch.isinf(b)]), what
+    return worst
+
+
+@pytest.mark.parametrize("K", [768, 3072])     # one workgroup a tile; split columns
+@pytest.mark.parametrize("entry", [float("inf"), float("nan")])
+def test_sparse_product_scale_beside_non_finite(nmg, K, entry):
+    """Binary32: an infinity or NaN does not take away the scale of the finite
+    entries of its token, or of the weights of its rows."""
+    M, N = 192, 130
+    W = synth.normal((M, K), 971, 0.02)
+    W[6] *= 2.0 ** 22          # above binary16's range
+    X = torch.ldexp(synth.normal((K, N), 972), torch.tensor(-40))
+    Wb, Xb = W.clone(), X.clone()
+    Wb[0, ::16] = entry        # 0::16: kept wherever magnitude decides
+    Xb[K // 2, ::3] = entry
+    Xb[17, 1::3] = -entry
+    for A, Z in ((W, Xb), (Wb, X), (Wb, Xb)):
+        for name, keff, product, mask, Wd in packed_kinds(nmg, A, (1, 8, 1), (1, 4, 16)):
+            check_kept_only(product, Z, keff, mask, Wd, torch.float32, f"{name} {K}")
