@@ -167,12 +167,12 @@ nmg_status x16_product(const nmg_layout *L, const void *prepared, const void *X,
                        hipStream_t stream);
 
 // the product on the sparse matrix instructions (k_spmm_sp.hip): layouts and
-// arguments it takes, bytes of scratch memory for its weight stream, the
-// preparation and product
+// arguments it takes, bytes of scratch memory for its weight stream (chunk_m:
+// m of the chunked layout, 0 for the group layout), the preparation and product
 bool sp_layout_supported(const nmg_layout *L);
 bool sp_p_layout_supported(const nmg_p_layout *L);
 bool sp_args_supported(nmg_dtype dtype, int64_t M, int64_t K, int64_t ldx, int64_t N);
-int64_t sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int64_t N);
+int64_t sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int64_t N, int chunk_m = 0);
 // whether AUTO takes it in place of `family` (its choice without workspace)
 bool sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epilogue epi, int64_t N);
 bool sp_p_preferred(const nmg_p_layout *L, int64_t N);

@@ -826,7 +826,7 @@ int64_t p_workspace_bytes(const nmg_p_layout *L, nmg_kernel kernel, int64_t N) {
     if (kernel != NMG_KERNEL_AUTO || !p_fits(L) || !sp_p_layout_supported(L) ||
         !sp_args_supported(L->dtype, L->M, L->K, N, N) || !sp_p_preferred(L, N))
         return 0;
-    return sp_stream_bytes(L->dtype, L->M, L->K, N);
+    return sp_stream_bytes(L->dtype, L->M, L->K, N, L->m);
 }
 
 nmg_status launch_p_spmm(const nmg_p_layout *L, nmg_kernel kernel, const void *values,

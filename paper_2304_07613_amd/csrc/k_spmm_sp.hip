@@ -25,9 +25,10 @@
 // 16 times the rate of v_mfma_f32_16x16x4f32.  (Three exact bfloat16 parts
 // need no scales, but six products: 65 us and 2.9e-7 against 50 us and 1.5e-7
 // at 3072 x 768 x 4096.)
-// Outputs that are not finite are recomputed by plain binary32 multiply-adds
-// of the kept columns in ascending order, so that infinities and NaN in X
-// reach only the outputs whose kept columns select them.
+// Outputs that are not finite are summed again from the packed weight in
+// binary32 multiply-adds (sp_exact, sp_again), so that infinities and NaN in X
+// reach the outputs whose kept columns select them -- kept zeros among them --
+// and no others.
 //
 // Binary16.  One part, products exact in binary32, as the other binary16
 // kernels (and the same recomputation for results that are not finite).
@@ -192,11 +193,23 @@ __device__ __forceinline__ int sp_token_exp(const uint32_t *xmax, int parts, int
     return sp_scale_exp(mx);
 }
 
-// Scratch memory: the weight stream, the partial sums of a product whose
-// columns are split over workgroups, and (binary32) the scale exponents of the
-// 16-row tiles and tokens and the partial maxima of the tokens
+// The packed weight as its owner holds it, for the outputs that are summed
+// again from it
+struct SpPacked {
+    const void *values;
+    const uint8_t *index;
+    int n, m, g, C;   // C chunks (chunked layout: block columns) a row
+    int S;            // rows of a chunk of the chunked layout, 0: group layout
+};
+
+// Scratch memory: the weight stream, (chunked layout) where every row's kept
+// weights lie, the partial sums of a product whose columns are split over
+// workgroups, and (binary32) the scale exponents of the 16-row tiles and
+// tokens and the partial maxima of the tokens
 struct SpScratch {
     char *stream;
+    uint16_t *origin;   // per 16-row tile, step and lane: its 16 / m blocks'
+                        // position in the chunk (8 bits) and kept offsets (4 each)
     int *wexp;
     uint32_t *xmax;
     int xparts;
@@ -229,11 +242,17 @@ inline int sp_splits(int64_t M, int64_t K, int64_t N, int parts) {
     const int per = (int)((np + s - 1) / s);
     return (np + per - 1) / per;     // none empty
 }
-inline SpScratch sp_scratch(void *ws, int64_t M, int64_t K, int64_t N, int parts) {
+// (chunk_m: m of the chunked layout, 0: group layout)
+inline int64_t sp_origin_bytes(int64_t M, int64_t K, int parts, int chunk_m) {
+    return chunk_m > 0 ? sp_tiles(M) * sp_steps(K, parts) * 64 * (16 / chunk_m) * 2 : 0;   // a multiple of 128
+}
+inline SpScratch sp_scratch(void *ws, int64_t M, int64_t K, int64_t N, int parts, int chunk_m) {
     char *p = static_cast<char *>(ws);
     SpScratch r = {};
     r.stream = p;
     p += sp_scale_offset(M, K, parts);
+    r.origin = reinterpret_cast<uint16_t *>(p);
+    p += sp_origin_bytes(M, K, parts, chunk_m);
     r.xparts = (int)sp_xparts(K);
     r.splits = sp_splits(M, K, N, parts);
     if (r.splits > 1) {
@@ -464,6 +483,7 @@ __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
         // the row's 1 to 4 blocks: every load in flight together
         T w0[4], w1[4];
         int o0[4], o1[4];
+        uint64_t from = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int w = min((4 * sl + q) * bpl + min(k, bpl - 1), nb - 1);
@@ -474,6 +494,7 @@ __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
             w1[k] = n == 2 ? v[1] : v[0];
             o0[k] = off[0];
             o1[k] = off[n - 1];
+            from |= (uint64_t)(uint32_t)(j | o0[k] << 8 | o1[k] << 12) << (16 * k);
         }
         SpLane<T> a;
 #pragma unroll
@@ -483,8 +504,12 @@ __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
             a.put(min(k * m + o1[k], 15), w1[k], in && n == 2);
         }
         const int row = r0 + rr;
-        sp_store<T>(ws.stream + ((int64_t)(row >> 4) * nsteps + s0 + sl) * sp_tile_bytes(sp_parts<T>()),
-                    (row & 15) + 16 * q, a.v, a.pos, scale);
+        const int64_t tile = (int64_t)(row >> 4) * nsteps + s0 + sl;
+        sp_store<T>(ws.stream + tile * sp_tile_bytes(sp_parts<T>()), (row & 15) + 16 * q, a.v, a.pos, scale);
+        uint16_t *org = ws.origin + (tile * 64 + (row & 15) + 16 * q) * bpl;
+        if (bpl == 4) *reinterpret_cast<uint64_t *>(org) = from;
+        else if (bpl == 2) *reinterpret_cast<uint32_t *>(org) = (uint32_t)from;
+        else *org = (uint16_t)from;
     }
     // rows past M in the last tile
     if (r0 + rows == M)
@@ -522,38 +547,166 @@ __device__ __forceinline__ sp_global *sp_uniform(const char *p) {
 #endif
 }
 
-// one output as a chain of binary32 multiply-adds over the kept columns
+// Kept slot s of a row of the packed weight: its value and column
 template <typename T>
-__device__ __attribute__((noinline)) float sp_chain(const char *stream, const T *X, int64_t ldx, int row,
-                                                    int tok, int K, int nsteps, int wexp) {
-    constexpr int PARTS = sp_parts<T>(), TB = sp_tile_bytes(PARTS);
+__device__ __forceinline__ T sp_slot(const SpPacked &pk, const uint16_t *origin, int row, int s, int nsteps,
+                                     int &col) {
+    const int ldv = pk.C * pk.n, two = pk.n == 2 ? 1 : 0;     // n is 1 or 2
+    const T *values = static_cast<const T *>(pk.values);
+    if (pk.S == 0) {
+        col = (s >> two) * pk.m + pk.index[(int64_t)(row / pk.g) * ldv + s];
+        return values[(int64_t)row * ldv + s];
+    }
+    // m is 4, 8 or 16: 16 / m blocks a lane of the stream
+    const int b = s >> two, lb = pk.m == 4 ? 2 : pk.m == 8 ? 1 : 0, sq = b >> lb;    // sq: 16-column range
+    const int64_t lane = ((int64_t)(row >> 4) * nsteps + (sq >> 2)) * 64 + (row & 15) + 16 * (sq & 3);
+    const uint32_t e = origin[(lane << lb) + (b & ((1 << lb) - 1))];
+    col = b * pk.m + (int)((e >> (8 + 4 * (s & two))) & 15u);
+    return values[(int64_t)(row - row % pk.S + (int)(e & 255u)) * ldv + s];
+}
+
+// One output by a wave: lane l sums the kept slots l, l + 64, .. of the row, the
+// lanes' sums are added as a tree (every lane gets the result).  U slots a lane
+// in flight; a NaN ends it.
+template <typename T, int U>
+__device__ __forceinline__ float sp_exact(const SpPacked &pk, const uint16_t *origin, const T *X, int64_t ldx,
+                                          int row, int tok, int K, int nsteps) {
+    const int lane = threadIdx.x & 63, ldv = pk.C * pk.n;
     float acc = 0.f;
-    for (int s = 0; s < nsteps; ++s) {
-        const char *tile = stream + ((int64_t)(row >> 4) * nsteps + s) * TB;
-        for (int q = 0; q < 4; ++q) {
-            const int lane = (row & 15) + 16 * q;
-            const uint32_t pos = reinterpret_cast<const uint32_t *>(tile + PARTS * 1024)[lane];
-            for (int e = 0; e < 8; ++e) {
-                float w = (float)reinterpret_cast<const _Float16 *>(tile)[8 * lane + e];
-                if constexpr (PARTS == 2) {
-                    // (an infinite weight's low part is NaN: not added)
-                    const float l = (float)reinterpret_cast<const _Float16 *>(tile + 1024)[8 * lane + e];
-                    w = fabsf(w) < __builtin_inff() ? fmaf(l, kSpLowInv, w) : w;
-                    w = __builtin_ldexpf(w, -wexp);
-                }
-                if (w == 0.f) continue;      // no kept column
-                const int k = kSpK * s + 16 * q + 4 * (e >> 1) + (int)((pos >> (2 * e)) & 3u);
-                if (k < K) acc = fmaf(w, (float)X[k * ldx + tok], acc);
-            }
+    for (int i = 0; i < ldv; i += 64 * U) {
+        T w[U];
+        int col[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            w[j] = sp_slot<T>(pk, origin, row, min(i + 64 * j + lane, ldv - 1), nsteps, col[j]);
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const float f = fmaf((float)w[j], (float)X[min(col[j], K - 1) * ldx + tok], acc);
+            acc = i + 64 * j + lane < ldv ? f : acc;
         }
+        if (__any(isnan(acc))) return __builtin_nanf("");
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    return acc;
+}
+
+// One output a lane (the same row in most lanes: its slots are broadcasts and
+// its entries of X whole runs), ascending columns
+template <typename T>
+__device__ __forceinline__ float sp_exact_lane(const SpPacked &pk, const uint16_t *origin, const T *X, int64_t ldx,
+                                               int row, int tok, int K, int nsteps) {
+    constexpr int U = 4;
+    const int ldv = pk.C * pk.n;
+    float acc = 0.f;
+    for (int i = 0; i < ldv; i += U) {
+        T w[U];
+        int col[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) w[j] = sp_slot<T>(pk, origin, row, min(i + j, ldv - 1), nsteps, col[j]);
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const float f = fmaf((float)w[j], (float)X[min(col[j], K - 1) * ldx + tok], acc);
+            acc = i + j < ldv ? f : acc;
+        }
+        if (isnan(acc)) break;
     }
     return acc;
+}
+
+// The flagged outputs of a workgroup's 64 RT rows x 128 tokens (bit t % 32 of
+// flag[row][t / 32]) summed again, by all of its waves.  Few of them: one a
+// wave at a time.  Many: 128 columns of X at a time in LDS, lane = two tokens,
+// 8 rows a wave; a lane fetches one of the row's kept slots and hands it to the
+// others, ascending columns.  3072 x 768 x 4096, 2:4:1, 59 us with none: one
+// token (1500 outputs) 131 us, every output 930 us.  A wave takes about 6.6 us
+// an output, the whole tile 440 us: equal near 530.
+constexpr int kSpAgainFew = 512;
+template <typename T>
+__device__ __forceinline__ void sp_again(const SpPacked &pk, const uint16_t *origin, const T *X, int64_t ldx,
+                                         T *Y, int64_t ldy, const T *R, int64_t ldr, int M, int K, int N,
+                                         int nsteps, int row0, int t0, int rows, int count,
+                                         const uint32_t (*flag)[kSpTok / 32], T *win) {
+    constexpr int KW = 128;
+    static_assert(KW * kSpTok * sizeof(T) <= 2 * 2 * 8 * kSpTok * 16, "the window fits the staging buffers");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto put = [&](int row, int tok, float y) __attribute__((always_inline)) {
+        T v = (T)y;
+        if (R != nullptr) v = (T)((float)v + (float)R[(int64_t)row * ldr + tok]);
+        Y[(int64_t)row * ldy + tok] = v;
+    };
+    if (count <= kSpAgainFew) {
+        for (int r = wave; r < rows; r += kSpWaves)
+            for (int q = 0; q < kSpTok / 32; ++q)
+                for (uint32_t bits = __builtin_amdgcn_readfirstlane(flag[r][q]); bits != 0; bits &= bits - 1) {
+                    const int tok = t0 + 32 * q + __builtin_ctz(bits);
+                    const float y = sp_exact<T, 8>(pk, origin, X, ldx, row0 + r, tok, K, nsteps);
+                    if (lane == 0) put(row0 + r, tok, y);
+                }
+        return;
+    }
+    const int ldv = pk.C * pk.n;
+    for (int rb = 0; rb < rows; rb += 8 * kSpWaves) {
+        float acc[8][2];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j][0] = acc[j][1] = 0.f;
+        for (int k0 = 0; k0 < K; k0 += KW) {
+            __syncthreads();
+            const int c = threadIdx.x % kSpTok;
+#pragma unroll 16
+            for (int r = threadIdx.x / kSpTok; r < KW; r += kSpThreads / kSpTok)
+                win[r * kSpTok + c] = X[(int64_t)min(k0 + r, K - 1) * ldx + min(t0 + c, N - 1)];
+            __syncthreads();
+            // at most 64 slots have their column in the window: n of m <= 1 of 2
+            const int s = k0 / pk.m * pk.n + lane, last = min(ldv, (k0 + KW + pk.m - 1) / pk.m * pk.n);
+            T w8[8];
+            int col8[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)   // (rows past M: the last one again, not stored)
+                w8[j] = sp_slot<T>(pk, origin, min(row0 + rb + 8 * wave + j, M - 1), min(s, ldv - 1), nsteps, col8[j]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float w = (float)w8[j];
+                const uint64_t in = __ballot(s < last && col8[j] >= k0 && col8[j] < k0 + KW);
+                const int off = min(max(col8[j] - k0, 0), KW - 1) * kSpTok;
+                const int q1 = in != 0 ? 64 - __builtin_clzll(in) : 0;
+                auto slots = [&](int q, auto count) __attribute__((always_inline)) {
+                    constexpr int Q = decltype(count)::value;
+                    T x[Q][2];
+#pragma unroll
+                    for (int k = 0; k < Q; ++k) {
+                        const T *p = win + __builtin_amdgcn_readlane(off, q + k) + 2 * lane;
+                        x[k][0] = p[0];
+                        x[k][1] = p[1];
+                    }
+#pragma unroll
+                    for (int k = 0; k < Q; ++k) {
+                        const float wq = __builtin_bit_cast(
+                            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), q + k));
+                        acc[j][0] = fmaf(wq, (float)x[k][0], acc[j][0]);
+                        acc[j][1] = fmaf(wq, (float)x[k][1], acc[j][1]);
+                    }
+                };
+                int q = in != 0 ? __builtin_ctzll(in) : 0;
+                for (; q + 8 <= q1; q += 8) slots(q, std::integral_constant<int, 8>{});
+                for (; q < q1; ++q) slots(q, std::integral_constant<int, 1>{});
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int r = rb + 8 * wave + j;
+            const uint32_t bits = flag[r][lane >> 4] >> (2 * lane & 31);
+            if (bits & 1u) put(row0 + r, t0 + 2 * lane, acc[j][0]);
+            if (bits & 2u) put(row0 + r, t0 + 2 * lane + 1, acc[j][1]);
+        }
+    }
 }
 
 // RT 16-row tiles per wave; VEC: two tokens a load (N >= 2); SPLIT: the
 // columns are split over gridDim.y workgroups, whose sums go to ws.part
 template <typename T, int RT, bool VEC, bool SPLIT>
-__global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *__restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, SpPacked pk,
+                                                        const T *__restrict__ X, int64_t ldx,
                                                         T *__restrict__ Y, int64_t ldy, int M, int K,
                                                         const T *__restrict__ R, int64_t ldr, int N,
                                                         int nsteps, int tiles16, int row_blocks,
@@ -568,6 +721,9 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
     // two buffers of two planes: the parts of one step (binary32), two steps (binary16)
     __shared__ __attribute__((aligned(16))) char xs[2 * 2 * UNITS * 16];
     __shared__ int texp[PARTS == 2 ? kSpTok : 1];  // the tokens' scale exponents
+    // outputs to be summed again: a bit each, and their number
+    __shared__ uint32_t flag[SPLIT ? 1 : 64 * RT][kSpTok / 32];
+    __shared__ int flagged;
 
     const char *const stream = ws.stream;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -760,6 +916,10 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
     };
     load_x(p0);
     load_a(p0, aops[0]);
+    if constexpr (!SPLIT) {   // (a barrier of the loop comes before their use)
+        for (int i = tid; i < 64 * RT * (kSpTok / 32); i += kSpThreads) (&flag[0][0])[i] = 0;
+        if (tid == 0) flagged = 0;
+    }
     if constexpr (PARTS == 2) {
         if (tid < kSpTok) {
             const int e = sp_token_exp(ws.xmax, ws.xparts, N, min(t0 + tid, N - 1));
@@ -811,6 +971,7 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
         const int we = PARTS == 2 ? ws.wexp[min(rt0 + i, tiles16 - 1)] : 0;
+        uint32_t again = 0;   // bit 4 t + r: this lane's output (t, r) is not finite
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -819,11 +980,17 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
                 if constexpr (PARTS == 2)
                     y = __builtin_ldexpf(fmaf(low[i][t][r], kSpLowInv, y), -(we + xe[t]));
                 const int row = 16 * (rt0 + i) + 4 * (lane >> 4) + r, tok = t0 + 64 * wt + 16 * t + (lane & 15);
-                if (__builtin_expect(!(fabsf(y) < __builtin_inff()) && row < M && tok < N, 0))
-                    y = sp_chain<T>(stream, X, ldx, row, tok, K, nsteps, we);
+                if (!(fabsf(y) < __builtin_inff()) && row < M && tok < N) again |= 1u << (4 * t + r);
                 *reinterpret_cast<T *>(ob + (4 * (lane >> 4) + r) * OPITCH + (16 * t + (lane & 15)) * ES) = (T)y;
             }
         p_wave_sync();
+        if (__builtin_expect(again != 0, 0)) {
+            atomicAdd(&flagged, __popc(again));
+            for (uint32_t bits = again; bits != 0; bits &= bits - 1) {
+                const int at = __builtin_ctz(bits), c = 64 * wt + 16 * (at >> 2) + (lane & 15);
+                atomicOr(&flag[16 * (wr * RT + i) + 4 * (lane >> 4) + (at & 3)][c >> 5], 1u << (c & 31));
+            }
+        }
 #pragma unroll
         for (int r0 = 0; r0 < 16; r0 += RPI) {
             const int r = r0 + lane / LPR, c = (lane % LPR) * EPL;
@@ -857,17 +1024,24 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, const T *_
         }
         p_wave_sync();
     }
+    sp_barrier();
+    if (__builtin_expect(flagged != 0, 0)) {
+        __threadfence();    // the stores above come before the ones here
+        __syncthreads();
+        sp_again<T>(pk, ws.origin, X, ldx, Y, ldy, R, ldr, M, K, N, nsteps, rb * (64 * RT), t0, 64 * RT,
+                    flagged, flag, reinterpret_cast<T *>(xs));
+    }
 }
 
 // The parts of a split product added in order, scaled back (or recomputed
 // where not finite), the residual added: one thread per output
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_sp_reduce(SpScratch ws, const T *__restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(kBlock) void k_sp_reduce(SpScratch ws, SpPacked pk, const T *__restrict__ X, int64_t ldx,
                                                       T *__restrict__ Y, int64_t ldy, int M, int K,
                                                       const T *__restrict__ R, int64_t ldr, int N,
                                                       int nsteps) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x, mn = (int64_t)M * N;
-    if (i >= mn) return;
+    const int64_t mn = (int64_t)M * N, at = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t i = min(at, mn - 1);   // (lanes past the end stay for the wave's recomputations)
     const int row = (int)(i / N), tok = (int)(i - (int64_t)row * N);
     float u[8];   // splits <= 8: every load in flight
 #pragma unroll
@@ -875,13 +1049,20 @@ __global__ __launch_bounds__(kBlock) void k_sp_reduce(SpScratch ws, const T *__r
     float y = u[0];
 #pragma unroll
     for (int z = 1; z < 8; ++z) y = z < ws.splits ? y + u[z] : y;
-    int we = 0;
-    if constexpr (sp_parts<T>() == 2) {
-        we = ws.wexp[row >> 4];
-        y = __builtin_ldexpf(y, -(we + ws.xexp[tok]));
+    if constexpr (sp_parts<T>() == 2) y = __builtin_ldexpf(y, -(ws.wexp[row >> 4] + ws.xexp[tok]));
+    bool again = at < mn && !(fabsf(y) < __builtin_inff());
+    uint64_t todo = __ballot(again);
+    if (__popcll(todo) > 8) {
+        if (again) y = sp_exact_lane<T>(pk, ws.origin, X, ldx, row, tok, K, nsteps);
+        todo = 0;
     }
-    if (__builtin_expect(!(fabsf(y) < __builtin_inff()), 0))
-        y = sp_chain<T>(ws.stream, X, ldx, row, tok, K, nsteps, we);
+    for (; todo != 0; todo &= todo - 1) {   // a wave an output
+        const int of = __builtin_ctzll(todo);
+        const float z = sp_exact<T, 4>(pk, ws.origin, X, ldx, __builtin_amdgcn_readlane(row, of),
+                                       __builtin_amdgcn_readlane(tok, of), K, nsteps);
+        y = (int)(threadIdx.x & 63) == of ? z : y;
+    }
+    if (at >= mn) return;
     T v = (T)y;
     if (R != nullptr) v = (T)((float)v + (float)R[(int64_t)row * ldr + tok]);
     Y[(int64_t)row * ldy + tok] = v;
@@ -914,7 +1095,7 @@ struct SpOut {
 };
 
 template <typename T, int RT>
-void sp_launch(const SpScratch &ws, const void *X, int64_t ldx, int M, int K, int N, const SpOut &o,
+void sp_launch(const SpScratch &ws, const SpPacked &pk, const void *X, int64_t ldx, int M, int K, int N, const SpOut &o,
                hipStream_t stream) {
     const int nsteps = (int)sp_steps(K, sp_parts<T>()), tiles16 = (int)sp_tiles(M);
     const int row_blocks = (tiles16 + 4 * RT - 1) / (4 * RT);
@@ -924,7 +1105,7 @@ void sp_launch(const SpScratch &ws, const void *X, int64_t ldx, int M, int K, in
     const bool yvec = aligned(o.Y, 16) && o.ldy % EPL == 0;
     const dim3 grid((unsigned)(row_blocks * tok_tiles), (unsigned)ws.splits), block(kSpThreads);
 #define NMG_SP(VEC, SPLIT)                                                                         \
-    hipLaunchKernelGGL((k_spmm_sp<T, RT, VEC, SPLIT>), grid, block, 0, stream, ws, (const T *)X, ldx, \
+    hipLaunchKernelGGL((k_spmm_sp<T, RT, VEC, SPLIT>), grid, block, 0, stream, ws, pk, (const T *)X, ldx, \
                        (T *)o.Y, o.ldy, M, K, (const T *)o.R, o.ldr, N, nsteps, tiles16, row_blocks, yvec)
     if constexpr (RT == 1) {   // split products have one row tile a wave
         if (ws.splits > 1) {
@@ -939,20 +1120,20 @@ void sp_launch(const SpScratch &ws, const void *X, int64_t ldx, int M, int K, in
 #undef NMG_SP
     if (ws.splits > 1)
         hipLaunchKernelGGL((k_sp_reduce<T>), dim3((unsigned)(((int64_t)M * N + kBlock - 1) / kBlock)),
-                           dim3(kBlock), 0, stream, ws, (const T *)X, ldx, (T *)o.Y, o.ldy, M, K,
+                           dim3(kBlock), 0, stream, ws, pk, (const T *)X, ldx, (T *)o.Y, o.ldy, M, K,
                            (const T *)o.R, o.ldr, N, nsteps);
 }
 
 template <typename T>
-nmg_status sp_product(const SpScratch &ws, const void *X, int64_t ldx, int M, int K, int N, const SpOut &o,
-                      hipStream_t stream) {
+nmg_status sp_product(const SpScratch &ws, const SpPacked &pk, const void *X, int64_t ldx, int M, int K, int N,
+                      const SpOut &o, hipStream_t stream) {
     switch (ws.splits > 1 ? 1 : sp_row_tiles(M, N, sp_parts<T>() == 2 ? 3 : 4)) {
         case 4:
-            if constexpr (sp_parts<T>() == 1) sp_launch<T, 4>(ws, X, ldx, M, K, N, o, stream);
+            if constexpr (sp_parts<T>() == 1) sp_launch<T, 4>(ws, pk, X, ldx, M, K, N, o, stream);
             break;
-        case 3: sp_launch<T, 3>(ws, X, ldx, M, K, N, o, stream); break;
-        case 2: sp_launch<T, 2>(ws, X, ldx, M, K, N, o, stream); break;
-        default: sp_launch<T, 1>(ws, X, ldx, M, K, N, o, stream); break;
+        case 3: sp_launch<T, 3>(ws, pk, X, ldx, M, K, N, o, stream); break;
+        case 2: sp_launch<T, 2>(ws, pk, X, ldx, M, K, N, o, stream); break;
+        default: sp_launch<T, 1>(ws, pk, X, ldx, M, K, N, o, stream); break;
     }
     return launched();
 }
@@ -969,10 +1150,10 @@ int spc_chunks(int S) {
 
 }  // namespace
 
-int64_t nmg_internal::sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int64_t N) {
+int64_t nmg_internal::sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int64_t N, int chunk_m) {
     const bool f32 = dtype == NMG_F32;
     const int splits = sp_splits(M, K, N, f32 ? 2 : 1);
-    return sp_scale_offset(M, K, f32 ? 2 : 1) + (splits > 1 ? splits * M * N * 4 : 0) +
+    return sp_scale_offset(M, K, f32 ? 2 : 1) + sp_origin_bytes(M, K, f32 ? 2 : 1, chunk_m) + (splits > 1 ? splits * M * N * 4 : 0) +
            (f32 ? 4 * (sp_tiles(M) + N + sp_xparts(K) * N) : 0);
 }
 
@@ -1041,7 +1222,8 @@ nmg_status nmg_internal::spmm_sp(const SpmmArgs &a, void *ws_) {
     const SpOut out{a.Y, a.ldy, a.epi == NMG_EPILOGUE_ADD ? a.R : nullptr, a.ldr};
     const int parts = L->dtype == NMG_F32 ? 2 : 1;
     const int nsteps = (int)sp_steps(L->K, parts), tiles = (int)sp_tiles(L->M);
-    const SpScratch ws = sp_scratch(ws_, L->M, L->K, a.N, parts);
+    const SpScratch ws = sp_scratch(ws_, L->M, L->K, a.N, parts, 0);
+    const SpPacked pk{a.values, a.indices, L->n, L->m, L->g, L->C, 0};
     if (L->dtype == NMG_F32) {
         const int sgroups = (nsteps + kSpPrep / 64 - 1) / (kSpPrep / 64), wblocks = tiles * sgroups;
         const dim3 grid((unsigned)(wblocks + (a.N + 63) / 64 * ws.xparts));
@@ -1058,7 +1240,7 @@ nmg_status nmg_internal::spmm_sp(const SpmmArgs &a, void *ws_) {
 #undef NMG_SP_PREP
         const nmg_status st = launched();
         if (st != NMG_OK) return st;
-        return sp_product<float>(ws, a.X, a.ldx, L->M, L->K, a.N, out, a.stream);
+        return sp_product<float>(ws, pk, a.X, a.ldx, L->M, L->K, a.N, out, a.stream);
     }
     const int total = tiles * nsteps;
     const dim3 grid((unsigned)((total + kBlock / 64 - 1) / (kBlock / 64)));
@@ -1075,7 +1257,7 @@ nmg_status nmg_internal::spmm_sp(const SpmmArgs &a, void *ws_) {
 #undef NMG_SP_PREP
     const nmg_status st = launched();
     if (st != NMG_OK) return st;
-    return sp_product<_Float16>(ws, a.X, a.ldx, L->M, L->K, a.N, out, a.stream);
+    return sp_product<_Float16>(ws, pk, a.X, a.ldx, L->M, L->K, a.N, out, a.stream);
 }
 
 bool nmg_internal::sp_p_layout_supported(const nmg_p_layout *L) {
@@ -1089,7 +1271,8 @@ nmg_status nmg_internal::p_spmm_sp(const nmg_p_layout *L, const void *values, co
     const bool f32 = L->dtype == NMG_F32;
     const int nsteps = (int)sp_steps(L->K, f32 ? 2 : 1), cpw = spc_chunks(L->S);
     const int groups = (L->M / L->S + cpw - 1) / cpw, sblocks = (nsteps + kSpcSteps - 1) / kSpcSteps;
-    const SpScratch ws = sp_scratch(ws_, L->M, L->K, N, f32 ? 2 : 1);
+    const SpScratch ws = sp_scratch(ws_, L->M, L->K, N, f32 ? 2 : 1, L->m);
+    const SpPacked pk{values, index, L->n, L->m, L->g, L->B, L->S};
     const SpOut out{Y, ldy, nullptr, 0};
     SpPatterns few = {};
     for (int p = 0; L->P <= kSpFew && p < L->P; ++p) p_unrank(L->m, L->n, p, few.off + p * L->n);
@@ -1104,6 +1287,6 @@ nmg_status nmg_internal::p_spmm_sp(const nmg_p_layout *L, const void *values, co
 #undef NMG_SPC
     const nmg_status st = launched();
     if (st != NMG_OK) return st;
-    if (f32) return sp_product<float>(ws, X, ldx, L->M, L->K, N, out, stream);
-    return sp_product<_Float16>(ws, X, ldx, L->M, L->K, N, out, stream);
+    if (f32) return sp_product<float>(ws, pk, X, ldx, L->M, L->K, N, out, stream);
+    return sp_product<_Float16>(ws, pk, X, ldx, L->M, L->K, N, out, stream);
 }

@@ -1161,3 +1161,21 @@ def test_sparse_product_scale_beside_non_finite(nmg, K, entry):
     for A, Z in ((W, Xb), (Wb, X), (Wb, Xb)):
         for name, keff, product, mask, Wd in packed_kinds(nmg, A, (1, 8, 1), (1, 4, 16)):
             check_kept_only(product, Z, keff, mask, Wd, torch.float32, f"{name} {K}")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("K", [768, 3072])
+def test_sparse_product_kept_zeros(nmg, dtype, K):
+    """Kept weights that are 0, or far below their rows' largest, still meet
+    an infinity or NaN of X: 0 * inf is NaN, tiny * inf is inf."""
+    M, N = 192, 130
+    W = synth.normal((M, K), 981, 0.02, dtype)
+    u = torch.rand((M, K), generator=torch.Generator().manual_seed(5))
+    W[u < 0.9] = 0
+    if dtype == torch.float32:
+        W[u > 0.97] *= 2.0 ** -60
+    W[16] = 0.0
+    X = synth.normal((K, N), 982, 1.0, dtype)
+    X[K // 3, ::2], X[5, 1::4], X[K - 9, 3::4] = float("inf"), float("nan"), float("-inf")
+    for name, keff, product, mask, Wd in packed_kinds(nmg, W, (2, 4, 1), (1, 8, 8)):
+        check_kept_only(product, X, keff, mask, Wd, dtype, f"{name} {K}")
