@@ -162,19 +162,25 @@ typedef enum nmg_kernel {
                                     every call (stream-ordered; 2.25 bytes per
                                     entry of W and the scales of rows and
                                     tokens for binary32, 1.25 for binary16,
+                                    2 per block more for the chunked layout,
                                     and up to 8 M N partial sums where the
                                     columns are split over workgroups): any
                                     g, any alignment, any N; needs n = 1
                                     (m >= 2) or n = 2 with m % 4 == 0.
                                     Binary32 operands, scaled by a power of
-                                    two per 16 rows and per token, are carried
-                                    as two binary16 parts (24 bits down to
-                                    2^-28 of the largest entry of the rows or
-                                    token, an error within 2^-51 of that entry
-                                    below) and summed in binary32 from the
-                                    three leading part products.  Results that
-                                    are not finite are recomputed as binary32
-                                    multiply-adds over the kept columns      */
+                                    two per token and per row (chunked layout:
+                                    per up to 256 rows of whole chunks), are
+                                    carried as two binary16 parts (within 2^-22
+                                    of themselves down to 2^-28 of the largest
+                                    finite entry of the token or rows) and
+                                    summed in binary32 from the three leading
+                                    part products.  Outputs that entries below
+                                    that may move by more than 2^-20 of
+                                    themselves, and outputs that are not
+                                    finite, are summed again as binary32
+                                    multiply-adds of the packed weight over the
+                                    kept columns (slower by up to an order of
+                                    magnitude where most outputs are such)   */
 } nmg_kernel;
 /* With n == m every column is kept and every index row is 0 .. m-1, so the
  * matrix-core kernels treat the weight as one group whatever g is. */

@@ -8,25 +8,34 @@
 // memory, and (binary32) the scale of every token of X beside it; k_spmm_sp
 // multiplies.
 //
-// Binary32.  Every entry, scaled by a power of two (per 16 rows of W, per
-// token of X: the largest magnitude goes to [2^14, 2^15)), is carried as two
-// binary16 numbers, h = f16(v) and l = f16(2^11 (v - h)), and the product is
-// summed in binary32 from h h (one accumulator) and h l + l h (another, scaled
-// back by 2^-11 at the end).  h + 2^-11 l is within 2^-24 |v| of v (each
-// rounding to nearest leaves 12 bits) down to 2^-28 of the largest entry, and
-// within 2^-51 of that entry below (without the factor l would lose bits from
-// 2^-16 on: outputs whose kept columns miss an entry 2^26 times the others had
-// errors of 4.5e-5, now 1.3e-7, for 2 us of 53 at 3072 x 768 x 4096); l l, left
-// out, is below 2^-24 |w x| and of either sign.  The binary32 families round
+// Binary32.  Every entry, scaled by a power of two (one per token of X and per
+// row of W, in the chunked layout per workgroup of the preparation, up to 256
+// rows: the largest finite magnitude goes to [2^14, 2^15)), is carried as
+// two binary16 numbers, h = f16(v) and l = f16(2^11 (v - h)), and the product
+// is summed in binary32 from h h (one accumulator) and h l + l h (another,
+// scaled back by 2^-11 at the end).  Each rounding to nearest leaves at most
+// 2^-11 of its number: h + 2^-11 l is within 2^-22 |v| of v, and l l, left
+// out, below 2^-22 |w x|, both of either sign.  The binary32 families round
 // once per kept column on the running sum; here the sum of h h is rounded once
 // per 8 stored columns, so the error against 64 bits is smaller: 1.3e-7 to
-// 2.6e-7 (2-norm, K = 768 to 3072) where the binary32 matrix instructions give 2.5e-7 to 7e-7 on the same
-// inputs.  Three sparse binary16 products count half of K's columns each at
-// 16 times the rate of v_mfma_f32_16x16x4f32.  (Three exact bfloat16 parts
-// need no scales, but six products: 65 us and 2.9e-7 against 50 us and 1.5e-7
-// at 3072 x 768 x 4096.)
-// Outputs that are not finite are summed again from the packed weight in
-// binary32 multiply-adds (sp_exact, sp_again), so that infinities and NaN in X
+// 2.6e-7 (2-norm, K = 768 to 3072) where the binary32 matrix instructions give
+// 2.5e-7 to 7e-7 on the same inputs.  Three sparse binary16 products count half
+// of K's columns each at 16 times the rate of v_mfma_f32_16x16x4f32.  (Three
+// exact bfloat16 parts need no scales, but six products: 65 us and 2.9e-7
+// against 50 us and 1.5e-7 at 3072 x 768 x 4096.)
+//
+// Entries below 2^-14 of the scaled range (2^-28 of the largest) are no longer
+// within 2^-22 of themselves, but within 2^-36: an output whose kept columns
+// miss the large entries would lose all of its bits.  So the preparation also
+// finds the smallest magnitude that is not 0 of every token and row.  Where it
+// is that far down (the range is "wide"), an output with kk kept columns
+// differs by less than kk 2^-20 in scaled units on top of the roundings above
+// (every product at most 2^15 2^-36 for either operand): at least kk in
+// magnitude, that is within 2^-20 of itself; below, it is summed again.  With
+// entries N(0, 1) a token in 10^4 is wide and an output in 10^6 of it below kk.
+//
+// These outputs, and those that are not finite, are summed again from the
+// packed weight in binary32 multiply-adds (sp_exact, sp_again), so that infinities and NaN in X
 // reach the outputs whose kept columns select them -- kept zeros among them --
 // and no others.
 //
@@ -86,18 +95,41 @@ __device__ __forceinline__ SpPair sp_split(float a, float b, float scale) {
                                             __builtin_fmaf((float)h[1], -kSpLow, b * kSpLow)}, h2);
     return SpPair{__builtin_bit_cast(uint32_t, h), __builtin_bit_cast(uint32_t, l)};
 }
-// |v| as bits, 0 for infinities and NaN: they take no part in a scale (and
-// come out of sp_split as such at any)
-__device__ __forceinline__ uint32_t sp_finite_bits(uint32_t u) {
-    u &= 0x7fffffffu;
-    return u < 0x7f800000u ? u : 0u;
+// Largest and smallest magnitude (as bits) of a set of binary32 numbers, zeros,
+// infinities and NaN left out (the latter come out of sp_split as such at any
+// scale)
+struct SpRange {
+    uint32_t mx = 0, mn1 = ~0u;    // mn1: the smallest less 1
+    __device__ __forceinline__ void take(uint32_t u) {
+        u &= 0x7fffffffu;
+        u = u < 0x7f800000u ? u : 0u;
+        mx = max(mx, u);
+        mn1 = min(mn1, u - 1u);
+    }
+    // exponent fields: the largest's plus 1 in the high half, 255 less the
+    // smallest's in the low half (0: no such number)
+    __device__ __forceinline__ uint32_t word() const {
+        return mx == 0 ? 0u : ((mx >> 23) + 1u) << 16 | (255u - ((mn1 + 1u) >> 23));
+    }
+};
+__device__ __forceinline__ uint32_t sp_join(uint32_t a, uint32_t b) {
+    return max(a & ~0xffffu, b & ~0xffffu) | max(a & 0xffffu, b & 0xffffu);
 }
-// Exponent that brings the largest finite magnitude (as bits) to [2^14, 2^15);
-// none for zero.  At most 2^126, so that the scale itself is a binary32 number.
-__device__ __forceinline__ int sp_scale_exp(uint32_t max_bits) {
-    if (max_bits == 0) return 0;
-    const int e = (int)(max_bits >> 23) - 127;   // (subnormal: below every normal one)
-    return min(14 - e, 126);
+// A set's scale: four times the exponent that brings its largest magnitude to
+// [2^14, 2^15) (at most 2^126, so that the scale itself is a binary32 number),
+// + 1 where its range is wide, or + 2 where it has no magnitudes.
+constexpr int kSpWide = 1, kSpZero = 2;
+__device__ __forceinline__ int sp_scale_code(uint32_t range) {
+    if (range == 0) return kSpZero;
+    const int e = min(14 + 127 - (int)((range >> 16) - 1u), 126);
+    const int low = 255 - (int)(range & 0xffffu);         // the smallest's exponent field
+    return 4 * e + ((low == 0 ? -149 : low - 127) + e < -14 ? kSpWide : 0);
+}
+__device__ __forceinline__ int sp_scale_exp(int code) { return code >> 2; }
+// Scaled magnitude from which on an output of a token and row stands: kk kept
+// columns, 0 where neither range is wide or all products are 0
+__device__ __forceinline__ float sp_floor(int xcode, int wcode, float kk) {
+    return ((xcode | wcode) & (kSpWide | kSpZero)) == kSpWide ? kk : 0.f;
 }
 
 // One lane's stored values (8, binary32 or binary16) and positions to the stream
@@ -119,11 +151,11 @@ __device__ __forceinline__ void sp_store(char *tile, int lane, const T (&v)[8], 
     reinterpret_cast<uint32_t *>(tile + sp_parts<T>() * 1024)[lane] = pos;
 }
 
-// Largest finite |value| (as bits) of `count` consecutive binary32 numbers, by a
+// Range (SpRange::word) of `count` consecutive binary32 numbers, by a
 // workgroup of TH threads; red: TH / 64 words of LDS
 template <int TH>
-__device__ __forceinline__ uint32_t sp_block_max(const float *p, int64_t count, uint32_t *red) {
-    uint32_t mx = 0;
+__device__ __forceinline__ uint32_t sp_block_range(const float *p, int64_t count, uint32_t *red) {
+    SpRange r;
     const int tid = threadIdx.x;
     // 16 bytes a load where the numbers allow, 4 loads in flight (past the
     // end: the last one again)
@@ -137,7 +169,7 @@ __device__ __forceinline__ uint32_t sp_block_max(const float *p, int64_t count, 
 #pragma unroll
             for (int k = 0; k < 4; ++k)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) mx = max(mx, sp_finite_bits(u[k][e]));
+                for (int e = 0; e < 4; ++e) r.take(u[k][e]);
         }
     } else {
         for (int64_t i = tid; i < count; i += 8 * TH) {
@@ -145,52 +177,56 @@ __device__ __forceinline__ uint32_t sp_block_max(const float *p, int64_t count, 
 #pragma unroll
             for (int k = 0; k < 8; ++k) u[k] = __builtin_bit_cast(uint32_t, p[min(i + k * TH, count - 1)]);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) mx = max(mx, sp_finite_bits(u[k]));
+            for (int k = 0; k < 8; ++k) r.take(u[k]);
         }
     }
+    uint32_t w = r.word();
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o));
-    if ((tid & 63) == 0) red[tid >> 6] = mx;
+    for (int o = 32; o > 0; o >>= 1) w = sp_join(w, (uint32_t)__shfl_xor((int)w, o));
+    if ((tid & 63) == 0) red[tid >> 6] = w;
     __syncthreads();
-    mx = 0;
+    w = 0;
 #pragma unroll
-    for (int k = 0; k < TH / 64; ++k) mx = max(mx, red[k]);
-    return mx;
+    for (int k = 0; k < TH / 64; ++k) w = sp_join(w, red[k]);
+    return w;
 }
 
-// Largest finite |entry| (as bits) of 64 tokens of X over kSpXRows rows, by a
-// workgroup of TH threads: part `rb` of the tokens' maxima
+// Ranges of 64 tokens of X over kSpXRows rows, by a workgroup of TH threads:
+// part `rb` of the tokens' ranges
 constexpr int kSpXRows = 192;
 template <int TH>
-__device__ __forceinline__ void sp_token_max(const float *X, int64_t ldx, int K, int N, int t0, int rb,
-                                             uint32_t *xmax, uint32_t *red) {
+__device__ __forceinline__ void sp_token_range(const float *X, int64_t ldx, int K, int N, int t0, int rb,
+                                               uint32_t *xrange, uint32_t *red) {
     const int tid = threadIdx.x, c = tid & 63, r0 = tid >> 6;
     constexpr int RG = TH / 64, IT = kSpXRows / RG;
     const float *xc = X + min(t0 + c, N - 1);
-    uint32_t u[IT], mx = 0;
+    uint32_t u[IT];
 #pragma unroll
     for (int j = 0; j < IT; ++j)
         u[j] = __builtin_bit_cast(uint32_t, xc[(int64_t)min(rb * kSpXRows + r0 + j * RG, K - 1) * ldx]);
+    SpRange r;
 #pragma unroll
-    for (int j = 0; j < IT; ++j) mx = max(mx, sp_finite_bits(u[j]));
-    red[tid] = mx;
+    for (int j = 0; j < IT; ++j) r.take(u[j]);
+    red[tid] = r.word();
     __syncthreads();
     if (tid < 64 && t0 + tid < N) {
+        uint32_t w = red[tid];
 #pragma unroll
-        for (int w = 1; w < RG; ++w) mx = max(mx, red[w * 64 + tid]);
-        xmax[(int64_t)rb * N + t0 + tid] = mx;
+        for (int k = 1; k < RG; ++k) w = sp_join(w, red[k * 64 + tid]);
+        xrange[(int64_t)rb * N + t0 + tid] = w;
     }
 }
-__device__ __forceinline__ int sp_token_exp(const uint32_t *xmax, int parts, int N, int tok) {
-    uint32_t mx = 0;
+// the token's scale code from the parts
+__device__ __forceinline__ int sp_token_code(const uint32_t *xrange, int parts, int N, int tok) {
+    uint32_t w = 0;
     for (int p = 0; p < parts; p += 8) {
         uint32_t u[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) u[j] = xmax[(int64_t)min(p + j, parts - 1) * N + tok];
+        for (int j = 0; j < 8; ++j) u[j] = xrange[(int64_t)min(p + j, parts - 1) * N + tok];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) mx = max(mx, u[j]);
+        for (int j = 0; j < 8; ++j) w = sp_join(w, u[j]);
     }
-    return sp_scale_exp(mx);
+    return sp_scale_code(w);
 }
 
 // The packed weight as its owner holds it, for the outputs that are summed
@@ -204,16 +240,16 @@ struct SpPacked {
 
 // Scratch memory: the weight stream, (chunked layout) where every row's kept
 // weights lie, the partial sums of a product whose columns are split over
-// workgroups, and (binary32) the scale exponents of the 16-row tiles and
-// tokens and the partial maxima of the tokens
+// workgroups, and (binary32) the scale codes of rows and tokens and the
+// partial ranges of the tokens
 struct SpScratch {
     char *stream;
     uint16_t *origin;   // per 16-row tile, step and lane: its 16 / m blocks'
                         // position in the chunk (8 bits) and kept offsets (4 each)
-    int *wexp;
-    uint32_t *xmax;
+    int *wcode;
+    uint32_t *xrange;
     int xparts;
-    int *xexp;
+    int *xcode;
     float *part;     // splits x M x N, or NULL
     int splits;
 };
@@ -259,9 +295,9 @@ inline SpScratch sp_scratch(void *ws, int64_t M, int64_t K, int64_t N, int parts
         r.part = reinterpret_cast<float *>(p);
         p += r.splits * M * N * 4;
     }
-    r.wexp = reinterpret_cast<int *>(p);
-    r.xexp = r.wexp + sp_tiles(M);
-    r.xmax = reinterpret_cast<uint32_t *>(r.xexp + N);
+    r.wcode = reinterpret_cast<int *>(p);
+    r.xcode = r.wcode + 16 * sp_tiles(M);
+    r.xrange = reinterpret_cast<uint32_t *>(r.xcode + N);
     return r;
 }
 
@@ -366,9 +402,10 @@ __global__ __launch_bounds__(kBlock) void k_sp_prepare_f16(const _Float16 *__res
     sp_store<_Float16>(stream + (int64_t)id * sp_tile_bytes(1), lane, a.v, a.pos, 1.f);
 }
 
-// Binary32: a workgroup per 16-row tile and 8 steps (the tile's scale from the
-// largest of its kept weights, found again by each of them, then a step per
-// wave), and one per 64 tokens and 192 rows of X (part of the tokens' maxima).
+// Binary32: a workgroup per 16-row tile and 8 steps (the rows' scales from the
+// ranges of their kept weights, two rows a wave, found again by each of the
+// tile's workgroups; then a step per wave), and one per 64 tokens and 192 rows
+// of X (part of the tokens' ranges).
 constexpr int kSpPrep = 512;
 template <int MC>
 __global__ __launch_bounds__(kSpPrep) void k_sp_prepare(const float *__restrict__ values,
@@ -380,20 +417,59 @@ __global__ __launch_bounds__(kSpPrep) void k_sp_prepare(const float *__restrict_
     const int lane = threadIdx.x & 63;
     if ((int)blockIdx.x >= wblocks) {
         const int i = blockIdx.x - wblocks;
-        sp_token_max<kSpPrep>(X, ldx, K, N, 64 * (i / ws.xparts), i % ws.xparts, ws.xmax, red);
+        sp_token_range<kSpPrep>(X, ldx, K, N, 64 * (i / ws.xparts), i % ws.xparts, ws.xrange, red);
         return;
     }
     const int rt = blockIdx.x / sgroups, s = ((int)blockIdx.x - rt * sgroups) * (kSpPrep / 64) + (threadIdx.x >> 6);
     const int64_t ldv = (int64_t)C * n;
-    SpLane<float> a;   // gathered while the maximum is found
+    SpLane<float> a;   // gathered while the range is found
     if (s < nsteps)
         sp_gather<float, MC>(values, indices, 16 * rt + (lane & 15), kSpK * s + 16 * (lane >> 4), M, K, n, m,
                              g, C, a);
-    const int e = sp_scale_exp(sp_block_max<kSpPrep>(values + 16 * rt * ldv, min(16, M - 16 * rt) * ldv, red));
-    if (threadIdx.x == 0) ws.wexp[rt] = e;   // (the same from each of the tile's workgroups)
+    const int r0 = 2 * (threadIdx.x >> 6);
+    SpRange range[2];
+    const bool vec = (reinterpret_cast<uintptr_t>(values) & 15) == 0 && ldv % 4 == 0;
+    const float *row[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) row[h] = values + min(16 * rt + r0 + h, M - 1) * ldv;
+    // (past the end: the last one again)
+    if (vec) {
+        for (int64_t i = lane; i < ldv / 4; i += 128) {
+            u4 u[2][2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) u[h][k] = reinterpret_cast<const u4 *>(row[h])[min(i + 64 * k, ldv / 4 - 1)];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) range[h].take(u[h][k >> 2][k & 3]);
+        }
+    } else {
+        for (int64_t i = lane; i < ldv; i += 256) {
+            uint32_t u[2][4];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) u[h][k] = __builtin_bit_cast(uint32_t, row[h][min(i + 64 * k, ldv - 1)]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) range[h].take(u[h][k]);
+        }
+    }
+    uint32_t word[2] = {range[0].word(), range[1].word()};
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) word[h] = sp_join(word[h], (uint32_t)__shfl_xor((int)word[h], o));
+    if (lane < 2) red[r0 + lane] = (uint32_t)sp_scale_code(lane == 0 ? word[0] : word[1]);
+    __syncthreads();
+    const int code = (int)red[lane & 15];        // (the same from each of the tile's workgroups)
+    if (threadIdx.x < 16) ws.wcode[16 * rt + threadIdx.x] = code;
     if (s < nsteps)
         sp_store<float>(ws.stream + ((int64_t)rt * nsteps + s) * sp_tile_bytes(2), lane, a.v, a.pos,
-                        __builtin_ldexpf(1.f, e));
+                        __builtin_ldexpf(1.f, sp_scale_exp(code)));
 }
 
 constexpr int kSpcRows = 256;          // chunk rows per workgroup, at most (S <= 256)
@@ -410,9 +486,9 @@ struct SpPatterns {
 // The chunked layout (m in {4, 8, 16}, n <= 2): a workgroup takes `cpw` chunks
 // (whole 16-row tiles, at most 256 rows) of 2 steps' block columns, inverts
 // their index in LDS and gathers every row's blocks.  Binary32: its rows share
-// one scale, from the largest of their kept weights (found again by each
+// one scale, from the range of their kept weights (found again by each
 // workgroup of the same chunks: they lie side by side in memory).  One
-// workgroup per 64 tokens and 192 rows of X finds part of the tokens' maxima.
+// workgroup per 64 tokens and 192 rows of X finds part of the tokens' ranges.
 template <typename T>
 __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
     const T *__restrict__ values, const uint8_t *__restrict__ index, const T *__restrict__ X, int64_t ldx,
@@ -425,7 +501,7 @@ __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
     if ((int)blockIdx.x >= groups * sblocks) {
         const int i = (int)blockIdx.x - groups * sblocks;
         if constexpr (sp_parts<T>() == 2)
-            sp_token_max<kSpcThreads>(X, ldx, K, N, 64 * (i / ws.xparts), i % ws.xparts, ws.xmax, red);
+            sp_token_range<kSpcThreads>(X, ldx, K, N, 64 * (i / ws.xparts), i % ws.xparts, ws.xrange, red);
         return;
     }
     const int grp = blockIdx.x / sblocks, s0 = ((int)blockIdx.x - grp * sblocks) * kSpcSteps;
@@ -443,10 +519,11 @@ __global__ __launch_bounds__(kSpcThreads) void k_sp_prepare_chunked(
     for (int i = tid; i < ns * bps * kSpcRows / 4; i += kSpcThreads) reinterpret_cast<uint32_t *>(inv)[i] = 0;
     float scale = 1.f;
     if constexpr (sp_parts<T>() == 2) {
-        const int e = sp_scale_exp(sp_block_max<kSpcThreads>(values + (int64_t)r0 * ldv, (int64_t)rows * ldv, red));
-        scale = __builtin_ldexpf(1.f, e);
+        const int code =
+            sp_scale_code(sp_block_range<kSpcThreads>(values + (int64_t)r0 * ldv, (int64_t)rows * ldv, red));
+        scale = __builtin_ldexpf(1.f, sp_scale_exp(code));
         if (s0 == 0)
-            for (int t = tid; 16 * t < rows; t += kSpcThreads) ws.wexp[r0 / 16 + t] = e;
+            for (int t = tid; t < (rows + 15) / 16 * 16; t += kSpcThreads) ws.wcode[r0 + t] = code;
     }
     __syncthreads();
     // stored row j's index bytes of the block columns, 4 at a time where its
@@ -720,7 +797,7 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, SpPacked p
     static_assert(kSpWaves * OTILE <= 2 * 2 * UNITS * 16, "outputs fit the staging buffers");
     // two buffers of two planes: the parts of one step (binary32), two steps (binary16)
     __shared__ __attribute__((aligned(16))) char xs[2 * 2 * UNITS * 16];
-    __shared__ int texp[PARTS == 2 ? kSpTok : 1];  // the tokens' scale exponents
+    __shared__ int tcode[PARTS == 2 ? kSpTok : 1]; // the tokens' scale codes
     // outputs to be summed again: a bit each, and their number
     __shared__ uint32_t flag[SPLIT ? 1 : 64 * RT][kSpTok / 32];
     __shared__ int flagged;
@@ -922,13 +999,13 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, SpPacked p
     }
     if constexpr (PARTS == 2) {
         if (tid < kSpTok) {
-            const int e = sp_token_exp(ws.xmax, ws.xparts, N, min(t0 + tid, N - 1));
-            texp[tid] = e;
-            if (SPLIT && rb == 0 && blockIdx.y == 0 && t0 + tid < N) ws.xexp[t0 + tid] = e;
+            const int code = sp_token_code(ws.xrange, ws.xparts, N, min(t0 + tid, N - 1));
+            tcode[tid] = code;
+            if (SPLIT && rb == 0 && blockIdx.y == 0 && t0 + tid < N) ws.xcode[t0 + tid] = code;
         }
         sp_barrier();
 #pragma unroll
-        for (int j = 0; j < 2; ++j) xscale[j] = __builtin_ldexpf(1.f, texp[xt[j]]);
+        for (int j = 0; j < 2; ++j) xscale[j] = __builtin_ldexpf(1.f, sp_scale_exp(tcode[xt[j]]));
     }
     write_x(0, 0);
     write_x(0, 1);
@@ -963,29 +1040,50 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, SpPacked p
     constexpr int RPI = 64 / LPR;                   // rows per store instruction
     typedef T OV __attribute__((ext_vector_type(EPL)));
     typedef OV OVu __attribute__((aligned(sizeof(T))));   // element-aligned
-    int xe[4] = {0, 0, 0, 0};
+    int xc[4] = {0, 0, 0, 0};
     if constexpr (PARTS == 2) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) xe[t] = texp[64 * wt + 16 * t + (lane & 15)];
+        for (int t = 0; t < 4; ++t) xc[t] = tcode[64 * wt + 16 * t + (lane & 15)];
     }
+    const float kk = (float)(pk.C * pk.n);
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
-        const int we = PARTS == 2 ? ws.wexp[min(rt0 + i, tiles16 - 1)] : 0;
-        uint32_t again = 0;   // bit 4 t + r: this lane's output (t, r) is not finite
+        uint64_t doubt = 0;   // lanes with an output that is not finite, or a wide range
+        int wc[4] = {0, 0, 0, 0};
+        if constexpr (PARTS == 2) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) wc[r] = ws.wcode[16 * min(rt0 + i, tiles16 - 1) + 4 * (lane >> 4) + r];
+            doubt = __ballot(((xc[0] | xc[1] | xc[2] | xc[3] | wc[0] | wc[1] | wc[2] | wc[3]) & kSpWide) != 0);
+        }
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 float y = acc[i][t][r];
                 if constexpr (PARTS == 2)
-                    y = __builtin_ldexpf(fmaf(low[i][t][r], kSpLowInv, y), -(we + xe[t]));
-                const int row = 16 * (rt0 + i) + 4 * (lane >> 4) + r, tok = t0 + 64 * wt + 16 * t + (lane & 15);
-                if (!(fabsf(y) < __builtin_inff()) && row < M && tok < N) again |= 1u << (4 * t + r);
+                    y = __builtin_ldexpf(fmaf(low[i][t][r], kSpLowInv, y), -(sp_scale_exp(wc[r]) + sp_scale_exp(xc[t])));
+                doubt |= __ballot(!(fabsf(y) < __builtin_inff()));
                 *reinterpret_cast<T *>(ob + (4 * (lane >> 4) + r) * OPITCH + (16 * t + (lane & 15)) * ES) = (T)y;
             }
         p_wave_sync();
-        if (__builtin_expect(again != 0, 0)) {
-            atomicAdd(&flagged, __popc(again));
+        if (__builtin_expect(doubt != 0, 0)) {
+            uint32_t again = 0;   // bit 4 t + r: this lane's output (t, r) does not stand
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float y = acc[i][t][r];
+                    bool stands = true;
+                    if constexpr (PARTS == 2) {
+                        y = fmaf(low[i][t][r], kSpLowInv, y);
+                        stands = fabsf(y) >= sp_floor(xc[t], wc[r], kk);
+                        y = __builtin_ldexpf(y, -(sp_scale_exp(wc[r]) + sp_scale_exp(xc[t])));
+                    }
+                    const int row = 16 * (rt0 + i) + 4 * (lane >> 4) + r, tok = t0 + 64 * wt + 16 * t + (lane & 15);
+                    stands = stands && fabsf(y) < __builtin_inff();
+                    if (!stands && row < M && tok < N) again |= 1u << (4 * t + r);
+                }
+            if (again != 0) atomicAdd(&flagged, __popc(again));
             for (uint32_t bits = again; bits != 0; bits &= bits - 1) {
                 const int at = __builtin_ctz(bits), c = 64 * wt + 16 * (at >> 2) + (lane & 15);
                 atomicOr(&flag[16 * (wr * RT + i) + 4 * (lane >> 4) + (at & 3)][c >> 5], 1u << (c & 31));
@@ -1034,7 +1132,7 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, SpPacked p
 }
 
 // The parts of a split product added in order, scaled back (or recomputed
-// where not finite), the residual added: one thread per output
+// where not finite or below its floor), the residual added: one thread per output
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_sp_reduce(SpScratch ws, SpPacked pk, const T *__restrict__ X, int64_t ldx,
                                                       T *__restrict__ Y, int64_t ldy, int M, int K,
@@ -1049,8 +1147,13 @@ __global__ __launch_bounds__(kBlock) void k_sp_reduce(SpScratch ws, SpPacked pk,
     float y = u[0];
 #pragma unroll
     for (int z = 1; z < 8; ++z) y = z < ws.splits ? y + u[z] : y;
-    if constexpr (sp_parts<T>() == 2) y = __builtin_ldexpf(y, -(ws.wexp[row >> 4] + ws.xexp[tok]));
-    bool again = at < mn && !(fabsf(y) < __builtin_inff());
+    bool stands = true;
+    if constexpr (sp_parts<T>() == 2) {
+        const int wc = ws.wcode[row], xc = ws.xcode[tok];
+        stands = fabsf(y) >= sp_floor(xc, wc, (float)(pk.C * pk.n));
+        y = __builtin_ldexpf(y, -(sp_scale_exp(wc) + sp_scale_exp(xc)));
+    }
+    const bool again = at < mn && !(stands && fabsf(y) < __builtin_inff());
     uint64_t todo = __ballot(again);
     if (__popcll(todo) > 8) {
         if (again) y = sp_exact_lane<T>(pk, ws.origin, X, ldx, row, tok, K, nsteps);
@@ -1154,7 +1257,7 @@ int64_t nmg_internal::sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int
     const bool f32 = dtype == NMG_F32;
     const int splits = sp_splits(M, K, N, f32 ? 2 : 1);
     return sp_scale_offset(M, K, f32 ? 2 : 1) + sp_origin_bytes(M, K, f32 ? 2 : 1, chunk_m) + (splits > 1 ? splits * M * N * 4 : 0) +
-           (f32 ? 4 * (sp_tiles(M) + N + sp_xparts(K) * N) : 0);
+           (f32 ? 4 * (16 * sp_tiles(M) + N + sp_xparts(K) * N) : 0);
 }
 
 bool nmg_internal::sp_args_supported(nmg_dtype dtype, int64_t M, int64_t K, int64_t ldx, int64_t N) {

@@ -1179,3 +1179,29 @@ def test_sparse_product_kept_zeros(nmg, dtype, K):
     X[K // 3, ::2], X[5, 1::4], X[K - 9, 3::4] = float("inf"), float("nan"), float("-inf")
     for name, keff, product, mask, Wd in packed_kinds(nmg, W, (2, 4, 1), (1, 8, 8)):
         check_kept_only(product, X, keff, mask, Wd, dtype, f"{name} {K}")
+
+
+WIDE = [20, 27, 30, 34, 38, 46, 60, 100]
+
+
+@pytest.mark.parametrize("K", [768, 3072])
+@pytest.mark.parametrize("exp", WIDE)
+def test_sparse_product_any_range(nmg, K, exp):
+    """Binary32 outputs whose kept columns miss an entry 2^exp above the
+    others, beside weights that much larger, and operands whose entries are
+    spread over all of that: within the product's bound everywhere."""
+    M, N = 192, 130
+    W, X = synth.normal((M, K), 991, 0.02), synth.normal((K, N), 992)
+    Xt = X.clone()
+    Xt[::64, ::2] = 2.0 ** exp
+    Xt[:, 7] = 0.0
+    Wr = W.clone()
+    Wr[::5] *= 2.0 ** -exp
+    Wr[3] = 0.0
+    gen = torch.Generator().manual_seed(exp)
+    spread = lambda t: torch.ldexp(t, -torch.randint(0, exp // 2 + 1, t.shape, generator=gen).float())
+    worst = {}
+    for what, A, Z in (("token", W, Xt), ("rows", Wr, X), ("both", Wr, Xt), ("spread", spread(W), spread(X))):
+        for name, keff, product, mask, Wd in packed_kinds(nmg, A, (1, 8, 1), (1, 4, 16)):
+            worst[what, name] = check_kept_only(product, Z, keff, mask, Wd, torch.float32, f"{what} {name}")
+    print("[any range]", exp, {k: f"{v:.1e}" for k, v in worst.items()}, flush=True)
