@@ -1,8 +1,9 @@
 """Benchmark of the n:m:g hot path on one MI355X.
 
 One step = the whole path on one batch: nmg_compress of a dense weight
-(group score, top-n select, pack) followed by nmg_spmm of the packed weight
-with a 4096-token activation.  Default workload: BERT-base FFN up-projection,
+(group score, top-n select, pack) followed by the product of the packed weight
+with a 4096-token activation (nmg_spmm_epilogue_ws, the call behind nmg.spmm,
+with the kernel family that nmg.auto_kernel names and one kept workspace).  Default workload: BERT-base FFN up-projection,
 W 3072 x 768 fp32 ~ N(0, 0.02^2), 1:4 (75% sparse), g = 8, X 768 x 4096 fp32
 ~ N(0, 1); synthetic, seeded.
 
@@ -92,8 +93,7 @@ def parse():
 
 # The sources that make the profiled kernels (the headline product and the
 # converter): the stored traffic figure holds while these are unchanged.
-TRAFFIC_SOURCES = ("common.hpp", "k_spmm_mfma_s.hpp", "k_spmm_mfma_s_f32_u8.hip",
-                   "k_elementwise.hip")
+TRAFFIC_SOURCES = ("common.hpp", "chunked.hpp", "k_spmm_sp.hip", "k_elementwise.hip")
 
 
 def traffic_digest() -> str:
@@ -170,11 +170,16 @@ def time_layer(ctx, args, workload, layer_no, lin, kernel_req):
     lib = nmg.lib()
     lref = ctypes.byref(L.c)
     vp = lambda t: ctypes.c_void_p(t.data_ptr())
+    # one workspace for all calls (they run one after the other on one stream),
+    # as a caller of nmg_spmm_epilogue_ws keeps it
+    ws_bytes = lib.nmg_spmm_workspace_bytes(lref, nmg.KERNELS[kernel], lin.N)
+    ws = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=ctx.dev)
     # arguments marshalled beforehand so the host never starves the GPU
     calls = [((lref, vp(W), lin.K, vp(v), vp(idx), ctx.sp),
-              (lref, nmg.KERNELS[kernel], vp(v), vp(idx), vp(X), lin.N, lin.N, vp(Y), lin.N,
-               ctx.sp)) for (W, X, v, idx, Y) in sets]
-    compress_c, spmm_c = lib.nmg_compress, lib.nmg_spmm_with
+              (lref, nmg.KERNELS[kernel], 0, vp(v), vp(idx), vp(X), lin.N, lin.N, None, 0, vp(Y),
+               lin.N, vp(ws) if ws_bytes else None, ws_bytes, ctx.sp))
+             for (W, X, v, idx, Y) in sets]
+    compress_c, spmm_c = lib.nmg_compress, lib.nmg_spmm_epilogue_ws
     status = []
     family = None
     if not args.no_family:
@@ -272,10 +277,10 @@ def layer_record(lin, res):
     kernel = res["kernel"]
     spmm_s = res["spmm_ms"] * 1e-3
     tflops = lin.useful_flop / spmm_s / 1e12
-    matrix = kernel.startswith("mfma") or kernel.startswith("smfmac")
-    # binary16 kernels on the binary16 matrix instructions; the others on the
-    # binary32 ones; the vector kernels without packed math
-    if kernel in ("mfma_f16", "smfmac_f16", "mfma_wide"):
+    matrix = kernel.startswith(("mfma", "smfmac", "sparse"))
+    # kernels on the binary16 matrix instructions (sparse: for binary32 too);
+    # the others on the binary32 ones; the vector kernels without packed math
+    if kernel in ("mfma_f16", "smfmac_f16", "mfma_wide", "sparse"):
         peak = FP16_MFMA_PEAK_TFLOPS
     else:
         peak = FP32_MFMA_PEAK_TFLOPS if matrix else FP32_VALU_PEAK_TFLOPS
@@ -379,7 +384,7 @@ def headline(ctx, args):
     lin = wl.layers[layer]
     res = time_layer(ctx, args, workload, layer, lin, args.kernel)
     rec = layer_record(lin, res)
-    if workload == 2:
+    if workload == 2 and res["kernel"] == "sparse":   # the profiled kernel
         rec["roofline"]["traffic"] = stored_traffic(traffic_digest())
     out = {
         "metric": METRIC if workload == 2 else "nmg_spmm useful GFLOP/s",
@@ -417,12 +422,6 @@ def sweep(ctx, args):
                           "kernel": res["kernel"], "energy": round(energy, 4),
                           "ms_per_step": round(res["ms_step"], 5), **rec}), flush=True)
         del res
-
-
-def binding_kernel(nmg, L, N):
-    """AUTO's family through the binding, which brings a workspace."""
-    need = [nmg.lib().nmg_spmm_workspace_bytes(L.c, nmg.KERNELS[k], N) for k in ("auto", "sparse")]
-    return "sparse" if need[0] == need[1] > 0 else nmg.auto_kernel(L, N)
 
 
 def chunked(ctx, args):
@@ -466,7 +465,7 @@ def chunked(ctx, args):
                "us_spmm_chunked": round(timed(lambda: nmg.p_spmm(pv, pidx, X, PL)), 2),
                "us_spmm_chunked_valu": round(timed(lambda: nmg.p_spmm(pv, pidx, X, PL, "valu")), 2),
                "us_spmm_chunked_mfma": round(timed(lambda: nmg.p_spmm(pv, pidx, X, PL, "mfma")), 2),
-               "group_kernel": binding_kernel(nmg, L, lin.N)}
+               "group_kernel": nmg.auto_kernel(L, lin.N)}
         rec["tflops_spmm_chunked"] = round(lin.useful_flop / rec["us_spmm_chunked"] / 1e6, 2)
         rec["tflops_spmm_group"] = round(lin.useful_flop / rec["us_spmm_group"] / 1e6, 2)
         print(json.dumps(rec), flush=True)

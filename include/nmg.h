@@ -301,6 +301,16 @@ nmg_status nmg_spmm_epilogue_ws(const nmg_layout *layout, nmg_kernel kernel, nmg
  * (or the arguments are invalid).  Pure host code. */
 int64_t nmg_spmm_workspace_bytes(const nmg_layout *layout, nmg_kernel kernel, int64_t N);
 
+/* The family nmg_spmm_epilogue_ws runs for `kernel` on these arguments when it
+ * is brought *workspace_bytes (may be NULL) of workspace, and those bytes: for
+ * this call exactly, where nmg_spmm_workspace_bytes covers every alignment.
+ * Of the pointers only the alignment counts; NULL is taken as aligned.
+ * NMG_KERNEL_AUTO (and 0 bytes) for an invalid layout, N or ldx.  Pure host
+ * code. */
+nmg_kernel nmg_spmm_plan(const nmg_layout *layout, nmg_kernel kernel, const void *values,
+                         const uint8_t *indices, const void *X, int64_t ldx, int64_t N,
+                         int64_t *workspace_bytes);
+
 /* The kernel family NMG_KERNEL_AUTO picks for this layout and N without
  * scratch memory for NMG_KERNEL_SPARSE (which it takes instead of
  * NMG_KERNEL_MFMA_EXPAND for the layouts that kernel takes, and instead of

@@ -513,33 +513,48 @@ int64_t nmg_p_spmm_workspace_bytes(const nmg_p_layout *L, nmg_kernel kernel, int
     return p_workspace_bytes(L, kernel, N);
 }
 
-int64_t nmg_spmm_workspace_bytes(const nmg_layout *L, nmg_kernel kernel, int64_t N) {
-    if (check_layout(L) != NMG_OK || N < 1) return 0;
+nmg_kernel nmg_spmm_plan(const nmg_layout *L, nmg_kernel kernel, const void *values,
+                         const uint8_t *indices, const void *X, int64_t ldx, int64_t N,
+                         int64_t *workspace_bytes) {
+    int64_t bytes = 0;
+    if (workspace_bytes) *workspace_bytes = 0;
+    if (check_layout(L) != NMG_OK || N < 1 || N > INT32_MAX || ldx < N) return NMG_KERNEL_AUTO;
     nmg_layout dense;
     L = effective_layout(L, &dense);
-    const bool sp = sp_layout_supported(L) && sp_args_supported(L->dtype, L->M, L->K, N, N);
+    const bool sp = sp_layout_supported(L) && sp_args_supported(L->dtype, L->M, L->K, ldx, N);
+    const nmg_kernel requested = kernel;
+    if (kernel == NMG_KERNEL_AUTO || kernel == NMG_KERNEL_MFMA)
+        kernel = auto_family(L, kernel, values, indices, X, ldx, N);
+    if (requested == NMG_KERNEL_AUTO && sp && sp_preferred(L, kernel, NMG_EPILOGUE_NONE, N))
+        kernel = NMG_KERNEL_SPARSE;
     switch (kernel) {
-        case NMG_KERNEL_AUTO: {
-            // the most that aligned and merely element-aligned buffers lead to
-            int64_t b = 0;
-            for (const uintptr_t at : {(uintptr_t)0, (uintptr_t)elem_size(L->dtype)}) {
-                const uint8_t *p = reinterpret_cast<const uint8_t *>(at);
-                const nmg_kernel f = auto_family(L, kernel, p, p, p, N, N);
-                if (sp && sp_preferred(L, f, NMG_EPILOGUE_NONE, N))
-                    b = std::max(b, sp_stream_bytes(L->dtype, L->M, L->K, N));
-                else if (f == NMG_KERNEL_MFMA_EXPAND)
-                    b = std::max(b, expand_scratch_bytes(L));
-            }
-            return b;
-        }
         case NMG_KERNEL_MFMA_WIDE:
         case NMG_KERNEL_MFMA_SPLIT:
-            return (kernel == NMG_KERNEL_MFMA_SPLIT) == (L->dtype == NMG_F32)
-                       ? std::max<int64_t>(x16_prepared_bytes(L), 0) : 0;
-        case NMG_KERNEL_MFMA_EXPAND: return expand_supported(L, N) ? expand_scratch_bytes(L) : 0;
-        case NMG_KERNEL_SPARSE: return sp ? sp_stream_bytes(L->dtype, L->M, L->K, N) : 0;
-        default: return 0;
+            if ((kernel == NMG_KERNEL_MFMA_SPLIT) == (L->dtype == NMG_F32))
+                bytes = std::max<int64_t>(x16_prepared_bytes(L), 0);
+            break;
+        case NMG_KERNEL_MFMA_EXPAND:
+            if (expand_supported(L, ldx)) bytes = expand_scratch_bytes(L);
+            break;
+        case NMG_KERNEL_SPARSE:
+            if (sp) bytes = sp_stream_bytes(L->dtype, L->M, L->K, N);
+            break;
+        default: break;
     }
+    if (workspace_bytes) *workspace_bytes = bytes;
+    return kernel;
+}
+
+int64_t nmg_spmm_workspace_bytes(const nmg_layout *L, nmg_kernel kernel, int64_t N) {
+    // the most that aligned and merely element-aligned buffers lead to
+    int64_t most = 0;
+    for (const uintptr_t at : {(uintptr_t)0, (uintptr_t)2}) {
+        const uint8_t *p = reinterpret_cast<const uint8_t *>(at);
+        int64_t b = 0;
+        (void)nmg_spmm_plan(L, kernel, p, p, p, N, N, &b);
+        most = std::max(most, b);
+    }
+    return most;
 }
 
 nmg_status nmg_p_densify(const nmg_p_layout *L, const void *values, const uint8_t *index,

@@ -89,6 +89,8 @@ def _load():
         "nmg_spmm_epilogue_ws": ([lp, ctypes.c_int, ctypes.c_int, vp, vp, vp, i64, i64, vp, i64, vp,
                                   i64, vp, i64, vp], ctypes.c_int),
         "nmg_spmm_workspace_bytes": ([lp, ctypes.c_int, i64], i64),
+        "nmg_spmm_plan": ([lp, ctypes.c_int, vp, vp, vp, i64, i64, ctypes.POINTER(i64)],
+                          ctypes.c_int),
         "nmg_p_spmm_ws": ([pp, ctypes.c_int, vp, vp, vp, i64, i64, vp, i64, vp, i64, vp],
                           ctypes.c_int),
         "nmg_p_spmm_workspace_bytes": ([pp, ctypes.c_int, i64], i64),
@@ -148,7 +150,7 @@ class Layout:
         self.M, self.K, self.n, self.m, self.g, self.C = c.M, c.K, c.n, c.m, c.g, c.C
         self.values_shape = (self.M, self.C * self.n)
         self.indices_shape = (self.M // self.g, self.C * self.n)
-        self._ws = (None, 0)     # (kernel, N) of the last product and its workspace bytes
+        self._ws = (None, 0)     # what sized the last product's workspace, and its bytes
 
     def __getstate__(self):
         return {"c": self.c, "dtype": self.dtype}
@@ -211,12 +213,16 @@ def _workspace(nbytes: int, like: torch.Tensor):
     return ws, ws.data_ptr(), nbytes
 
 
-def _workspace_bytes(layout, code: int, N: int) -> int:
-    """nmg_spmm_workspace_bytes (a function of the layout, kernel and N)."""
+def _workspace_bytes(layout, code: int, vp: int, ip: int, xp: int, ldx: int, N: int) -> int:
+    """The workspace of nmg_spmm_plan: a function of the layout, kernel, sizes and
+    the pointers' alignment to 16 bytes."""
+    at = (code, N, ldx, vp & 15, ip & 15, xp & 15)
     key, nbytes = layout._ws
-    if key != (code, N):
-        nbytes = lib().nmg_spmm_workspace_bytes(layout.c, code, N)
-        layout._ws = ((code, N), nbytes)
+    if key != at:
+        out = ctypes.c_int64(0)
+        lib().nmg_spmm_plan(layout.c, code, vp, ip, xp, ldx, N, ctypes.byref(out))
+        nbytes = out.value
+        layout._ws = (at, nbytes)
     return nbytes
 
 
@@ -324,10 +330,10 @@ def spmm_into(layout: Layout, values, indices, X, Y, kernel: str = "auto"):
     _packed_ok(layout, values, indices)
     L = lib()
     N, code = X.shape[1], KERNELS[kernel]
-    ws, wp, wb = _workspace(_workspace_bytes(layout, code, N), X)
-    _check(L.nmg_spmm_epilogue_ws(layout.c, code, 0, values.data_ptr(), indices.data_ptr(),
-                                  X.data_ptr(), _rows(X, "X"), N, None, 0, Y.data_ptr(), _rows(Y, "Y"),
-                                  wp, wb, _stream(X)), "nmg_spmm")
+    vp, ip, xp, ldx = values.data_ptr(), indices.data_ptr(), X.data_ptr(), _rows(X, "X")
+    ws, wp, wb = _workspace(_workspace_bytes(layout, code, vp, ip, xp, ldx, N), X)
+    _check(L.nmg_spmm_epilogue_ws(layout.c, code, 0, vp, ip, xp, ldx, N, None, 0, Y.data_ptr(),
+                                  _rows(Y, "Y"), wp, wb, _stream(X)), "nmg_spmm")
 
 
 def spmm(values, indices, X, layout: Layout, kernel: str = "auto"):
@@ -379,17 +385,21 @@ def _spmm_epilogue(fn, values, indices, X, layout, epilogue, R, kernel, Y):
             raise ValueError("R must be M x N of the layout's dtype")
         rp, ldr = R.data_ptr(), _rows(R, "R")
     L = lib()
-    args = [layout.c, KERNELS[kernel], EPILOGUES[epilogue], values.data_ptr(),
-            indices.data_ptr(), X.data_ptr(), _rows(X, "X"), N, rp, ldr, Y.data_ptr(), _rows(Y, "Y")]
+    vp, ip, xp, ldx = values.data_ptr(), indices.data_ptr(), X.data_ptr(), _rows(X, "X")
+    args = [layout.c, KERNELS[kernel], EPILOGUES[epilogue], vp, ip, xp, ldx, N, rp, ldr,
+            Y.data_ptr(), _rows(Y, "Y")]
     if fn == "nmg_spmm_epilogue_ws":
-        ws, wp, wb = _workspace(_workspace_bytes(layout, args[1], N), X)
+        ws, wp, wb = _workspace(_workspace_bytes(layout, args[1], vp, ip, xp, ldx, N), X)
         args += [wp, wb]
     _check(getattr(L, fn)(*args, _stream(X)), fn)
     return Y
 
 
 def auto_kernel(layout: Layout, N: int) -> str:
-    return _KERNEL_NAME[lib().nmg_spmm_auto_kernel(layout.c, N)]
+    """The family spmm / spmm_into / spmm_epilogue run for "auto" on aligned,
+    contiguous operands (``nmg_spmm_plan``: they bring a workspace; the family
+    without one is ``nmg_spmm_auto_kernel``)."""
+    return _KERNEL_NAME[lib().nmg_spmm_plan(layout.c, KERNELS["auto"], None, None, None, N, N, None)]
 
 
 def densify(values, indices, layout: Layout):

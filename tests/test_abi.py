@@ -282,3 +282,23 @@ def test_gelu_table_rules(tmp_path):
     x = b.astype(np.uint16).view(np.float16)
     assert 3.0 < float(x[ident]) < 4.0 and -6.0 < float(x[negz]) < -5.0
     assert 2 * ident <= 36 * 1024 and 2 * (negz - 0x8000) <= 36 * 1024
+
+
+def test_plan_names_the_family_with_a_workspace(lib):
+    """nmg_spmm_plan: AUTO's family with a workspace, what that workspace is,
+    and only the call's own alignment counts."""
+    L, b = nmg._Layout(), ctypes.c_int64(0)
+    plan = lambda k, N, at=None, ldx=None: nmg._KERNEL_NAME[lib.nmg_spmm_plan(
+        ctypes.byref(L), nmg.KERNELS[k], at, at, at, ldx or N, N, ctypes.byref(b))]
+    assert lib.nmg_layout_init(ctypes.byref(L), 3072, 768, 1, 4, 8, nmg.F32) == nmg.OK
+    assert plan("auto", 4096) == "sparse"
+    assert b.value == lib.nmg_spmm_workspace_bytes(ctypes.byref(L), nmg.KERNELS["sparse"], 4096) > 0
+    assert plan("mfma_scalar", 4096) == "mfma_scalar" and b.value == 0
+    # binary16 on aligned buffers keeps its kernel and needs no workspace;
+    # misaligned X takes the sparse instructions, and workspace_bytes covers both
+    assert lib.nmg_layout_init(ctypes.byref(L), 3072, 768, 2, 8, 8, nmg.F16) == nmg.OK
+    assert plan("auto", 1024) == "mfma_f16" and b.value == 0
+    assert plan("auto", 1024, 2) == "sparse"
+    assert b.value == lib.nmg_spmm_workspace_bytes(ctypes.byref(L), nmg.KERNELS["auto"], 1024) > 0
+    assert plan("auto", 1024, None, 1027) == "sparse" and b.value > 0
+    assert plan("auto", 1024, None, 1000) == "auto" and b.value == 0     # ldx < N

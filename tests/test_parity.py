@@ -1205,3 +1205,35 @@ def test_sparse_product_any_range(nmg, K, exp):
         for name, keff, product, mask, Wd in packed_kinds(nmg, A, (1, 8, 1), (1, 4, 16)):
             worst[what, name] = check_kept_only(product, Z, keff, mask, Wd, torch.float32, f"{what} {name}")
     print("[any range]", exp, {k: f"{v:.1e}" for k, v in worst.items()}, flush=True)
+
+
+# ---------------------------------------------------- the family AUTO takes
+
+NAMED = [
+    (3072, 768, 4096, 1, 4, 8, torch.float32), (3072, 768, 512, 2, 4, 1, torch.float32),
+    (768, 768, 128, 2, 4, 4, torch.float32), (768, 3072, 300, 1, 10, 16, torch.float32),
+    (3072, 768, 4096, 2, 4, 8, torch.float16), (3072, 768, 512, 2, 4, 8, torch.float16),
+    (64, 96, 30, 1, 3, 2, torch.float16), (96, 64, 33, 3, 5, 3, torch.float32),
+]
+
+
+@pytest.mark.parametrize("M,K,N,n,m,g,dtype", NAMED)
+def test_auto_kernel_names_what_runs(nmg, M, K, N, n, m, g, dtype):
+    """nmg.auto_kernel is the family nmg.spmm runs: the same bits as that family
+    by name.  X in wider or misaligned rows, where AUTO's choice may differ:
+    the family nmg_spmm_plan names for them."""
+    W = synth.normal((M, K), 1011, 0.02, dtype).to(DEV)
+    X = synth.normal((K, N), 1012, 1.0, dtype).to(DEV)
+    v, idx, L = nmg.compress(W, n, m, g)
+    flat = torch.zeros(K * (N + 5) + 1, dtype=dtype, device=DEV)
+    wide = flat[:-1].view(K, N + 5)[:, :N]
+    off = flat[1:].view(K, N + 5)[:, :N]
+    for what, Z in (("contiguous", X), ("wider rows", wide), ("misaligned", off)):
+        Z.copy_(X)
+        name = nmg._KERNEL_NAME[nmg.lib().nmg_spmm_plan(L.c, 0, v.data_ptr(), idx.data_ptr(), Z.data_ptr(),
+                                                        Z.stride(0), N, None)]
+        Y, Yk = nmg.spmm(v, idx, Z, L), nmg.spmm(v, idx, Z, L, name)
+        torch.cuda.synchronize()
+        print("[auto]", L, N, what, name, flush=True)
+        assert what != "contiguous" or name == nmg.auto_kernel(L, N)
+        assert torch.equal(Y.view(torch.uint8), Yk.view(torch.uint8)), (what, name)
