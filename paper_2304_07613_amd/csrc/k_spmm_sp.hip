@@ -1274,43 +1274,76 @@ bool nmg_internal::sp_layout_supported(const nmg_layout *L) {
 }
 
 // AUTO's rule, over its choice without a workspace (us a call, that choice /
-// this one; 3072 x 768 unless said otherwise):
+// this one, through the binding).  Its own cost is two launches, the weight
+// stream (about 1.25 us per 10^6 entries of W, a third more for n = 1) and half
+// of K's columns whatever is kept; theirs is launch plus kept columns, so it
+// loses where few are kept, and on small products:
 //  - Binary32 needs 64 kept columns a row: below that a chain of multiply-adds
 //    rounds as rarely as this product does (1:20 of 768 columns: error 1.14e-7
 //    against 1.22e-7; 1:10: 1.58e-7 against 1.45e-7).
-//  - The expanded product and the vector kernels lose everywhere: 2:4:1
-//    79 / 23 at one token, 188 / 56 at 4096 (177 with its scratch allocation
-//    amortised), 768 x 3072 262 / 55 and 286 / 72; 1:10:1 135 / 23 and 162 / 53.
+//  - The expanded product and the staged vector kernel lose everywhere (2:4:1 at
+//    3072 x 768: 79 / 23 at one token, 188 / 56 at 4096; 768 x 3072 262 / 55
+//    and 286 / 72; 1:10:1 135 / 23 and 162 / 53; 1:32:1 at 4096 x 4096 by 1.5
+//    to 9 times).
+//  - The vector kernel: binary32 everywhere (1:128:1 at 1024 x 8192 3.4 times at
+//    512 tokens, 170 / 178 at 4096), binary16 down to one column in 32; beyond,
+//    a row's chain costs it 1 us a kept column (2 for groups of one row, whose
+//    indices no other row shares), which has to make up for the stream: 1:64:1
+//    30 / 13 at 768 x 768, 1:64:8 17 / 22 and 1:128:8 10 / 22 at 8192 x 1024,
+//    31 / 31 at 4096 x 4096, 1:255:8 15 / 27 at 768 x 3072.
 //  - mfma_scalar, binary32: its X goes through registers when the tokens do
-//    not fill its tiles (1:4:8 at 1021 tokens 44 / 34); at half density it
-//    loses at every size it is chosen for (2:4:8 31 / 25 at 512 tokens,
-//    104 / 56 at 4096); else from about 10^9 kept products (1:4:8 19 / 27 at
-//    512 tokens, 36 / 34 at 2048, 60 / 56 at 4096).  Binary16 goes there only
-//    for token counts off 8: 2:8:8 31 / 15 at one token, 55 / 26 at 1021.
+//    not fill its tiles (1:4:8 at 1021 tokens 44 / 34; 1:8:8 30 / 28 at 1000,
+//    21 / 31 at 17, 8192 x 1024); at half density it loses but for one tile of
+//    64 tokens (2:4:8 31 / 25 at 512, 104 / 56 at 4096; 2:4:32 at 64 tokens of
+//    8192 x 1024 25 / 28); at a quarter from about 10^9 kept products (1:4:8
+//    19 / 27 at 512 tokens, 36 / 34 at 2048, 60 / 56 at 4096) where there are
+//    tokens enough for the stream of many rows (8192 x 1024 1:4:8 59 / 64 at
+//    1024, 190 / 182 at 4096, 1:4:32 89 / 98 at 2048); below a quarter it wins
+//    (1:8:8 39 / 52 at 4096, 8192 x 1024 121 / 172).  Binary16 goes there only
+//    for token counts off 8: 2:8:8 31 / 15 at one token, 55 / 26 at 1021, not
+//    for a few columns (64 x 256, 1:8: 9 / 12).
 //  - mfma_direct keeps its layouts (few kept columns, few rows or tokens),
 //    where its partial sums also round less, but for half density from 2048
 //    columns: 768 x 3072 2:4:4 40 / 19 at 16 tokens, 113 / 40 at 1021, 2:4:16
-//    28 / 19 and 74 / 41, errors 1.9e-7 to 2.6e-7 / 1.3e-7 to 2.0e-7.
-//  - The binary16 kernels with the epilogue folded in: smfmac from 3 10^9
-//    expanded products (2:4:1 11 / 16 at 512 tokens, 30 / 21 at 2048) or 2048
-//    columns (768 x 3072 50 / 15 at 16 tokens), mfma_f16 at half density from
-//    4 10^9 (2:4:8 13 / 16 at 512 tokens, 35 / 21 at 2048; 1:4:8 27 / 35 at
-//    4096) or 2048 columns (768 x 3072 2:4:8 29 / 16 at 16 tokens, 31 / 26 at
-//    1024; 2:4:16 24 / 21 at 512, 25 / 26 at 1024); GELU stays with them.
+//    28 / 19 and 74 / 41, errors 1.9e-7 to 2.6e-7 / 1.3e-7 to 2.0e-7; with many
+//    rows only for groups of 4 (4096 x 4096 2:4:4 91 / 70, 2:4:32 55 / 70).
+//  - smfmac, whose columns are one chain: from 3 10^9 expanded products in 1000
+//    tokens or more (2:4:1 30 / 20 at 2048, 11 / 16 at 512; 8192 x 1024 1:4:1
+//    52 / 46 at 1000, 24 / 36 at 512), or 2048 columns (768 x 3072 50 / 15 at 16
+//    tokens), with many rows at few tokens only (4096 x 4096 2:4:1 38 / 29 at 8,
+//    43 / 47 at 512, 1:4:1 38 / 49 at 8).
+//  - mfma_f16 at half density: 2:4 from 4 10^9 (2:4:8 13 / 16 at 512 tokens,
+//    35 / 20 at 2048) or 2048 columns (768 x 3072 2:4:8 29 / 16 at 16 tokens,
+//    2:4:32 25 / 26 at 1024); 1:2, whose stream takes longer, likewise but for
+//    large groups (1:2:32 16 / 21 at 1000 tokens; 8192 x 1024 38 / 40) and many
+//    rows at few tokens (4096 x 4096 1:2:8 37 / 38 at 8, 55 / 58 at 512).
+//  GELU stays with the binary16 kernels that fold it in.
 bool nmg_internal::sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epilogue epi, int64_t N) {
-    const double kept = (double)L->M * L->C * L->n * (double)N, dense = (double)L->M * L->K * (double)N;
-    const bool f32 = L->dtype == NMG_F32, half = 2 * L->n >= L->m;
-    if (f32 && (int64_t)L->C * L->n < 64) return false;
+    const int64_t M = L->M, K = L->K, n = L->n, m = L->m, g = L->g, slots = (int64_t)L->C * n;
+    const double kept = (double)M * slots * (double)N, dense = (double)M * K * (double)N;
+    const bool f32 = L->dtype == NMG_F32, half = 2 * n >= m, quarter = 4 * n >= m;
+    if (f32 && slots < 64) return false;
     switch (family) {
         case NMG_KERNEL_MFMA_EXPAND:
-        case NMG_KERNEL_VALU_STAGED:
-        case NMG_KERNEL_VALU: return true;
-        case NMG_KERNEL_MFMA_DIRECT: return f32 && half && L->K >= 2048;
-        case NMG_KERNEL_MFMA_SCALAR: return !f32 || half || N % 64 != 0 || kept >= 1e9;
-        case NMG_KERNEL_SMFMAC_F16: return epi != NMG_EPILOGUE_GELU && (dense >= 3e9 || L->K >= 2048);
+        case NMG_KERNEL_VALU_STAGED: return true;
+        case NMG_KERNEL_VALU:
+            return f32 || m <= 32 * n ||
+                   ((g == 1 || m <= 128 * n) && (double)slots * (g == 1 ? 2 : 1) >= 6 + 1.25e-6 * (double)M * K);
+        case NMG_KERNEL_MFMA_DIRECT: return f32 && half && K >= 2048 && (M <= 2048 || g <= 4);
+        case NMG_KERNEL_MFMA_SCALAR:
+            if (!f32) return half || K >= 512;
+            if (half) return N != 64 || g <= 8;
+            if (N % 64 != 0) return quarter ? N >= 64 || g <= 8 : N >= 512;
+            return quarter && kept >= 1e9 && (g <= 4 || M <= (g <= 8 ? 4 : 2) * N);
+        case NMG_KERNEL_SMFMAC_F16:
+            return epi != NMG_EPILOGUE_GELU &&
+                   ((dense >= 3e9 && N >= 1000) ||
+                    (K >= 2048 && (M <= 2048 || (N <= 256 && (n == 2 || m >= 8)))));
         case NMG_KERNEL_MFMA_F16:
-            return epi != NMG_EPILOGUE_GELU && half &&
-                   (dense >= 4e9 || (L->K >= 2048 && (L->g <= 8 || N <= 512)));
+            if (epi == NMG_EPILOGUE_GELU || !half) return false;
+            if (n == 2) return dense >= 4e9 || (K >= 2048 && (g <= 8 || N <= 512));
+            return (dense >= 4e9 && N >= 1000 && (g <= 8 || K >= 2048 || dense >= 1.2e10)) ||
+                   (K >= 2048 && (M <= 2048 || g <= 4) && (g <= 8 || N <= 512));
         default: return false;
     }
 }

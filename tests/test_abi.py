@@ -302,3 +302,32 @@ def test_plan_names_the_family_with_a_workspace(lib):
     assert b.value == lib.nmg_spmm_workspace_bytes(ctypes.byref(L), nmg.KERNELS["auto"], 1024) > 0
     assert plan("auto", 1024, None, 1027) == "sparse" and b.value > 0
     assert plan("auto", 1024, None, 1000) == "auto" and b.value == 0     # ldx < N
+
+
+def test_plan_keeps_layouts_the_sparse_product_is_slower_for(lib):
+    """The sparse product counts half of K's columns whatever is kept and reads
+    the whole weight stream: AUTO keeps the family it takes without a workspace
+    where few columns are kept, or few products, and takes it just beside."""
+    L = nmg._Layout()
+    for M, K, n, m, g, dt, N, family in (
+            (8192, 1024, 1, 255, 8, nmg.F16, 64, "valu"),        # 8 us against 21
+            (8192, 1024, 1, 128, 8, nmg.F16, 1, "valu"),         # 10 / 22
+            (4096, 4096, 1, 255, 32, nmg.F16, 512, "valu"),      # 18 / 46
+            (3072, 768, 1, 128, 1, nmg.F16, 64, "sparse"),       # 19 / 13
+            (4096, 4096, 1, 64, 8, nmg.F16, 1, "sparse"),        # 58 / 31
+            (64, 256, 1, 16, 8, nmg.F16, 17, "mfma_scalar"),     # 9 / 18
+            (768, 768, 1, 16, 8, nmg.F16, 17, "sparse"),         # 22 / 13
+            (3072, 768, 1, 8, 8, nmg.F32, 4096, "mfma_scalar"),  # 39 / 52
+            (8192, 1024, 1, 8, 8, nmg.F32, 17, "mfma_scalar"),   # 21 / 31
+            (3072, 768, 1, 8, 8, nmg.F32, 1000, "sparse"),       # 30 / 28
+            (4096, 4096, 1, 4, 32, nmg.F32, 512, "mfma_scalar"), # 76 / 94
+            (4096, 4096, 1, 4, 8, nmg.F32, 1024, "sparse"),      # 129 / 108
+            (4096, 4096, 2, 4, 32, nmg.F32, 128, "mfma_direct"), # 56 / 73
+            (1024, 8192, 2, 4, 32, nmg.F32, 128, "sparse"),      # 69 / 49
+            (4096, 4096, 1, 4, 1, nmg.F16, 512, "smfmac_f16"),   # 41 / 68
+            (4096, 4096, 1, 4, 1, nmg.F16, 1024, "sparse"),      # 77 / 71
+            (4096, 4096, 1, 2, 32, nmg.F16, 64, "mfma_f16"),     # 31 / 39
+            (1024, 8192, 1, 2, 32, nmg.F16, 64, "sparse")):      # 57 / 32
+        assert lib.nmg_layout_init(ctypes.byref(L), M, K, n, m, g, dt) == nmg.OK
+        got = lib.nmg_spmm_plan(ctypes.byref(L), 0, None, None, None, N, N, None)
+        assert nmg._KERNEL_NAME[got] == family, (M, K, n, m, g, dt, N, nmg._KERNEL_NAME[got])
