@@ -332,7 +332,7 @@ nmg_status nmg_internal::spmm_epilogue_ws(const nmg_layout *L, nmg_kernel kernel
         // memory anyway (never from the shared array of the allocation-free
         // entry point for a call that used none)
         if (requested == NMG_KERNEL_AUTO && sp_layout_supported(L) &&
-            sp_args_supported(L->dtype, L->M, L->K, ldx, N) && sp_preferred(L, kernel, epi, N)) {
+            sp_args_supported(L->dtype, L->M, L->K, ldx, N) && sp_preferred(L, kernel, N)) {
             const int64_t need = sp_stream_bytes(L->dtype, L->M, L->K, N);
             const bool own = scratch.workspace && need <= scratch.workspace_bytes;
             const bool instead = kernel == NMG_KERNEL_MFMA_EXPAND &&
@@ -525,7 +525,7 @@ nmg_kernel nmg_spmm_plan(const nmg_layout *L, nmg_kernel kernel, const void *val
     const nmg_kernel requested = kernel;
     if (kernel == NMG_KERNEL_AUTO || kernel == NMG_KERNEL_MFMA)
         kernel = auto_family(L, kernel, values, indices, X, ldx, N);
-    if (requested == NMG_KERNEL_AUTO && sp && sp_preferred(L, kernel, NMG_EPILOGUE_NONE, N))
+    if (requested == NMG_KERNEL_AUTO && sp && sp_preferred(L, kernel, N))
         kernel = NMG_KERNEL_SPARSE;
     switch (kernel) {
         case NMG_KERNEL_MFMA_WIDE:

@@ -174,7 +174,7 @@ bool sp_p_layout_supported(const nmg_p_layout *L);
 bool sp_args_supported(nmg_dtype dtype, int64_t M, int64_t K, int64_t ldx, int64_t N);
 int64_t sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int64_t N, int chunk_m = 0);
 // whether AUTO takes it in place of `family` (its choice without workspace)
-bool sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epilogue epi, int64_t N);
+bool sp_preferred(const nmg_layout *L, nmg_kernel family, int64_t N);
 bool sp_p_preferred(const nmg_p_layout *L, int64_t N);
 nmg_status spmm_sp(const SpmmArgs &a, void *ws);
 nmg_status p_spmm_sp(const nmg_p_layout *L, const void *values, const uint8_t *index, const void *X,

@@ -1317,8 +1317,12 @@ bool nmg_internal::sp_layout_supported(const nmg_layout *L) {
 //    2:4:32 25 / 26 at 1024); 1:2, whose stream takes longer, likewise but for
 //    large groups (1:2:32 16 / 21 at 1000 tokens; 8192 x 1024 38 / 40) and many
 //    rows at few tokens (4096 x 4096 1:2:8 37 / 38 at 8, 55 / 58 at 512).
-//  GELU stays with the binary16 kernels that fold it in.
-bool nmg_internal::sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epilogue epi, int64_t N) {
+//  The choice is the same for every epilogue, so that an epilogue gives the bits
+//  of the product followed by it; GELU, which the binary16 kernels fold in and
+//  this one takes as a pass of its own, still gains (3072 x 768 2:4:8 38 / 29
+//  at 2048 tokens, 45 / 42 at 4096; 768 x 3072 34 / 19 at 64; at worst 1:2:32
+//  768 x 3072 38 / 40 at 2048).
+bool nmg_internal::sp_preferred(const nmg_layout *L, nmg_kernel family, int64_t N) {
     const int64_t M = L->M, K = L->K, n = L->n, m = L->m, g = L->g, slots = (int64_t)L->C * n;
     const double kept = (double)M * slots * (double)N, dense = (double)M * K * (double)N;
     const bool f32 = L->dtype == NMG_F32, half = 2 * n >= m, quarter = 4 * n >= m;
@@ -1336,11 +1340,10 @@ bool nmg_internal::sp_preferred(const nmg_layout *L, nmg_kernel family, nmg_epil
             if (N % 64 != 0) return quarter ? N >= 64 || g <= 8 : N >= 512;
             return quarter && kept >= 1e9 && (g <= 4 || M <= (g <= 8 ? 4 : 2) * N);
         case NMG_KERNEL_SMFMAC_F16:
-            return epi != NMG_EPILOGUE_GELU &&
-                   ((dense >= 3e9 && N >= 1000) ||
-                    (K >= 2048 && (M <= 2048 || (N <= 256 && (n == 2 || m >= 8)))));
+            return (dense >= 3e9 && N >= 1000) ||
+                   (K >= 2048 && (M <= 2048 || (N <= 256 && (n == 2 || m >= 8))));
         case NMG_KERNEL_MFMA_F16:
-            if (epi == NMG_EPILOGUE_GELU || !half) return false;
+            if (!half) return false;
             if (n == 2) return dense >= 4e9 || (K >= 2048 && (g <= 8 || N <= 512));
             return (dense >= 4e9 && N >= 1000 && (g <= 8 || K >= 2048 || dense >= 1.2e10)) ||
                    (K >= 2048 && (M <= 2048 || g <= 4) && (g <= 8 || N <= 512));

@@ -1237,3 +1237,27 @@ def test_auto_kernel_names_what_runs(nmg, M, K, N, n, m, g, dtype):
         print("[auto]", L, N, what, name, flush=True)
         assert what != "contiguous" or name == nmg.auto_kernel(L, N)
         assert torch.equal(Y.view(torch.uint8), Yk.view(torch.uint8)), (what, name)
+
+
+AUTO_EPILOGUE = [
+    (3072, 768, 4096, 2, 4, 8, torch.float16), (3072, 768, 2048, 2, 4, 1, torch.float16),
+    (768, 3072, 512, 2, 4, 16, torch.float16), (768, 3072, 16, 2, 8, 1, torch.float16),
+    (768, 3072, 200, 2, 4, 1, torch.float32), (3072, 768, 1021, 2, 8, 8, torch.float16),
+]
+
+
+@pytest.mark.parametrize("M,K,N,n,m,g,dtype", AUTO_EPILOGUE)
+def test_auto_epilogue_equals_composition(nmg, M, K, N, n, m, g, dtype):
+    """AUTO through the binding where its choice goes to the sparse matrix
+    instructions: the epilogues give the bits of the product followed by
+    nmg_gelu / nmg_add."""
+    W = synth.normal((M, K), 71 + M, 0.02, dtype).to(DEV)
+    X = synth.normal((K, N), 72 + N, 1.0, dtype).to(DEV)
+    R = synth.normal((M, N), 73 + N, 1.0, dtype).to(DEV)
+    v, idx, L = nmg.compress(W, n, m, g)
+    P = nmg.spmm(v, idx, X, L)
+    Yg = nmg.spmm_epilogue(v, idx, X, L, "gelu")
+    Ya = nmg.spmm_epilogue(v, idx, X, L, "add", R)
+    torch.cuda.synchronize()
+    assert torch.equal(Ya.view(torch.uint8), nmg.add(P, R).view(torch.uint8))
+    assert torch.equal(Yg.view(torch.uint8), nmg.gelu(P).view(torch.uint8))
