@@ -221,7 +221,8 @@ nmg_status nmg_repack(const nmg_layout *layout, const void *W, int64_t ldw,
  * writes them; other contents are not detected and give unspecified Y (the
  * kernels still never read outside X's K rows).  Uses NMG_KERNEL_AUTO, which
  * takes NMG_KERNEL_SPARSE or, for layouts that kernel refuses or that keep
- * fewer than 64 columns a row, NMG_KERNEL_MFMA_EXPAND (both scratch memory in
+ * fewer than 64 columns a row (or whose stream passes 16 MiB where the dense
+ * weight does not), NMG_KERNEL_MFMA_EXPAND (both scratch memory in
  * stream order; the latter with a dense product's treatment of non-finite X)
  * for binary32 layouts the grouped matrix-core kernels cannot take when
  * m <= 8 n. */

@@ -188,7 +188,7 @@ nmg_status nmg_spmm_epilogue_ws(const nmg_layout *L, nmg_kernel kernel, nmg_epil
     if (workspace_bytes < 0) return NMG_ERR_PARAM;
     if (workspace && !aligned(workspace, 256)) return NMG_ERR_ALIGN;
     return spmm_epilogue_ws(L, kernel, epi, values, indices, X, ldx, N, R, ldr, Y, ldy, stream,
-                            Scratch{nullptr, workspace, workspace ? workspace_bytes : 0, 0});
+                            Scratch{nullptr, workspace, workspace ? workspace_bytes : 0});
 }
 
 }  // extern "C"
@@ -330,13 +330,15 @@ nmg_status nmg_internal::spmm_epilogue_ws(const nmg_layout *L, nmg_kernel kernel
         // the sparse matrix instructions where their scratch memory is at
         // hand: in the caller's workspace, or where the choice has scratch
         // memory anyway (never from the shared array of the allocation-free
-        // entry point for a call that used none)
+        // entry point for a call that used none).  The entry points without a
+        // workspace take the same family wherever the scratch comes from: the
+        // expanded product where only its scratch fits the shared array.
         if (requested == NMG_KERNEL_AUTO && sp_layout_supported(L) &&
             sp_args_supported(L->dtype, L->M, L->K, ldx, N) && sp_preferred(L, kernel, N)) {
             const int64_t need = sp_stream_bytes(L->dtype, L->M, L->K, N);
             const bool own = scratch.workspace && need <= scratch.workspace_bytes;
             const bool instead = kernel == NMG_KERNEL_MFMA_EXPAND &&
-                                 (!scratch.source || need <= scratch.source_bytes);
+                                 (need <= kFixedScratchBytes || expand_scratch_bytes(L) > kFixedScratchBytes);
             if (own || instead) kernel = NMG_KERNEL_SPARSE;
         }
     }

@@ -26,13 +26,12 @@ using namespace nmg_internal;
 
 namespace {
 
-constexpr int64_t kScratchBytes = (int64_t)16 << 20;  // 16 MiB per GPU
 constexpr int kMaxDevices = 64;
 
 // Device-side storage; host code never passes this name to a kernel or a
 // copy (on the host it only names the symbol): the address of each GPU's
 // copy comes from hipGetSymbolAddress with that GPU current.
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kFixedScratchBytes];
 
 std::mutex scratch_lock;
 std::atomic<void *> scratch_ptr[kMaxDevices];
@@ -58,7 +57,7 @@ void *scratch_address(int device) {
 // (after checking that the work's stream is on that device), or
 // NMG_ERR_CAPACITY before any runtime call when the request exceeds it.
 void *fixed_scratch(int64_t bytes, hipStream_t stream, nmg_status *st) {
-    if (bytes > kScratchBytes) {
+    if (bytes > kFixedScratchBytes) {
         *st = NMG_ERR_CAPACITY;
         return nullptr;
     }
@@ -91,5 +90,5 @@ nmg_status nmg_spmm_epilogue_noalloc(const nmg_layout *L, nmg_kernel kernel, nmg
                                      int64_t ldx, int64_t N, const void *R, int64_t ldr, void *Y,
                                      int64_t ldy, hipStream_t stream) {
     return spmm_epilogue_ws(L, kernel, epi, values, indices, X, ldx, N, R, ldr, Y, ldy, stream,
-                            Scratch{fixed_scratch, nullptr, 0, kScratchBytes});
+                            Scratch{fixed_scratch, nullptr, 0});
 }

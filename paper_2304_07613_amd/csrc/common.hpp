@@ -133,8 +133,8 @@ struct Scratch {
     scratch_source source = nullptr;  // else a stream-ordered allocation
     void *workspace = nullptr;        // the caller's, taken first when it is large enough
     int64_t workspace_bytes = 0;
-    int64_t source_bytes = 0;         // what `source` can give
 };
+constexpr int64_t kFixedScratchBytes = (int64_t)16 << 20;   // of the allocation-free entry point, per GPU
 // nmg_spmm_epilogue; the families with scratch memory (the 16 x 16 x 32
 // products' prepared operands, the expanded weight, the weight stream) take
 // it from `scratch`

@@ -112,3 +112,21 @@ def test_noalloc_capacity(nmg):
     torch.cuda.synchronize()
     assert same_bits(a, b)
     assert np.isfinite(a.float().cpu().numpy()).all()
+
+
+def test_noalloc_equals_allocating_past_capacity(nmg):
+    """The sparse product's scratch memory grows with the tokens: where it
+    passes the fixed array, and the expanded weight does not, both entry points
+    still take the same family."""
+    M, K, N = 16, 128, 2_300_000
+    W = synth.normal((M, K), 1001, 0.02).to(DEV)
+    X = torch.randn((K, N), device=DEV, generator=torch.Generator(device=DEV).manual_seed(1))
+    v, idx, L = nmg.compress(W, 2, 4, 1)
+    Y = torch.empty((M, N), device=DEV)
+    lib = nmg.lib()
+    st = lib.nmg_spmm_epilogue(L.c, 0, 0, v.data_ptr(), idx.data_ptr(), X.data_ptr(), N, N, None, 0,
+                               Y.data_ptr(), N, nmg._stream(X))
+    assert st == nmg.OK
+    Yn = nmg.spmm_epilogue_noalloc(v, idx, X, L)
+    torch.cuda.synchronize()
+    assert torch.equal(Y.view(torch.int32), Yn.view(torch.int32))
