@@ -1260,11 +1260,13 @@ int64_t nmg_internal::sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int
            (f32 ? 4 * (16 * sp_tiles(M) + N + sp_xparts(K) * N) : 0);
 }
 
+// 32-bit offsets along a row of X; every launch below 2^32 threads (HIP refuses
+// more): both preparations and the product at one row tile a wave
 bool nmg_internal::sp_args_supported(nmg_dtype dtype, int64_t M, int64_t K, int64_t ldx, int64_t N) {
-    const int64_t es = (int64_t)elem_size(dtype), lim = (int64_t)1 << 31;
-    return ldx * es < lim && sp_tiles(M) * sp_steps(K, 1) < lim &&
-           sp_tiles(M) * ((K + 511) / 512) + (N + 63) / 64 * sp_xparts(K) < lim &&
-           ((M + 31) / 32) * ((N + kSpTok - 1) / kSpTok) < lim;
+    const int64_t es = (int64_t)elem_size(dtype), threads = (int64_t)1 << 32;
+    const int64_t prep = sp_tiles(M) * ((K + 511) / 512) + (N + 63) / 64 * sp_xparts(K);
+    return ldx * es < (int64_t)1 << 31 && sp_tiles(M) * sp_steps(K, 1) * 64 < threads &&
+           prep * kSpPrep < threads && (M + 63) / 64 * ((N + kSpTok - 1) / kSpTok) * kSpThreads < threads;
 }
 
 // at most 2 kept of every aligned 4 columns: one of m >= 2 (a chunk ends

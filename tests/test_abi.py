@@ -331,3 +331,16 @@ def test_plan_keeps_layouts_the_sparse_product_is_slower_for(lib):
         assert lib.nmg_layout_init(ctypes.byref(L), M, K, n, m, g, dt) == nmg.OK
         got = lib.nmg_spmm_plan(ctypes.byref(L), 0, None, None, None, N, N, None)
         assert nmg._KERNEL_NAME[got] == family, (M, K, n, m, g, dt, N, nmg._KERNEL_NAME[got])
+
+
+def test_plan_stays_below_the_launch_limit(lib):
+    """Products whose preparation or grid would pass 2^32 threads, which HIP does
+    not launch, keep the family without a workspace."""
+    L, b = nmg._Layout(), ctypes.c_int64(0)
+    for M, K, N, dt, fits in ((1 << 18, 1 << 17, 64, nmg.F16, True), (1 << 18, 1 << 18, 64, nmg.F16, False),
+                              (1 << 20, 256, 1 << 14, nmg.F16, True), (1 << 20, 256, 1 << 17, nmg.F16, False),
+                              (64, 256, 1 << 27, nmg.F32, True), (64, 256, 1 << 28, nmg.F32, False)):
+        assert lib.nmg_layout_init(ctypes.byref(L), M, K, 2, 4, 1, dt) == nmg.OK
+        for k in ("sparse", "auto"):
+            got = lib.nmg_spmm_plan(ctypes.byref(L), nmg.KERNELS[k], 2, 2, 2, N, N, ctypes.byref(b))
+            assert (b.value > 0 and nmg._KERNEL_NAME[got] == "sparse") == fits, (M, K, N, k)
