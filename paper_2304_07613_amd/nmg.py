@@ -152,11 +152,8 @@ class Layout:
         self.indices_shape = (self.M // self.g, self.C * self.n)
         self._ws = (None, 0)     # what sized the last product's workspace, and its bytes
 
-    def __getstate__(self):
-        return {"c": self.c, "dtype": self.dtype}
-
-    def __setstate__(self, state):
-        self.c, self.dtype = state["c"], state["dtype"]
+    def __setstate__(self, state):     # (also states of c and dtype alone)
+        self.__dict__.update(state)
         self._derive()
 
     def __repr__(self):
@@ -452,11 +449,8 @@ class PLayout:
         self.values_shape = (self.M, self.B * self.n)
         self.index_shape = (self.M, self.B)
 
-    def __getstate__(self):
-        return {"c": self.c, "dtype": self.dtype}
-
-    def __setstate__(self, state):
-        self.c, self.dtype = state["c"], state["dtype"]
+    def __setstate__(self, state):     # (also states of c and dtype alone)
+        self.__dict__.update(state)
         self._derive()
 
 

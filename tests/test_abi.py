@@ -1,7 +1,9 @@
 """The C ABI without a GPU: the library loads, exports every function
 ``include/nmg.h`` declares, and validates arguments on the host (no call here
 reaches a kernel launch)."""
+import copy
 import ctypes
+import pickle
 
 import pytest
 import torch
@@ -344,3 +346,15 @@ def test_plan_stays_below_the_launch_limit(lib):
         for k in ("sparse", "auto"):
             got = lib.nmg_spmm_plan(ctypes.byref(L), nmg.KERNELS[k], 2, 2, 2, N, N, ctypes.byref(b))
             assert (b.value > 0 and nmg._KERNEL_NAME[got] == "sparse") == fits, (M, K, N, k)
+
+
+def test_layout_state(lib):
+    """A layout keeps its caller's attributes through copy and pickle."""
+    for L in (nmg.Layout(64, 64, 2, 4, 8), nmg.PLayout(96, 64, 2, 4, 8)):
+        L.name = "ffn"
+        for c in (copy.copy(L), copy.deepcopy(L), pickle.loads(pickle.dumps(L))):
+            assert c.name == "ffn" and c.M == L.M and c.values_shape == L.values_shape
+            assert c.c.K == L.c.K
+        old = L.__class__.__new__(L.__class__)
+        old.__setstate__({"c": L.c, "dtype": L.dtype})      # an earlier version's state
+        assert old.M == L.M and old.values_shape == L.values_shape
