@@ -1042,14 +1042,20 @@ def test_sparse_product_non_finite(nmg, dtype, K):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("M,K,N,n,m,g", [(6, 4, 1, 2, 4, 1), (30, 68, 3, 2, 4, 5), (96, 132, 129, 2, 4, 16),
                                          (192, 1000, 260, 2, 4, 32), (28, 72, 70, 2, 8, 1), (240, 64, 33, 1, 16, 15),
-                                         (512, 776, 131, 1, 8, 32), (96, 2176, 130, 2, 4, 4)])
+                                         (512, 776, 131, 1, 8, 32), (96, 2176, 130, 2, 4, 4),
+                                         # 64 kept columns and more, which binary32 needs
+                                         (30, 132, 3, 2, 4, 5), (28, 264, 70, 2, 8, 1), (240, 1040, 33, 1, 16, 15),
+                                         (222, 260, 129, 2, 4, 1), (120, 2192, 1, 1, 16, 1)])
 def test_chunked_sparse_product(nmg, M, K, N, n, m, g, dtype):
     """The chunked layout on the sparse matrix instructions (AUTO through the
-    binding, which brings a workspace): chunks that share 16-row tiles, rows
-    past M in the last tile, block columns past the last step."""
+    binding, which brings a workspace; binary32 below 64 kept columns goes
+    elsewhere): chunks that share 16-row tiles, several workgroups of chunks,
+    rows past M in the last tile, block columns past the last step."""
     W = synth.normal((M, K), 931 + M, 0.02, dtype)
     X = synth.normal((K, N), 932 + N, 1.0, dtype)
     v, idx, L = nmg.p_compress(W.to(DEV), n, m, g)
+    takes = nmg.lib().nmg_p_spmm_workspace_bytes(L.c, 0, N) > 0
+    assert takes == (dtype == torch.float16 or L.B * n >= 64)
     Y = nmg.p_spmm(v, idx, X.to(DEV), L)
     Yv = nmg.p_spmm(v, idx, X.to(DEV), L, "valu")
     torch.cuda.synchronize()
