@@ -1045,7 +1045,7 @@ def test_sparse_product_non_finite(nmg, dtype, K):
                                          (512, 776, 131, 1, 8, 32), (96, 2176, 130, 2, 4, 4),
                                          # 64 kept columns and more, which binary32 needs
                                          (30, 132, 3, 2, 4, 5), (28, 264, 70, 2, 8, 1), (240, 1040, 33, 1, 16, 15),
-                                         (222, 260, 129, 2, 4, 1), (120, 2192, 1, 1, 16, 1)])
+                                         (222, 260, 129, 2, 4, 1), (112, 2192, 1, 1, 16, 1)])
 def test_chunked_sparse_product(nmg, M, K, N, n, m, g, dtype):
     """The chunked layout on the sparse matrix instructions (AUTO through the
     binding, which brings a workspace; binary32 below 64 kept columns goes
