@@ -1,7 +1,7 @@
 // k_spmm_sp.hip -- Y = W_s X for weights whose aligned groups of 4 columns
 // keep at most 2 (n = 1, or n = 2 with m % 4 == 0), whatever rows share a
 // pattern: group layouts with any g and the paper's chunked layout alike, on
-// gfx950's sparse matrix instructions v_smfmac_f32_16x16x64_{f16,bf16}.
+// gfx950's sparse matrix instructions v_smfmac_f32_16x16x64_f16.
 //
 // Two kernels.  k_sp_prepare / k_sp_prepare_chunked write the weight once per
 // call as a stream of instruction operands ("weight stream") in scratch
@@ -32,12 +32,15 @@
 // differs by less than kk 2^-20 in scaled units on top of the roundings above
 // (every product at most 2^15 2^-36 for either operand): at least kk in
 // magnitude, that is within 2^-20 of itself; below, it is summed again.  With
-// entries N(0, 1) a token in 10^4 is wide and an output in 10^6 of it below kk.
+// entries N(0, 1) a token of 768 columns in 10^5 is wide, and an output in 10^6
+// of it below kk.  (Rows of the chunked layout share a scale because a packed
+// row of a chunk holds blocks of many of its rows: the rows' own maxima would
+// take 37 000 LDS atomics a workgroup of the preparation.)
 //
 // These outputs, and those that are not finite, are summed again from the
-// packed weight in binary32 multiply-adds (sp_exact, sp_again), so that infinities and NaN in X
-// reach the outputs whose kept columns select them -- kept zeros among them --
-// and no others.
+// packed weight in binary32 multiply-adds (sp_exact, sp_again), so that
+// infinities and NaN in X reach the outputs whose kept columns select them --
+// kept zeros among them -- and no others.
 //
 // Binary16.  One part, products exact in binary32, as the other binary16
 // kernels (and the same recomputation for results that are not finite).

@@ -1213,6 +1213,30 @@ def test_sparse_product_any_range(nmg, K, exp):
     print("[any range]", exp, {k: f"{v:.1e}" for k, v in worst.items()}, flush=True)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("M,N", [(1536, 4093), (2048, 4096), (1000, 4100)])   # 1 to 4 row tiles a wave
+def test_sparse_product_summed_again(nmg, M, N, dtype):
+    """Outputs summed again in large tiles: one token, a whole tile of tokens, one
+    row and (binary32) a wide range, the residual added to them as to the rest."""
+    K = 132
+    W = synth.normal((M, K), 995, 0.02, dtype)
+    X = synth.normal((K, N), 996, 1.0, dtype)
+    X[5, 1], X[130, N - 1] = float("nan"), float("inf")
+    X[::7, 256:384] = float("-inf")
+    if dtype == torch.float32:
+        X[64, 512:640], X[64, 700] = 2.0 ** 70, 2.0 ** 60
+        W[M // 2] *= 2.0 ** -70
+    v, idx, L = nmg.compress(W.to(DEV), 1, 4, 1)
+    mask, Wd = nmg.densify(torch.ones_like(v), idx, L).double(), nmg.densify(v, idx, L).double()
+    check_kept_only(lambda Z, k: nmg.spmm(v, idx, Z, L, k), X, L.C, mask, Wd, dtype, f"{M} x {N}")
+    R = synth.normal((M, N), 997, 1.0, dtype).to(DEV)
+    P, Y = nmg.spmm(v, idx, X.to(DEV), L, "sparse"), nmg.spmm_epilogue(v, idx, X.to(DEV), L, "add", R, "sparse")
+    torch.cuda.synchronize()
+    ref = nmg.add(P, R)
+    fin = torch.isfinite(ref)
+    assert torch.equal(fin, torch.isfinite(Y)) and torch.equal(ref[fin], Y[fin])
+
+
 # ---------------------------------------------------- the family AUTO takes
 
 NAMED = [
