@@ -343,7 +343,8 @@ __device__ __forceinline__ void sp_gather(const T *__restrict__ values, const ui
         typedef uint8_t IV __attribute__((ext_vector_type(2 * CH)));
         const T *v0 = vr + 2 * c0;
         const uint8_t *i0 = ir + 2 * c0;
-        if (n == 2 && c0 + CH <= C && (reinterpret_cast<uintptr_t>(v0) & (sizeof(T) * 2 * CH > 16 ? 15 : sizeof(TV) - 1)) == 0 &&
+        if (n == 2 && c0 + CH <= C &&
+            (reinterpret_cast<uintptr_t>(v0) & (sizeof(T) * 2 * CH > 16 ? 15 : sizeof(TV) - 1)) == 0 &&
             (reinterpret_cast<uintptr_t>(i0) & (2 * CH - 1)) == 0) {
             // two of every chunk, all of them there: whole vectors
             IV iv = *reinterpret_cast<const IV *>(i0);
@@ -442,7 +443,8 @@ __global__ __launch_bounds__(kSpPrep) void k_sp_prepare(const float *__restrict_
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int k = 0; k < 2; ++k) u[h][k] = reinterpret_cast<const u4 *>(row[h])[min(i + 64 * k, ldv / 4 - 1)];
+                for (int k = 0; k < 2; ++k)
+                    u[h][k] = reinterpret_cast<const u4 *>(row[h])[min(i + 64 * k, ldv / 4 - 1)];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1064,7 +1066,8 @@ __global__ __launch_bounds__(kSpThreads) void k_spmm_sp(SpScratch ws, SpPacked p
             for (int r = 0; r < 4; ++r) {
                 float y = acc[i][t][r];
                 if constexpr (PARTS == 2)
-                    y = __builtin_ldexpf(fmaf(low[i][t][r], kSpLowInv, y), -(sp_scale_exp(wc[r]) + sp_scale_exp(xc[t])));
+                    y = __builtin_ldexpf(fmaf(low[i][t][r], kSpLowInv, y),
+                                         -(sp_scale_exp(wc[r]) + sp_scale_exp(xc[t])));
                 doubt |= __ballot(!(fabsf(y) < __builtin_inff()));
                 *reinterpret_cast<T *>(ob + (4 * (lane >> 4) + r) * OPITCH + (16 * t + (lane & 15)) * ES) = (T)y;
             }
@@ -1259,8 +1262,8 @@ int spc_chunks(int S) {
 int64_t nmg_internal::sp_stream_bytes(nmg_dtype dtype, int64_t M, int64_t K, int64_t N, int chunk_m) {
     const bool f32 = dtype == NMG_F32;
     const int splits = sp_splits(M, K, N, f32 ? 2 : 1);
-    return sp_scale_offset(M, K, f32 ? 2 : 1) + sp_origin_bytes(M, K, f32 ? 2 : 1, chunk_m) + (splits > 1 ? splits * M * N * 4 : 0) +
-           (f32 ? 4 * (16 * sp_tiles(M) + N + sp_xparts(K) * N) : 0);
+    return sp_scale_offset(M, K, f32 ? 2 : 1) + sp_origin_bytes(M, K, f32 ? 2 : 1, chunk_m) +
+           (splits > 1 ? splits * M * N * 4 : 0) + (f32 ? 4 * (16 * sp_tiles(M) + N + sp_xparts(K) * N) : 0);
 }
 
 // 32-bit offsets along a row of X; every launch below 2^32 threads (HIP refuses
